@@ -73,9 +73,8 @@ typedef enum simsense_status {
  *                   matching (SGBM, Sec. VI-D: the Hamming distance between the pixels' local
  *                   regions): the Hamming costs summed over the block centred on the pixel,
  *                   block samples outside the image clamped to the edge.  SGBM keeps 16-bit
- *                   path values and requires bits * block_w * block_h + p2 <= 8191; it runs
- *                   the aggregation with one block per line block (the tuning is not used),
- *                   and is not available to batches or the learned path.
+ *                   path values and requires bits * block_w * block_h + p2 <= 8191; it does
+ *                   not use the tuning, and is not available to batches or the learned path.
  */
 typedef struct simsense_params {
     uint32_t struct_size;
@@ -319,9 +318,8 @@ int simsense_learned_compute(simsense_handle *h, simsense_net *net, const uint8_
 /* ------------------------------------------------------------------------
  * Batches (a project addition): many pairs of uneven sizes and disparity
  * ranges, as from many simulated cameras, computed by one graph launch.  Each
- * pass of the path runs once over every pair; the aggregation pass is a
- * persistent kernel that takes line blocks of all pairs from a queue, longest
- * first.  The batch owns per-pair scratch like a handle (simsense_scratch_bytes
+ * pass of the path runs once over every pair of a phase; the aggregation pass
+ * takes the line blocks of all of them, longest first.  The batch owns per-pair scratch like a handle (simsense_scratch_bytes
  * of each pair's parameters).
  * ---------------------------------------------------------------------- */
 typedef struct simsense_batch simsense_batch; /* opaque */
@@ -337,11 +335,13 @@ typedef struct simsense_pair {
 
 /* Launch shape of the batch kernels.
  *  horizontal_lanes  lanes that hold one horizontal scanline's disparity vector:
- *                    16, 32 or 64 (a quarter, half or whole wavefront), 0 = the
+ *                    16, 32 or 64 (a quarter, half or whole wavefront; fewer where
+ *                    that would leave less than two disparities per lane), 0 = the
  *                    default for each disparity range; pairs whose padded
  *                    disparity count it does not divide keep their default.
- *  blocks_per_cu     resident blocks per compute unit of the persistent
- *                    aggregation kernel, 1..8. */
+ *  blocks_per_cu     1..8.  Kept for callers that set it: the aggregation's blocks
+ *                    are taken largest first for every value, and how many are
+ *                    resident on a compute unit follows from their registers. */
 typedef struct simsense_batch_tuning {
     uint32_t struct_size;
     int32_t horizontal_lanes;
@@ -395,10 +395,9 @@ int simsense_batch_autotune(simsense_batch *b, const simsense_pair *pairs, int32
                             void *stream);
 
 /* Launch shape of one handle's aggregation pass (the results do not depend on
- * it).  Same struct as the batch tuning, with blocks_per_cu 0 meaning one
- * block per line block of work (a grid of all of them, in direction order) and
- * 1..8 a persistent grid of that many blocks per compute unit that takes line
- * blocks longest first.  Default: horizontal_lanes 0, blocks_per_cu 3.
+ * it).  Same struct as the batch tuning, with blocks_per_cu 0 meaning line
+ * blocks in direction order and 1..8 largest first.  Default: horizontal_lanes 0
+ * (by image size, disparities and paths), blocks_per_cu 3.
  * Synchronous (uploads the work list); returns SIMSENSE_ERR_INVALID_ARGUMENT
  * for values outside those ranges or a lane count that does not divide the
  * padded disparity count. */
@@ -415,8 +414,7 @@ int simsense_autotune(simsense_handle *h, const uint8_t *left, const uint8_t *ri
 /* For callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): simsense_compute without
  * a handle.  Same arguments and results as simsense_create + simsense_compute +
- * simsense_destroy with `params` (bit for bit: the same kernels, the aggregation
- * launched one block per line block), but the scratch lives in one static device
+ * simsense_destroy with `params` (bit for bit: the same kernels), but the scratch lives in one static device
  * array of SIMSENSE_NOALLOC_SCRATCH_BYTES per GPU, which the library holds from
  * its first call on that GPU until the process ends; the call allocates nothing.
  * Parameters whose scratch (simsense_scratch_bytes) exceeds it return

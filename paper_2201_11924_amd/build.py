@@ -32,8 +32,15 @@ FLAGS = [
 # Per-file additions.  The fused net inference keeps its MFMA accumulators in
 # the vector registers its epilogues read (the default places them in the
 # accumulation registers and copies every result across).
+# The aggregation's steps are serial chains with DPP moves, which need idle issue
+# slots after the instruction that makes their source: the ILP scheduler fills them
+# with other steps' independent work (the default one, after low register counts,
+# leaves 3 times the s_nops).
+_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 FILE_FLAGS = {
     "net_infer.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "sgbm.hip": _ILP,
+    **{f"agg_dpl{n}.hip": _ILP for n in (1, 2, 4, 6, 8, 12, 16)},
 }
 
 

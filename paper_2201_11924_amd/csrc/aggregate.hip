@@ -1,12 +1,10 @@
-// Host side of the aggregation pass: work layout and dispatch to the
+// Host side of the aggregation pass: its units and items, and dispatch to the
 // per-disparity-count instantiations (agg_dpl*.hip).
 #include <algorithm>
 
 #include "internal.h"
 
 namespace ss {
-
-constexpr int kChunkClocks = 16;  // clocks per census tile chunk (= lines of a row-sharing block)
 
 hipError_t launch_agg_dpl1(const AggregateArgs *a, const AggregateQueue *q, int grid, int hl, bool wide, hipStream_t s);
 hipError_t launch_agg_dpl2(const AggregateArgs *a, const AggregateQueue *q, int grid, int hl, bool wide, hipStream_t s);
@@ -31,6 +29,21 @@ hipError_t launch_agg(const AggregateArgs *a, const AggregateQueue *q, int grid,
     default: return hipErrorInvalidValue;
     }
 }
+
+int line_length(int dx, int dy, int l, int W, int H)
+{
+    if (dy == 0) return W;
+    if (dx == 0) return H;
+    if (l < W) return std::min(dx > 0 ? W - l : l + 1, H);
+    return std::min(W, H - 1 - (l - W));
+}
+
+// lines of one item of a unit
+int item_lines(const AggregateArgs &a, int unit, int hl)
+{
+    const int lanes = a.dy[unit] == 0 ? effective_lanes(a.Dpad, hl) : kLanesPerLine;
+    return 64 / lanes * kWavesPerItem / (a.pair[unit] ? 2 : 1);
+}
 }  // namespace
 
 bool horizontal_lanes_valid(int dpad, int hl)
@@ -38,63 +51,66 @@ bool horizontal_lanes_valid(int dpad, int hl)
     return (hl == 16 || hl == 32 || hl == 64) && dpad % hl == 0;
 }
 
-int aggregate_blocks(int dx, int dy, int W, int H, int hl)
+int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool pairs)
 {
-    if (dy == 0) {
-        const int lines = kBlock / hl;
-        return (H + lines - 1) / lines;
+    const int walks = pairs ? 2 * 2 + 3 * (num_paths - 2) : 2 * num_paths;  // twice the walks over the image
+    return (int64_t)W * H / 4 * walks / 2 * agg_step_cost(lane_disparities(dpad, kLanesPerLine), kLanesPerLine);
+}
+
+int default_lanes(int W, int dpad, int64_t total_work)
+{
+    constexpr int kSimds = 1024;
+    const int64_t row = (int64_t)W * agg_step_cost(lane_disparities(dpad, kLanesPerLine), kLanesPerLine);
+    const int64_t per_simd = total_work / kSimds;
+    return 10 * per_simd >= 16 * row ? 16 : 10 * per_simd >= 5 * row ? 32 : 64;
+}
+
+// Units.  Horizontal directions are units of their own (their lines are the longest
+// chains: walking them one and a half times would hold up the launch).  The cost
+// volume takes the last path buffer: pairs leave it free; otherwise the direction that
+// fills it runs after all others and replaces each cost by its path value (each is
+// read once, before it is overwritten), so the scratch stays one buffer per direction.
+void plan_aggregation(AggregateArgs &a, int num_paths, bool pairs, bool block, int hl, uint8_t *const *buffers)
+{
+    if (!block) a.cost = num_paths > 2 ? buffers[num_paths - 1] : nullptr;
+    a.nunits = 0;
+    for (int r = 0; r < num_paths; ++r) {
+        const bool pair = pairs && kPathDy[r] != 0;
+        if (pair && kPathDy[r] < 0) continue;  // stored with its opposite
+        const int u = a.nunits++;
+        a.dx[u] = kPathDx[r];
+        a.dy[u] = kPathDy[r];
+        a.pair[u] = pair;
+        a.out[u] = buffers[u];
     }
-    const int top = (W + kChunkClocks - 1) / kChunkClocks;
-    if (dx == 0) return top;
-    return top + (H - 1 + kChunkClocks - 1) / kChunkClocks;
-}
-
-int aggregate_block_clocks(int dx, int dy, int blk, int W, int H, int hl)
-{
-    if (dy == 0) return W;
-    const int top = (W + kChunkClocks - 1) / kChunkClocks;
-    if (dx == 0) return H;
-    if (blk < top) {
-        const int g0 = blk * kChunkClocks, nvalid = std::min(kChunkClocks, W - g0);
-        const int lfirst = dx > 0 ? W - g0 : g0 + 1;
-        const int llast = dx > 0 ? W - (g0 + nvalid - 1) : g0 + nvalid;
-        return std::min(std::max(lfirst, llast), H);
+    a.last_first = a.out[a.nunits - 1] == a.cost ? a.nunits - 1 : a.nunits;
+    a.item_begin[0] = 0;
+    a.max_item_work = 1;
+    for (int u = 0; u < a.nunits; ++u) {
+        const int lines = item_lines(a, u, hl), n = (path_lines(a.dx[u], a.dy[u], a.W, a.H) + lines - 1) / lines;
+        a.item_begin[u + 1] = a.item_begin[u] + n;
+        for (int i = 0; i < n; ++i) a.max_item_work = std::max(a.max_item_work, aggregate_item_work(a, u, i, hl));
     }
-    const int j0 = (blk - top) * kChunkClocks, nvalid = std::min(kChunkClocks, H - 1 - j0);
-    int c = 0;
-    for (int i = 0; i < nvalid; ++i) c = std::max(c, i + std::min(W, H - j0 - i - 1));
-    return c;
 }
 
-int aggregate_block_work(int dx, int dy, int blk, int W, int H, int hl, int dpad)
+int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl)
 {
-    const int cost = dy == 0 ? agg_step_cost(dpad / hl, hl) : agg_step_cost(dpad / kLanesPerLine, kLanesPerLine);
-    return aggregate_block_clocks(dx, dy, blk, W, H, hl) * cost;
-}
-
-namespace {
-__global__ void zero_counters_kernel(unsigned *c, int n)
-{
-    if ((int)threadIdx.x < n) c[threadIdx.x] = 0u;
-}
-}  // namespace
-
-hipError_t launch_zero_counters(unsigned *c, int n, hipStream_t s)
-{
-    if (n < 1 || n > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, c, n);
-    return hipGetLastError();
+    const int dx = a.dx[unit], dy = a.dy[unit], n = path_lines(dx, dy, a.W, a.H);
+    const int lines = item_lines(a, unit, hl), lanes = dy == 0 ? effective_lanes(a.Dpad, hl) : kLanesPerLine;
+    int len = 0;
+    for (int l = item * lines; l < std::min(n, (item + 1) * lines); ++l) len = std::max(len, line_length(dx, dy, l, a.W, a.H));
+    const int steps = a.pair[unit] ? 3 * len / 2 : len;  // of each wave, in a row
+    return steps * agg_step_cost(lane_disparities(a.Dpad, lanes), lanes);
 }
 
 hipError_t launch_aggregate(const AggregateArgs &a, bool wide, int hl, hipStream_t s)
 {
-    if (a.block_begin[a.ndirs] == 0) return hipSuccess;
-    return launch_agg(&a, nullptr, 0, a.Dpad, hl, wide, s);
+    return launch_agg(&a, nullptr, a.item_begin[a.last_first], a.Dpad, hl, wide, s);
 }
 
 hipError_t launch_aggregate_queue(const AggregateQueue &q, int dpad, bool wide, int hl, int grid, hipStream_t s)
 {
-    if (q.nitems == 0) return hipSuccess;
+    if (grid + q.nlast == 0) return hipSuccess;
     return launch_agg(nullptr, &q, grid, dpad, hl, wide, s);
 }
 

@@ -1,41 +1,47 @@
 // Semi-global path aggregation kernels (included by the per-disparity-count
-// translation units agg_dpl*.hip, which instantiate them in parallel builds).
+// translation units agg_dpl*.hip, which instantiate them in parallel builds,
+// and by sgbm.hip for the 16-bit block costs).
 //
 // Semi-global path aggregation (Sec. VI-D; the SGM recurrence of Hirschmueller,
 // which the paper cites):
 //   L_r(p,d) = C(p,d) + min(L_r(p-r,d), L_r(p-r,d+-1) + P1, m + P2) - m,
 //   m = min_k L_r(p-r,k),  C(p,d) = popcount(cL(p) ^ cR(p - d)).
 //
-// Every scanline of every direction is an independent sequence, so each one is
-// given to 16 lanes (one DPP row of a wave64) that hold its D-vector, dpl
-// consecutive disparities per lane.  A step of the recurrence is then:
-//   * the matching cost recomputed from census words held in LDS (XOR +
-//     popcount), so no cost volume is ever written;
-//   * the d-1 / d+1 neighbours from the lane's own registers, and at the lane
-//     edges through a row_shr / row_shl DPP move;
-//   * the path minimum m through a row_ror butterfly (4 DPP steps);
-// The lanes keep the un-normalised sums
+// Every scanline of every direction is an independent chain of steps.  A line's
+// D-vector is held by LPL lanes of one wave (16: one DPP row, so a wave runs four
+// lines), DPL consecutive disparities per lane, two disparities per register: the
+// values are integers far below 2^16, so packed 16-bit adds and minima give exactly
+// the 32-bit results at half the instructions.  Register j of a lane holds
+// disparities d0 + j and d0 + j + DPL/2, so the d-1 / d+1 neighbours of a register
+// are the neighbouring registers, and only the two edge registers take a DPP move.
+//
+// The lanes keep un-normalised sums
 //   U(p,d) = C(p,d) + min(U(p-r,d), U(p-r,d+-1) + P1, u + P2),  u = min_k U(p-r,k),
-// for which induction gives L_r(p,d) = U(p,d) - u exactly (the subtraction of m
-// in the recurrence only shifts every value of a step by the same amount), so a
-// step needs no normalisation pass: the stored byte is U - u, written straight
-// into its byte of the output word (SDWA destination select).  A line starts
-// from U = 0, u = 0, which yields L = C at its first pixel; U grows by at most
-// bits + P2 per pixel, so 32 bits hold it for any line of the image.
+// for which induction gives L_r(p,d) = U(p,d) - u exactly, so a step that stores
+// nothing needs no normalisation; U is brought back to U - u once per segment of
+// kSeg steps (16-bit block costs, whose sums grow faster, every step).  All values
+// stay below 0x7C00, where 16-bit patterns order the same as half floats and as
+// integers, so three-way minima use v_pk_minimum3_f16 (no value is ever a NaN
+// or changed by it).
 //
-// A 256-thread block owns 16 lines of one direction and advances them by one
-// "clock" at a time.  Lines are grouped so that at every clock the block's 16
-// pixels lie in one image row and 16 consecutive columns (vertical lines, and
-// diagonals entering through the top/bottom row), or all in one column of 16
-// consecutive rows (horizontal lines).  Diagonals entering through a side column
-// are started one clock apart so they also share a row.  The census words a
-// block needs for 16 clocks are then a 16 x (Dpad + 31) word tile: it is loaded
-// from global memory while the previous 16 clocks are computed from the other
-// half of a double-buffered LDS tile, so the scanline loop waits on global
-// memory only once per 16 steps.
+// No LDS; a wave owns its lines alone, or shares them with one other (below).
 //
-// Each direction writes its path values (<= bits + P2 <= 255) as bytes into a
-// buffer of its own, d fastest; the selection pass sums the directions.
+// Two kinds of unit:
+//  * single: one direction, its path values stored as bytes, one buffer per
+//    direction.  The horizontal directions run this way from the census words
+//    (a lane's right words slide by one column per step, so a segment of 8 steps
+//    needs 8 new words per lane: four 16-byte loads in all).
+//  * pair: a direction and its opposite, whose lines are the same pixels; the SUM of
+//    both path values is stored, so that one byte per pixel and disparity is written,
+//    and read by the selection, instead of two (both passes are bound by that
+//    traffic: stores alone reach 4.1 TB/s on this GPU).  The price is a third walk of
+//    arithmetic (run_pair).  Needs sums of two path values to fit a byte:
+//    bits + P2 <= 127.
+// Vertical and diagonal units read the matching costs from a volume of bytes that
+// cost_kernel wrote (1 byte per pixel and disparity, in the path buffers' layout):
+// recomputing them from the census words costs 4.7 SIMD cycles more per disparity
+// and step than unpacking a byte.  Costs where x - d < 0 are `bits`, and 255 where
+// d >= D, so the steps need no border case.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -47,16 +53,34 @@ namespace ss {
 
 namespace {
 
-// the neighbour value of a disparity outside the line (the identity of min: the
-// neighbour term min(v(d-1), v(d+1)) then takes the one neighbour that exists)
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr uint32_t kPadCost = 0x01000000u;  // cost of the padding disparities >= D
-constexpr int kChunk = 16;                  // clocks per LDS tile (= lines per block)
-static_assert(kChunk == kLinesPerBlock, "one tile slot per line");
+// ---------------------------------------------------------------- small pieces
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// the neighbour value of a disparity outside the line: above every real value
+// plus P1, and the largest pattern that is a finite half float
+constexpr uint32_t kNone = 0x7BFF7BFFu;
 
 // DPP controls (GFX9 encoding)
 constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111;
 constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
+constexpr int kWaveShl1 = 0x130, kWaveShr1 = 0x138;
+
+__device__ __forceinline__ u16x2_t h2(uint32_t v) { return __builtin_bit_cast(u16x2_t, v); }
+__device__ __forceinline__ uint32_t w1(u16x2_t v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) { return w1(h2(a) + h2(b)); }
+__device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) { return w1(h2(a) - h2(b)); }
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) { return w1(__builtin_elementwise_min(h2(a), h2(b))); }
+__device__ __forceinline__ uint32_t pk_min3(uint32_t a, uint32_t b, uint32_t c)
+{
+    const f16x2_t m = __builtin_elementwise_minimum(__builtin_bit_cast(f16x2_t, a), __builtin_bit_cast(f16x2_t, b));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(m, __builtin_bit_cast(f16x2_t, c)));
+}
+// a 16-bit value in both halves
+__device__ __forceinline__ uint32_t both(uint32_t v) { return w1(u16x2_t{(uint16_t)v, (uint16_t)v}); }
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_mov(uint32_t old, uint32_t v)
@@ -67,53 +91,82 @@ __device__ __forceinline__ uint32_t dpp_mov(uint32_t old, uint32_t v)
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_rot(uint32_t v)
 {
-    // a row rotation reads a valid lane for every lane, so no old value is needed
+    // (the caller replaces what lanes without a source receive, if there are any)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
 }
 
-// minimum over the 16 lanes of a DPP row, returned in every lane of the row
-__device__ __forceinline__ uint32_t row_min(uint32_t v)
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p)
 {
-    v = min(v, dpp_rot<kRowRor8>(v));
-    v = min(v, dpp_rot<kRowRor4>(v));
-    v = min(v, dpp_rot<kRowRor2>(v));
-    v = min(v, dpp_rot<kRowRor1>(v));
-    return v;
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (T *)(((uint64_t)hi << 32) | lo);
 }
 
-constexpr int kWaveShl1 = 0x130, kWaveShr1 = 0x138;
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
-// Cross-lane pieces of a line that spans LPL lanes (16: one DPP row, 32: half a
-// wave, 64: the whole wave).  Lanes hold consecutive disparity blocks.
-template <int LPL>
+// buffer resource word 3 for raw byte buffers (GFX9 family); offsets at or past
+// the size are dropped (stores) or read as zero (loads): a lane off its line passes
+// kOff instead of branching
+constexpr int kBufferWord3 = 0x00020000;
+constexpr uint32_t kOff = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t open_buffer(const void *base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7FFFFFFF, kBufferWord3);
+}
+
+// Cache policy of the path-value stores: non-temporal (NT).  Only the selection
+// reads them back; stored with the default policy they leave the last-level caches
+// full of dirty lines whose write-back then competes with the selection's reads
+// (measured on the 8-buffer form: selection 241 -> 185 us).
+constexpr int kStoreAux = 2;
+
+// ---------------------------------------------------------------- lanes of a line
+// LPL lanes of which the first ACTIVE hold the line's disparities (the others
+// idle: nothing they hold reaches an active lane)
+template <int LPL, int ACTIVE>
 struct LineOps {
-    // value of the previous lane (lane 0 of the line gets kNone)
-    static __device__ __forceinline__ uint32_t from_prev(uint32_t v, bool first)
+    // value of the previous / next lane (the line's end lanes get kNone)
+    static __device__ __forceinline__ uint32_t from_prev(uint32_t v, int lane)
     {
-        if constexpr (LPL == 16) {
-            return dpp_mov<kRowShr1>(kNone, v);
-        } else {
-            const uint32_t r = dpp_mov<kWaveShr1>(kNone, v);
-            return LPL == 32 && first ? kNone : r;
+        if constexpr (LPL == 16) return dpp_mov<kRowShr1>(kNone, v);
+        else if constexpr (LPL == 64) return dpp_mov<kWaveShr1>(kNone, v);
+        else {
+            const uint32_t r = dpp_rot<kWaveShr1>(v);  // (every lane takes part in the move)
+            return lane == 0 ? kNone : r;
         }
     }
-    // value of the next lane (the line's last lane gets kNone)
-    static __device__ __forceinline__ uint32_t from_next(uint32_t v, bool last)
+    static __device__ __forceinline__ uint32_t from_next(uint32_t v, int lane)
     {
-        if constexpr (LPL == 16) {
-            return dpp_mov<kRowShl1>(kNone, v);
-        } else {
-            const uint32_t r = dpp_mov<kWaveShl1>(kNone, v);
-            return LPL == 32 && last ? kNone : r;
+        if constexpr (LPL == 16 && ACTIVE == LPL) return dpp_mov<kRowShl1>(kNone, v);
+        else if constexpr (LPL == 64 && ACTIVE == LPL) return dpp_mov<kWaveShl1>(kNone, v);
+        else {
+            const uint32_t r = dpp_rot<LPL == 16 ? kRowShl1 : kWaveShl1>(v);
+            return lane == ACTIVE - 1 ? kNone : r;
         }
     }
-    // minimum over the line's lanes, in every lane of the line: the DPP-row
-    // minimum, then rows exchanged in pairs (permlane16 swap: row 0 with row 1,
-    // row 2 with row 3) and, for a whole-wave line, halves exchanged (permlane32
-    // swap); a swap of a value with itself hands every lane its partner's value
-    static __device__ __forceinline__ uint32_t line_min(uint32_t v)
+    // minimum over the line's lanes, in every lane of the line: a DPP row's minimum
+    // by rotations, then rows exchanged in pairs (permlane16 swap) and, for a
+    // whole-wave line, halves (permlane32 swap)
+    static __device__ __forceinline__ uint32_t line_min(uint32_t v, int lane)
     {
-        v = row_min(v);
+        if constexpr (ACTIVE < LPL) v = lane < ACTIVE ? v : 0xFFFFu;
+        v = min(v, dpp_rot<kRowRor8>(v));
+        v = min(v, dpp_rot<kRowRor4>(v));
+        v = min(v, dpp_rot<kRowRor2>(v));
+        v = min(v, dpp_rot<kRowRor1>(v));
         if constexpr (LPL >= 32) {
             const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
             v = min((uint32_t)s[0], (uint32_t)s[1]);
@@ -126,6 +179,472 @@ struct LineOps {
     }
 };
 
+// ---------------------------------------------------------------- a lane's values
+// DPL values of a lane in memory (bytes, or 16-bit words for V16) and in N packed
+// registers.  Bytes: register j = disparities (j, j + N); 16-bit: (2j, 2j + 1), the
+// order in memory.  DPL = 1 uses the low half only.
+template <int DPL, bool V16>
+struct Lane {
+    static_assert(DPL <= 2 || DPL % 4 == 0, "two disparities per register, whole words in memory");
+    static constexpr int N = DPL == 1 ? 1 : DPL / 2;
+    static constexpr int kBytes = DPL * (V16 ? 2 : 1);
+    static constexpr int NW = (kBytes + 3) / 4;  // words in memory
+
+    static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t off, int soff, uint32_t (&w)[NW])
+    {
+        if constexpr (kBytes == 1) {
+            w[0] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rs, off, soff, 0);
+        } else if constexpr (kBytes == 2) {
+            w[0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, soff, 0);
+        } else {
+            static_assert(kBytes % 4 == 0, "");
+            static_for<(NW + 3) / 4>([&](auto ic) {
+                constexpr int i = 4 * decltype(ic)::value, n = NW - i < 4 ? NW - i : 4;
+                if constexpr (n == 1) {
+                    w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * i, soff, 0);
+                } else if constexpr (n == 2) {
+                    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 4 * i, soff, 0);
+                    w[i] = v[0]; w[i + 1] = v[1];
+                } else if constexpr (n == 3) {
+                    const u32x3_t v = __builtin_amdgcn_raw_buffer_load_b96(rs, off + 4 * i, soff, 0);
+                    w[i] = v[0]; w[i + 1] = v[1]; w[i + 2] = v[2];
+                } else {
+                    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 4 * i, soff, 0);
+                    w[i] = v[0]; w[i + 1] = v[1]; w[i + 2] = v[2]; w[i + 3] = v[3];
+                }
+            });
+        }
+    }
+
+    template <int AUX>
+    static __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t rs, uint32_t off, int soff, const uint32_t (&w)[NW])
+    {
+        if constexpr (kBytes == 1) {
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)w[0], rs, off, soff, AUX);
+        } else if constexpr (kBytes == 2) {
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w[0], rs, off, soff, AUX);
+        } else {
+            static_for<(NW + 3) / 4>([&](auto ic) {
+                constexpr int i = 4 * decltype(ic)::value, n = NW - i < 4 ? NW - i : 4;
+                // (stores of more than 8 bytes take the whole offset in the address
+                // register: the next instructions may overwrite their data registers
+                // while a busy memory pipe still reads them, and the compiler keeps the
+                // wait states for that only where the scalar offset is a constant;
+                // measured wrong values at 1920x1080, D = 256 with a register there)
+                if constexpr (n == 1) __builtin_amdgcn_raw_buffer_store_b32(w[i], rs, off + 4 * i, soff, AUX);
+                else if constexpr (n == 2)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{w[i], w[i + 1]}, rs, off + 4 * i, soff, AUX);
+                else if constexpr (n == 3)
+                    __builtin_amdgcn_raw_buffer_store_b96(u32x3_t{w[i], w[i + 1], w[i + 2]}, rs, off + soff + 4 * i, 0, AUX);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{w[i], w[i + 1], w[i + 2], w[i + 3]}, rs,
+                                                           off + soff + 4 * i, 0, AUX);
+            });
+        }
+    }
+
+    // register j from the loaded words
+    template <int J>
+    static __device__ __forceinline__ uint32_t get(const uint32_t (&w)[NW])
+    {
+        if constexpr (V16 || DPL == 1) {
+            return w[J];
+        } else {
+            constexpr int a = J, b = J + N;
+            constexpr uint32_t sel = (uint32_t)(a % 4) | 0x0C00u | ((uint32_t)(4 + b % 4) << 16) | 0x0C000000u;
+            return __builtin_amdgcn_perm(w[b / 4], w[a / 4], sel);
+        }
+    }
+
+    // the words of N registers whose halves are below 256 (bytes beyond stay inside
+    // their own halves: every byte is selected, never shifted in)
+    static __device__ __forceinline__ void pack(const uint32_t (&r)[N], uint32_t (&w)[NW])
+    {
+        if constexpr (V16 || DPL == 1) {
+            static_for<N>([&](auto j) { w[j] = r[j]; });
+        } else if constexpr (DPL == 2) {
+            w[0] = __builtin_amdgcn_perm(r[0], r[0], 0x0C0C0200u);
+        } else {
+            static_assert(N % 2 == 0, "");
+            uint32_t p[N / 2];  // lo bytes of registers 2i, 2i + 1, then their hi bytes
+            static_for<N / 2>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                p[i] = __builtin_amdgcn_perm(r[2 * i + 1], r[2 * i], 0x06020400u);
+            });
+            if constexpr (NW == 1) {
+                w[0] = p[0];
+            } else {
+                static_for<NW>([&](auto kc) {  // 16-bit pieces 2k, 2k + 1: the low halves of p, then the high halves
+                    constexpr int a = 2 * decltype(kc)::value, b = a + 1, M = N / 2;
+                    constexpr uint32_t sa = a < M ? 0x0100u : 0x0302u, sb = b < M ? 0x05040000u : 0x07060000u;
+                    w[kc] = __builtin_amdgcn_perm(p[b % M], p[a % M], sa | sb);
+                });
+            }
+        }
+    }
+};
+
+// One line's state and one step of the recurrence.
+template <int DPL, int LPL, int ACTIVE, bool V16>
+struct Line {
+    using LV = Lane<DPL, V16>;
+    using LO = LineOps<LPL, ACTIVE>;
+    static constexpr int N = LV::N;
+    uint32_t U[N];  // un-normalised sums (V16: normalised path values)
+    uint32_t u;     // the line's minimum of U, in the low half
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) U[j] = 0;
+        u = 0;
+    }
+
+    // U becomes C + min(...): add(j, t) returns t plus the costs of register j
+    template <typename ADD>
+    __device__ __forceinline__ void step(uint32_t p1, uint32_t p2, int lane, ADD add)
+    {
+        uint32_t P[N], low[N], up[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) P[j] = pk_add(U[j], p1);
+        const uint32_t prev = LO::from_prev(P[N - 1], lane), next = LO::from_next(P[0], lane);
+        if constexpr (DPL == 1) {
+            low[0] = prev;
+            up[0] = next;
+        } else if constexpr (V16) {  // register j = (2j, 2j + 1)
+#pragma unroll
+            for (int j = 0; j < N; ++j) low[j] = __builtin_amdgcn_alignbit(P[j], j > 0 ? P[j - 1] : prev, 16);
+#pragma unroll
+            for (int j = 0; j < N; ++j) up[j] = j < N - 1 ? low[j + 1] : __builtin_amdgcn_alignbit(next, P[j], 16);
+        } else {  // register j = (j, j + N)
+            low[0] = __builtin_amdgcn_alignbit(P[N - 1], prev, 16);
+#pragma unroll
+            for (int j = 1; j < N; ++j) low[j] = P[j - 1];
+#pragma unroll
+            for (int j = 0; j < N - 1; ++j) up[j] = P[j + 1];
+            up[N - 1] = __builtin_amdgcn_alignbit(next, P[0], 16);
+        }
+        const uint32_t cap = pk_add(both(u), p2);
+        const uint32_t ub = both(u);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            uint32_t t = pk_min(pk_min3(U[j], low[j], up[j]), cap);
+            if constexpr (V16) t = pk_sub(t, ub);
+            low[j] = t;
+        }
+        static_for<N>([&](auto j) { U[j] = add(j, low[j]); });
+        uint32_t m = U[0];
+        if constexpr (N % 2 == 0) m = pk_min(m, U[1]);
+#pragma unroll
+        for (int j = N % 2 == 0 ? 2 : 1; j < N; j += 2) m = pk_min3(m, U[j], U[j + 1]);
+        m = DPL == 1 ? m & 0xFFFFu : min(m & 0xFFFFu, m >> 16);
+        u = LO::line_min(m, lane);
+    }
+
+    // brings U back to U - u
+    __device__ __forceinline__ void rebase()
+    {
+        if constexpr (!V16) {
+            const uint32_t ub = both(u);
+#pragma unroll
+            for (int j = 0; j < N; ++j) U[j] = pk_sub(U[j], ub);
+            u = 0;
+        }
+    }
+    // what a step that starts from minimum u adds to a path value
+    static __device__ __forceinline__ uint32_t base(uint32_t u) { return V16 ? 0u : u; }
+};
+
+// ---------------------------------------------------------------- geometry
+// Lines of a direction: first pixel and length of line l.
+__device__ __forceinline__ void line_start(int dx, int dy, int l, int W, int H, int &x, int &y, int &len)
+{
+    if (dy == 0) {
+        x = dx > 0 ? 0 : W - 1;
+        y = l;
+        len = W;
+    } else if (dx == 0) {
+        x = l;
+        y = dy > 0 ? 0 : H - 1;
+        len = H;
+    } else if (l < W) {  // enters through the top / bottom row
+        x = l;
+        y = dy > 0 ? 0 : H - 1;
+        len = min(dx > 0 ? W - l : l + 1, H);
+    } else {  // enters through the side column
+        const int j = l - W;
+        x = dx > 0 ? 0 : W - 1;
+        y = dy > 0 ? j + 1 : H - 2 - j;
+        len = min(W, H - 1 - j);
+    }
+}
+
+// A wave's lines: the first pixel (elements of the image) all offsets count from,
+// each lane's byte offset from it, its line's length, the shortest and longest
+// length, and the image step per clock.  Lanes past the direction's last line repeat
+// that line (they load and store the same values at the same places, in lockstep).
+struct WaveLines {
+    int64_t base;
+    uint32_t off;
+    int len, minlen, maxlen, step;
+};
+
+__device__ __forceinline__ int line_count(int dx, int dy, int W, int H) { return dy == 0 ? H : dx == 0 ? W : W + H - 1; }
+
+// (wave: a running number over the direction's waves, below the last line's)
+template <int LPL, int DPADB>
+__device__ __forceinline__ WaveLines wave_lines(int dx, int dy, int wave, int W, int H, int lane_bytes)
+{
+    constexpr int kLines = 64 / LPL;
+    const int nlines = line_count(dx, dy, W, H);
+    WaveLines g;
+    g.minlen = 1 << 30;
+    g.maxlen = 0;
+    g.base = (int64_t)1 << 60;
+    int64_t mine = 0;
+    const int sub = (int)(threadIdx.x & 63) / LPL;
+#pragma unroll
+    for (int i = 0; i < kLines; ++i) {
+        int x, y, len;
+        line_start(dx, dy, min(wave * kLines + i, nlines - 1), W, H, x, y, len);
+        const int64_t at = (int64_t)y * W + x;
+        g.base = at < g.base ? at : g.base;
+        g.minlen = min(g.minlen, len);
+        g.maxlen = max(g.maxlen, len);
+        if (sub == i) {
+            mine = at;
+            g.len = len;
+        }
+    }
+    g.off = lane_bytes < DPADB ? (uint32_t)(mine - g.base) * DPADB + lane_bytes : kOff;  // idle lanes: nowhere
+    g.step = dy * W + dx;
+    return g;
+}
+
+// Issue priority from a wave's remaining work relative to the launch's largest:
+// the waves sharing a SIMD then drain in order of remaining work and finish
+// together instead of the longest running on alone.
+__device__ __forceinline__ void set_priority(int remaining, int max_work)
+{
+    if (remaining > max_work / 100 * 43) __builtin_amdgcn_s_setprio(3);
+    else if (remaining > max_work / 100 * 21) __builtin_amdgcn_s_setprio(2);
+    else if (remaining > max_work / 100 * 7) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+// The S pixels of a line from index q*S on, walked forwards or (back) backwards, in a
+// buffer of path-layout values: the resource of their first address in memory, and
+// each step's scalar offset from it.
+struct Segment {
+    __amdgpu_buffer_rsrc_t rs;
+    int stride;  // bytes per pixel of the line in memory order (>= 0)
+    bool down;   // the walk runs against memory order
+};
+template <int S, int DPADB>
+__device__ __forceinline__ Segment segment(const uint8_t *buf, const WaveLines &g, int q, bool back)
+{
+    const bool neg = g.step < 0;
+    const int64_t first = g.base + (int64_t)(q * S + (neg ? S - 1 : 0)) * g.step;
+    return Segment{open_buffer(buf + first * DPADB), (neg ? -g.step : g.step) * DPADB, neg != back};
+}
+// offset of the walk's step s
+template <int S>
+__device__ __forceinline__ int at_step(const Segment &b, int s)
+{
+    return (b.down ? S - 1 - s : s) * b.stride;
+}
+// the line index of the walk's step s of segment q
+template <int S>
+__device__ __forceinline__ int index_of(int q, int s, bool back)
+{
+    return q * S + (back ? S - 1 - s : s);
+}
+
+// the costs of segment q, in walking order: all S pixels (WHOLE: the caller knows
+// that every line has them), or those that exist (the others read as zero cost,
+// which leaves a line's state before its first pixel as it is)
+template <bool WHOLE, int DPAD, int DPL, bool V16, int S>
+__device__ __forceinline__ void load_segment(const uint8_t *vol, const WaveLines &g, int q, bool back,
+                                             uint32_t (&w)[S][Lane<DPL, V16>::NW])
+{
+    using LV = Lane<DPL, V16>;
+    const Segment b = segment<S, DPAD * (V16 ? 2 : 1)>(vol, g, q, back);
+    static_for<S>([&](auto s) {
+        LV::load(b.rs, WHOLE || (uint32_t)index_of<S>(q, s, back) < (uint32_t)g.len ? g.off : kOff, at_step<S>(b, s), w[s]);
+    });
+}
+
+// Costs are loaded in segments of 4 steps into a ring of 4 segments, 12 steps
+// ahead: vector loads and stores complete in issue order, so waiting for a load
+// also waits for the stores issued before it, and stores take longer.  The ring is
+// unrolled (16 steps a block, each slot in fixed registers); longer rings cost more
+// instruction cache than they gain (32 steps a block: 54 -> 72 us at 320x240).
+constexpr int kLoadSeg = 4, kLoadRing = 4;
+
+// ---------------------------------------------------------------- one direction from the cost volume
+template <int DPAD, int DPL, int LPL, bool V16>
+__device__ __forceinline__ void run_single(const uint8_t *vol, uint8_t *out, const WaveLines &g, uint32_t p1, uint32_t p2,
+                                           int cost, int max_work)
+{
+    using LV = Lane<DPL, V16>;
+    using L = Line<DPL, LPL, DPAD / DPL, V16>;
+    constexpr int S = kLoadSeg, R = kLoadRing, kDpadB = DPAD * (V16 ? 2 : 1), N = LV::N;
+    const int lane = (int)threadIdx.x % LPL;
+    L line;
+    line.clear();
+    const int nseg = (g.maxlen + S - 1) / S;
+    uint32_t ring[R][S][LV::NW];
+    auto block = [&](auto wc, int k) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        static_for<R>([&](auto r) {
+            if (!WHOLE && k + r >= nseg) return;
+            load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, k + r + R - 1, false, ring[(r + R - 1) % R]);
+            const Segment o = segment<S, kDpadB>(out, g, k + r, false);
+            static_for<S>([&](auto s) {
+                const uint32_t ub = both(L::base(line.u));
+                line.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(ring[r][s])); });
+                uint32_t v[N], m[LV::NW];
+#pragma unroll
+                for (int j = 0; j < N; ++j) v[j] = V16 ? line.U[j] : pk_sub(line.U[j], ub);
+                LV::pack(v, m);
+                LV::template store<kStoreAux>(o.rs, WHOLE || (k + r) * S + s < g.len ? g.off : kOff, at_step<S>(o, s), m);
+            });
+        });
+        line.rebase();
+    };
+    static_for<R - 1>([&](auto r) { load_segment<false, DPAD, DPL, V16, S>(vol, g, r, false, ring[r]); });
+    for (int k = 0; k < nseg; k += R) {
+        set_priority((g.maxlen - k * S) * cost, max_work);
+        if ((k + 2 * R - 1) * S <= g.minlen) block(std::true_type{}, k);
+        else block(std::false_type{}, k);
+    }
+}
+
+// ---------------------------------------------------------------- a direction and its opposite
+// Two waves share a group of lines: wave `back` 0 walks them forwards, 1 backwards.
+// Each first walks its own half without storing values, only its state before every
+// segment of SUMS steps (in the slot of the segment's first pixel of `out`); after a
+// barrier it walks on through the other's half: there, per segment, it recomputes the
+// other direction's values from the state the other wave stored, keeps them in
+// registers, walks the segment itself and stores the sums.  Three steps of work per
+// pixel in all, one and a half per wave in a row.
+// (live: the wave has lines; all waves of a block meet at the barrier)
+template <int DPAD, int DPL, int LPL, bool V16, int SUMS>
+__device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const WaveLines &g, bool live, bool back,
+                                         uint32_t p1, uint32_t p2, int cost, int max_work)
+{
+    using LV = Lane<DPL, V16>;
+    using L = Line<DPL, LPL, DPAD / DPL, V16>;
+    constexpr int kDpadB = DPAD * (V16 ? 2 : 1), N = LV::N, NW = LV::NW;
+    const int lane = (int)threadIdx.x % LPL;
+    const int nseg = (g.maxlen + SUMS - 1) / SUMS;
+    const int half = back ? nseg - nseg / 2 : nseg / 2;  // segments of the wave's own half
+    L mine;
+    mine.clear();
+    if (live) {
+        constexpr int S = kLoadSeg, R = kLoadRing, kPer = SUMS / S;
+        static_assert(SUMS % S == 0 && (R * S) % SUMS == 0, "states fall on load segments");
+        uint32_t ring[R][S][NW];
+        const int nall = nseg * kPer, nload = half * kPer;
+        auto seg = [&](int k) { return back ? nall - 1 - k : k; };  // load segment k of the walk
+        auto block = [&](auto wc, int k) {
+            constexpr bool WHOLE = decltype(wc)::value;
+            static_for<R>([&](auto r) {
+                if (!WHOLE && k + r >= nload) return;
+                load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, seg(k + r + R - 1), back, ring[(r + R - 1) % R]);
+                static_for<S>([&](auto s) {
+                    mine.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(ring[r][s])); });
+                });
+                if constexpr ((r + 1) * S % SUMS == 0) {
+                    // the state before the walk's next segment.  (Values of padding
+                    // disparities can exceed a byte: 255 is still above every real
+                    // value plus P2 - P1, so the clamp changes no real one.)
+                    const uint32_t ub = both(mine.u);
+                    uint32_t v[N], m[NW];
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        v[j] = pk_sub(mine.U[j], ub);
+                        if constexpr (!V16) {
+                            mine.U[j] = v[j];
+                            v[j] = pk_min(v[j], 0x00FF00FFu);
+                        }
+                    }
+                    if constexpr (!V16) mine.u = 0;
+                    LV::pack(v, m);
+                    const int next = (k + r + 1) / kPer, q = back ? nseg - 1 - next : next;
+                    const Segment o = segment<SUMS, kDpadB>(out, g, q, false);
+                    LV::template store<0>(o.rs, next < half && (WHOLE || q * SUMS < g.len) ? g.off : kOff, at_step<SUMS>(o, 0), m);
+                }
+            });
+        };
+        static_for<R - 1>([&](auto r) { load_segment<false, DPAD, DPL, V16, S>(vol, g, seg(r), back, ring[r]); });
+        for (int k = 0; k < nload; k += R) {
+            set_priority((3 * nseg * SUMS / 2 - k * S) * cost, max_work);
+            const int ahead = k + 2 * R - 2;  // the block's last load
+            if (k + R <= nload && ahead < nall && (max(seg(k), seg(ahead)) + 1) * S <= g.minlen) block(std::true_type{}, k);
+            else block(std::false_type{}, k);
+        }
+    }
+    // the states are in memory before the other wave reads them
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (!live) return;
+
+    constexpr int S = SUMS;
+    auto seg = [&](int k) { return back ? nseg - 1 - k : k; };  // segment k of the walk
+    uint32_t ring[2][S][NW], states[2][NW];
+    auto load = [&](auto wc, int k, uint32_t (&w)[S][NW], uint32_t (&m)[NW]) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        if (!WHOLE && k >= nseg) return;
+        const int q = seg(k);
+        load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, q, back, w);
+        // (the other wave starts from zeros in its first segment, this walk's last)
+        const Segment o = segment<S, kDpadB>(out, g, q, false);
+        LV::load(o.rs, WHOLE || (k < nseg - 1 && q * S < g.len) ? g.off : kOff, at_step<S>(o, 0), m);
+    };
+    auto sums = [&](auto wc, int k, const uint32_t (&w)[S][NW], const uint32_t (&state)[NW]) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        L other;
+        uint32_t F[S][N], fu[S];
+        static_for<N>([&](auto j) { other.U[j] = LV::template get<j>(state); });
+        other.u = 0;  // a state is normalised
+        static_for<S>([&](auto sc) {
+            constexpr int s = S - 1 - decltype(sc)::value;
+            fu[s] = L::base(other.u);
+            other.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(w[s])); });
+#pragma unroll
+            for (int j = 0; j < N; ++j) F[s][j] = other.U[j];
+        });
+        const int q = seg(k);
+        const Segment o = segment<S, kDpadB>(out, g, q, back);
+        static_for<S>([&](auto s) {
+            const uint32_t sub = both(L::base(mine.u) + fu[s]);
+            mine.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(w[s])); });
+            uint32_t v[N], m[NW];
+#pragma unroll
+            for (int j = 0; j < N; ++j) v[j] = V16 ? pk_add(mine.U[j], F[s][j]) : pk_sub(pk_add(mine.U[j], F[s][j]), sub);
+            LV::pack(v, m);
+            LV::template store<kStoreAux>(o.rs, WHOLE || index_of<S>(q, s, back) < g.len ? g.off : kOff, at_step<S>(o, s), m);
+        });
+        mine.rebase();
+    };
+    auto block = [&](auto wc, int k) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        load(wc, k + 1, ring[1], states[1]);
+        sums(wc, k, ring[0], states[0]);
+        if (!WHOLE && k + 1 >= nseg) return;
+        load(wc, k + 2, ring[0], states[0]);
+        sums(wc, k + 1, ring[1], states[1]);
+    };
+    load(std::false_type{}, half, ring[0], states[0]);
+    for (int k = half; k < nseg; k += 2) {
+        set_priority(2 * (nseg - k) * S * cost, max_work);
+        if (k + 2 < nseg - 1 && (max(seg(k), seg(k + 2)) + 1) * S <= g.minlen) block(std::true_type{}, k);
+        else block(std::false_type{}, k);
+    }
+}
+
+// ---------------------------------------------------------------- horizontal lines from census words
 template <bool WIDE>
 struct CensusWord;
 template <>
@@ -139,753 +658,335 @@ struct CensusWord<true> {
     static __device__ __forceinline__ uint32_t hamming(T a, T b) { return __popcll(a ^ b); }
 };
 
-// Path-value stores go through global-address-space pointers: a generic (flat)
-// store would also count against the LDS counter and make every wait for a
-// census read from LDS wait for the outstanding stores as well.
-template <typename T>
-__device__ __forceinline__ void gstore(uint8_t *p, T v)
+// S consecutive words from word `at` of a census map, 16 bytes per load.  Words outside the map's rows are other words of the scratch
+// (they only reach disparities with x - d < 0 or pixels past the line's end); the
+// caller keeps `at` >= 0.
+template <bool WIDE, int S>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, int at, typename CensusWord<WIDE>::T (&w)[S])
 {
-    *(__attribute__((address_space(1))) T *)p = v;
-}
-// (native vector types: HIP's uint2/uint4 classes assign through a generic
-// `this` pointer, which would turn the store back into a flat one)
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
-
-// Cache policy of the path-value stores: non-temporal (NT).  The pass writes
-// ~1 GB that only the selection pass reads back; stored with the default policy
-// it leaves the last-level caches full of dirty lines whose write-back then
-// competes with the selection's reads (measured: selection 241 -> 185 us after
-// a 1280x720 D=128 8-path pass, the aggregation itself unchanged).
-constexpr int kStoreAux = 2;
-
-
-// byte B of w = the low byte of a - b, written in place by the subtraction
-// itself (SDWA destination select; byte 0 clears the rest of the word, bytes
-// 1..3 keep it)
-__device__ __forceinline__ void put_byte(uint32_t &w, uint32_t a, uint32_t b, int B)
-{
-    if (B == 0)
-        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD"
-            : "=v"(w) : "v"(a), "v"(b));
-    else if (B == 1)
-        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
-            : "+v"(w) : "v"(a), "v"(b));
-    else if (B == 2)
-        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
-            : "+v"(w) : "v"(a), "v"(b));
-    else
-        asm("v_sub_u32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD"
-            : "+v"(w) : "v"(a), "v"(b));
-}
-
-// disparities packed per output word: 4 when dpl allows whole words, else
-// pairs (16-bit stores) or single bytes
-template <int DPL>
-__host__ __device__ constexpr int bytes_per_word()
-{
-    return DPL % 4 == 0 ? 4 : (DPL % 2 == 0 ? 2 : 1);
-}
-
-// The lane's dpl path values L = U - u as bytes at byte offset `off` of the
-// buffer rs (d0 .. d0 + dpl - 1 of one pixel).  Buffer stores take a 32-bit
-// offset, and one at or past the buffer's size is dropped by the hardware, so
-// a lane off its line passes such an offset instead of branching.
-template <int DPL>
-__device__ __forceinline__ void store_path(__amdgpu_buffer_rsrc_t rs, uint32_t off, const uint32_t (&U)[DPL], uint32_t u)
-{
-    constexpr int G = bytes_per_word<DPL>(), NW = DPL / G;
-    uint32_t w[NW];
-#pragma unroll
-    for (int k = 0; k < NW; ++k)
-#pragma unroll
-        for (int b = 0; b < G; ++b) put_byte(w[k], U[G * k + b], u, b);
-    if constexpr (G == 4) {
-        if constexpr (NW == 1) {
-            __builtin_amdgcn_raw_buffer_store_b32(w[0], rs, off, 0, kStoreAux);
-        } else if constexpr (NW == 2) {
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{w[0], w[1]}, rs, off, 0, kStoreAux);
-        } else if constexpr (NW == 3) {
-            // 12 bytes at a 4-byte-aligned offset: two stores of natural width
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{w[0], w[1]}, rs, off, 0, kStoreAux);
-            __builtin_amdgcn_raw_buffer_store_b32(w[2], rs, off + 8, 0, kStoreAux);
-        } else {
-            static_assert(NW == 4, "unsupported disparities per lane");
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{w[0], w[1], w[2], w[3]}, rs, off, 0, kStoreAux);
-        }
-    } else if constexpr (G == 2) {
-#pragma unroll
-        for (int k = 0; k < NW; ++k) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w[k], rs, off + 2 * k, 0, kStoreAux);
-    } else {
-#pragma unroll
-        for (int k = 0; k < NW; ++k) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)w[k], rs, off + k, 0, kStoreAux);
-    }
-}
-
-// store instructions store_path issues per step
-template <int DPL>
-__host__ __device__ constexpr int store_ops()
-{
-    return bytes_per_word<DPL>() == 4 ? (DPL == 12 ? 2 : 1) : DPL / bytes_per_word<DPL>();
-}
-
-// a buffer offset past every buffer: the store is dropped
-constexpr uint32_t kNoStore = 0x80000000u;
-
-// buffer resource word 3 for raw byte buffers (GFX9 family)
-constexpr int kBufferWord3 = 0x00020000;
-
-// s_waitcnt immediate that waits for vmcnt <= n and leaves the other counters
-// alone (GFX9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14])
-__host__ __device__ constexpr int vmcnt_encoding(int n)
-{
-    // counts above the 6-bit maximum wait for more than needed, which is safe
-    return n > 63 ? vmcnt_encoding(63) : (n & 0xF) | (0x7 << 4) | (0xF << 8) | (((n >> 4) & 0x3) << 14);
-}
-
-// dpl 16-bit values (the low halves of v) to consecutive u16 slots (global)
-template <int DPL>
-__device__ __forceinline__ void store_u16(uint16_t *dst, const uint32_t (&v)[DPL])
-{
-    uint8_t *p = (uint8_t *)dst;
-    if constexpr (DPL == 1) {
-        gstore(p, (uint16_t)v[0]);
-    } else {
-        constexpr int NW = DPL / 2;
-        uint32_t w[NW];
-#pragma unroll
-        for (int i = 0; i < NW; ++i) w[i] = (v[2 * i] & 0xFFFFu) | (v[2 * i + 1] << 16);
-        if constexpr (NW % 4 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 4) gstore(p + 4 * i, u32x4_t{w[i], w[i + 1], w[i + 2], w[i + 3]});
-        } else if constexpr (NW % 2 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 2) gstore(p + 4 * i, u32x2_t{w[i], w[i + 1]});
-        } else {
-#pragma unroll
-            for (int i = 0; i < NW; ++i) gstore(p + 4 * i, w[i]);
-        }
-    }
-}
-
-// dpl consecutive 16-bit values, widened to 32 bits
-template <int DPL>
-__device__ __forceinline__ void load_u16(const uint16_t *src, uint32_t (&v)[DPL])
-{
-    if constexpr (DPL == 1) {
-        v[0] = *src;
-    } else {
-        constexpr int NW = DPL / 2;
-        uint32_t w[NW];
-        const uint32_t *p = (const uint32_t *)src;
-        if constexpr (NW % 4 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 4) {
-                const uint4 q = *(const uint4 *)(p + i);
-                w[i] = q.x; w[i + 1] = q.y; w[i + 2] = q.z; w[i + 3] = q.w;
-            }
-        } else if constexpr (NW % 2 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 2) {
-                const uint2 q = *(const uint2 *)(p + i);
-                w[i] = q.x; w[i + 1] = q.y;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NW; ++i) w[i] = p[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-            v[2 * i] = w[i] & 0xFFFFu;
-            v[2 * i + 1] = w[i] >> 16;
-        }
-    }
-}
-
-// Geometry of one block of 16 lines of one direction.
-//  kind 0: horizontal; the 16 lines are rows r0..r0+15 and every line is at
-//          column xs + t*dx at clock t;
-//  kind 1: vertical, or diagonal entering through the top/bottom row ye: line i
-//          starts at column g0 + i; at clock t every line is in row ye + t*dy and
-//          line i in column g0 + t*dx + i;
-//  kind 2: diagonal entering through the side column xe: line i starts at row
-//          ye + dy*(j0 + i + 1) and runs one clock behind line i-1, so at clock t
-//          every line is in row ye + dy*(j0 + 1 + t).
-struct BlockGeom {
-    int kind, dx, dy;
-    int r0, g0, j0;
-    int xs, xe, ye;
-    int clocks;  // clocks the block runs
-    int nvalid;  // lines of the block that exist
-};
-
-__device__ __forceinline__ BlockGeom block_geometry(int dx, int dy, int blk, int W, int H, int hlines)
-{
-    BlockGeom g{};
-    g.dx = dx;
-    g.dy = dy;
-    g.ye = dy > 0 ? 0 : H - 1;
-    g.xe = dx > 0 ? 0 : W - 1;
-    if (dy == 0) {
-        g.kind = 0;
-        g.r0 = blk * hlines;
-        g.xs = dx > 0 ? 0 : W - 1;
-        g.clocks = W;
-        g.nvalid = min(hlines, H - g.r0);
-    } else {
-        const int top_blocks = (W + kChunk - 1) / kChunk;
-        if (dx == 0 || blk < top_blocks) {
-            g.kind = 1;
-            g.g0 = blk * kChunk;
-            g.nvalid = min(kChunk, W - g.g0);
-            if (dx == 0) {
-                g.clocks = H;
-            } else {
-                // the longest line of the block starts farthest from its exit column
-                const int lfirst = dx > 0 ? W - g.g0 : g.g0 + 1;
-                const int llast = dx > 0 ? W - (g.g0 + g.nvalid - 1) : g.g0 + g.nvalid;
-                g.clocks = min(max(lfirst, llast), H);
-            }
-        } else {
-            g.kind = 2;
-            g.j0 = (blk - top_blocks) * kChunk;
-            g.nvalid = min(kChunk, H - 1 - g.j0);
-            int c = 0;  // line i: skew i, length min(W, H - j0 - i - 1)
-            for (int i = 0; i < g.nvalid; ++i) c = max(c, i + min(W, H - g.j0 - i - 1));
-            g.clocks = c;
-        }
-    }
-    return g;
-}
-
-// row and leftmost column of the block's 16-column window at clock t (kinds 1, 2)
-__device__ __forceinline__ void window_at(const BlockGeom &g, int t, int &row, int &xm)
-{
-    if (g.kind == 1) {
-        row = g.ye + t * g.dy;
-        xm = g.g0 + t * g.dx;
-    } else {
-        row = g.ye + g.dy * (g.j0 + 1 + t);
-        xm = g.dx > 0 ? g.xe + t - (kChunk - 1) : g.xe - t;
-    }
-}
-
-}  // namespace
-
-// One block's scanlines.  HORIZ selects the horizontal layout (kind 0);
-// otherwise the block is of kind 1 or 2, whose lines share one image row per
-// clock: row(t) = row0 + t*dy, leftmost column xm(t) = xm0 + t*dx, lane column
-// xm(t) + xlane.  LPL lanes hold one line, DPL disparities each (LPL * DPL = Dpad).
-//
-// Census tiles move global -> LDS with direct-to-LDS loads into a ring of three
-// tile buffers, two chunks ahead of the chunk being computed; every lane of a
-// wave writes 4 consecutive bytes, so the tile is filled as a flat array of
-// dwords (two per word when census words are 64-bit).
-//
-// A kind-2 line that has not started yet (clock < its skew) is fed zero cost:
-// from U = 0 the recurrence then yields U = 0 and u = 0 until the line's first
-// pixel, exactly the state a line starts from.  Lanes of lines that have ended
-// (or not started) pass an offset past the buffer, whose store the hardware
-// drops, so every step issues the same unconditional store (the chunk-end wait
-// counts on that).
-// Census words are read from the LDS tile with inline-assembly ds_read_b32: the
-// tile is filled by direct-to-LDS loads, and for compiler-visible LDS reads the
-// compiler would wait for every outstanding vector memory operation (those loads
-// and all path-value stores) before each read.  The tile's readiness is already
-// guaranteed by the explicit vmcnt wait and barrier at each chunk boundary, so the
-// reads need only their own LDS counter: lds_wait() waits for it and ties the
-// results to that wait.
-template <int OFF>
-__device__ __forceinline__ uint32_t ds_read_at(uint32_t addr)
-{
-    uint32_t v;
-    asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
-    return v;
-}
-
-template <int N, int BASE = 0, int J = 0>
-__device__ __forceinline__ void ds_read_run(uint32_t addr, uint32_t (&w)[N])
-{
-    if constexpr (J < N) {
-        w[J] = ds_read_at<BASE + 4 * J>(addr);
-        ds_read_run<N, BASE, J + 1>(addr, w);
-    }
-}
-
-// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>): a loop
-// whose index is a constant expression in the body (LDS offsets as immediates)
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-template <int N>
-__device__ __forceinline__ void lds_wait(uint32_t &a, uint32_t (&w)[N])
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a));
-#pragma unroll
-    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(w[j]));
-}
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(size_t)p; }
-
-// The scalars one block of lines needs, each made explicitly wavefront-uniform
-// (readfirstlane) so that they live in scalar registers even when they were read
-// from a work list in memory, which the compiler cannot prove uniform.
-struct LineArgs {
-    const uint32_t *cl, *cr;  // census words (dwords; two per word when 64-bit)
-    uint8_t *out;             // this direction's path values
-    int W, H, D, p1, p2, bits;
-    int max_work;             // largest block work of the launch (agg_step_cost units)
-};
-
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-template <typename T>
-__device__ __forceinline__ T *uniform(T *p)
-{
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T *)(((uint64_t)hi << 32) | lo);
-}
-
-// HDIR: 0 for lines that share an image row per clock (kinds 1 and 2); +1 / -1
-// for horizontal lines running left-to-right / right-to-left.  A horizontal
-// line's cR words slide by one column per clock, so the lane keeps its DPL words
-// in registers and reads one new word per clock (plus cL), at offsets that are
-// compile-time constants for a given direction.
-template <int DPL, int LPL, bool WIDE, int HDIR, int TILE>
-__device__ __forceinline__ void run_lines(const LineArgs &a, const BlockGeom &g, uint32_t (*tile)[TILE])
-{
-    constexpr bool HORIZ = HDIR != 0;
-    using CW = CensusWord<WIDE>;
-    using LO = LineOps<LPL>;
-    using Word = typename CW::T;
-    constexpr int kWordDw = WIDE ? 2 : 1;                // dwords per census word
-    constexpr int kDpad = LPL * DPL;
-    constexpr int kLines = kBlock / LPL;                 // lines per block
-    constexpr int kSlots = HORIZ ? kLines : kChunk;      // tile slots: lines or clocks
-    // tile layout (words): the cR windows of all slots (Dpad + 15 words each),
-    // then the cL windows (16 words each)
-    constexpr int kSlotR = kDpad + kChunk - 1;
-    constexpr int kRdw = kSlotR * kWordDw, kLdw = kChunk * kWordDw;  // dwords per window
-    constexpr int kWaves = kBlock / 64;
-    constexpr int kSPW = kSlots / kWaves;                // slots loaded by each wave
-    constexpr int kRl = (kRdw + 63) / 64, kLl = (kSPW * kLdw + 63) / 64;
-    constexpr int kLoads = kSPW * kRl + kLl;             // load instructions per wave and chunk
-    static_assert(kSPW >= 1 && kSlots % kWaves == 0, "every wave loads whole slots");
-    static_assert(kSlots * (kRdw + kLdw) <= TILE, "tile too small");
-    static_assert(HORIZ || LPL == kLanesPerLine, "row-sharing lines use one DPP row per line");
-    const int W = a.W, H = a.H, D = a.D;
-    const int lane = threadIdx.x % LPL, li = threadIdx.x / LPL;
-    const bool first = lane == 0, last = lane == LPL - 1;
-    const int d0 = lane * DPL;
-    const uint32_t *__restrict__ cl = a.cl;
-    const uint32_t *__restrict__ cr = a.cr;
-    uint8_t *__restrict__ out = a.out;
-    const uint32_t p1 = a.p1, p2 = a.p2, bits = a.bits;
-    const bool padded = D < kDpad;
-    // the census bits of a word (a word XORed with this differs from it in `bits` bits)
-    const Word bits_mask = bits >= 8 * sizeof(Word) ? ~(Word)0 : (((Word)1 << bits) - 1);
-
-    // per-block line layout
-    int row0 = 0, xm0 = 0, xlane = 0, len = 0, skew = 0;
-    if (HORIZ) {
-        if (li < g.nvalid) len = W;
-    } else if (g.kind == 1) {
-        row0 = g.ye;
-        xm0 = g.g0;
-        xlane = li;
-        if (li < g.nvalid) {
-            const int x0 = g.g0 + li;
-            len = g.dx == 0 ? H : min(g.dx > 0 ? W - x0 : x0 + 1, H);
-        }
-    } else {
-        row0 = g.ye + g.dy * (g.j0 + 1);
-        xm0 = g.dx > 0 ? g.xe - (kChunk - 1) : g.xe;
-        xlane = g.dx > 0 ? kChunk - 1 - li : li;
-        skew = li;
-        if (li < g.nvalid) len = min(W, H - g.j0 - li - 1);
-    }
-    const bool skewed = !HORIZ && g.kind == 2;
-
-    // row and leftmost column of the 16-column window of tile slot `slot` of the
-    // chunk that starts at clock c0
-    auto slot_window = [&](int c0, int slot, int &row, int &xm) {
-        if (HORIZ) {
-            row = g.r0 + slot;
-            const int xc = g.xs + c0 * g.dx;
-            xm = g.dx > 0 ? xc : xc - (kChunk - 1);
-        } else {
-            row = row0 + (c0 + slot) * g.dy;
-            xm = xm0 + (c0 + slot) * g.dx;
-        }
-    };
-    // Direct-to-LDS loads of the chunk starting at clock c0 into ring buffer buf.
-    // A window is contiguous in its census map, and the image position of slot s's
-    // window is A0 + c0 * Sc + s * Ss (words), so a lane's byte offset is its lane
-    // index plus a wave-uniform window offset.  Loads go through buffer resources
-    // over the two census maps: a window position outside the image is either
-    // another pixel's word or an offset outside the map (the load returns zero);
-    // such words reach only disparities with x - d < 0, clocks before a line's
-    // start or after its end and lines off the image, whose values the steps
-    // replace or never store.
-    const int lane64 = threadIdx.x & 63;
-    const int s0 = uniform((int)(threadIdx.x >> 6)) * kSPW;
-    const int Sc = HORIZ ? g.dx : g.dy * W + g.dx;
-    const int Ss = HORIZ ? W : Sc;
-    const int A0 = HORIZ ? g.r0 * W + g.xs - (g.dx > 0 ? 0 : kChunk - 1) : row0 * W + xm0;
-    const uint32_t map_bytes = (uint32_t)W * H * kWordDw * 4;
-    const __amdgpu_buffer_rsrc_t rs_cl = __builtin_amdgcn_make_buffer_rsrc((void *)cl, 0, map_bytes, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t rs_cr = __builtin_amdgcn_make_buffer_rsrc((void *)cr, 0, map_bytes, kBufferWord3);
-    // a lane's byte offset within the cL loads, relative to the window of slot s0
-    uint32_t lofs[kLl];
-#pragma unroll
-    for (int j = 0; j < kLl; ++j) {
-        const int e = lane64 + 64 * j;
-        lofs[j] = (uint32_t)(((e / kLdw) * Ss * kWordDw + e % kLdw) * 4);
-    }
-    auto stage = [&](int c0, int buf) {
-        const int base = A0 + c0 * Sc + s0 * Ss;  // window position of slot s0
-#pragma unroll
-        for (int i = 0; i < kSPW; ++i) {
-            const int w0 = (base + i * Ss - (kDpad - 1)) * kWordDw * 4;
-#pragma unroll
-            for (int m = 0; m < kRl; ++m) {
-                auto *dst = (__attribute__((address_space(3))) void *)&tile[buf][(s0 + i) * kRdw + 64 * m];
-                const uint32_t vo = (uint32_t)(w0 + 256 * m) + (uint32_t)lane64 * 4;
-                if (64 * (m + 1) <= kRdw || lane64 < kRdw - 64 * m)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_cr, dst, 4, vo, 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kLl; ++j) {
-            auto *dst = (__attribute__((address_space(3))) void *)&tile[buf][kSlots * kRdw + s0 * kLdw + 64 * j];
-            const uint32_t vo = (uint32_t)(base * kWordDw * 4) + lofs[j];
-            if (64 * (j + 1) <= kSPW * kLdw || lane64 < kSPW * kLdw - 64 * j)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_cl, dst, 4, vo, 0, 0, 0);
-        }
-    };
-    // lane's pixel, tile slot and window at clock c0 + k
-    auto locate = [&](int c0, int k, int &x, int &row, int &xm, int &slot) {
-        const int t = c0 + k;
-        slot = HORIZ ? li : k;
-        slot_window(c0, slot, row, xm);
-        x = HORIZ ? g.xs + t * g.dx : xm + xlane;
-    };
-    // census words of one clock: cL(x) and cR(x - d) for d = d0 + DPL - 1 .. d0
-    auto fetch = [&](int buf, int slot, int xo, Word &wl, Word(&wr)[DPL]) {
-        const Word *sl = (const Word *)&tile[buf][0] + kSlots * kSlotR + slot * kChunk;  // cL window
-        const Word *sr = (const Word *)&tile[buf][0] + slot * kSlotR;                      // cR window
-        if constexpr (WIDE) {
-            wl = sl[xo];
-            const Word *p = sr + (xo + kDpad - d0 - DPL);
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) wr[j] = p[j];
-        } else {
-            wl = ds_read_at<0>(lds_addr(sl + xo));
-            ds_read_run<DPL>(lds_addr(sr + (xo + kDpad - d0 - DPL)), wr);
-        }
-    };
-    // the words of a fetch may be used only after this
-    auto ready = [&](Word &wl, Word(&wr)[DPL]) {
-        if constexpr (!WIDE) lds_wait<DPL>(wl, wr);
-    };
-
-    // un-normalised path sums U of the lane's disparities and the line minimum
-    // u of the previous clock's U
-    uint32_t U[DPL];
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) U[j] = 0;
-    uint32_t u = 0;
-    // a lane's output byte offset moves by this much per clock
-    const int step_off = (HORIZ ? g.dx : g.dy * W + g.dx) * kDpad;
-
-    const int nchunks = (g.clocks + kChunk - 1) / kChunk;
-    stage(0, 0);
-    if (nchunks > 1) stage(kChunk, 1);
-    // chunk 0 must be in LDS: at most chunk 1's loads may still be in flight
-    if (nchunks > 1) __builtin_amdgcn_s_waitcnt(vmcnt_encoding(kLoads));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_encoding(0));
-    __syncthreads();
-
-    // horizontal lines: the lane's sliding window of cR words, preloaded with the
-    // words of clock 0 that the first step keeps (tile indices within the line's
-    // slot: a column col of chunk 0 is at col - xm + kDpad - 1)
-    // (dx > 0: win[i] = cR(x0 - d0 - DPL + i) for i >= 1; dx < 0:
-    // win[i] = cR(x0 - d0 - DPL + 2 + i) for i <= DPL - 2; the other word is
-    // shifted out by the first step)
-    Word win[DPL];
-    if constexpr (HORIZ) {
-        constexpr int kFirst = HDIR > 0 ? 1 : 0;
-        const int idx0 = (HDIR > 0 ? kDpad - 1 - d0 - DPL : kDpad - d0 - DPL + 16) + kFirst;
-        if constexpr (DPL == 1) {
-            (void)idx0;
-        } else if constexpr (!WIDE) {
-            uint32_t w[DPL - 1], a0 = lds_addr((const Word *)&tile[0][0] + li * kSlotR + idx0);
-            ds_read_run<DPL - 1>(a0, w);
-            lds_wait<DPL - 1>(a0, w);
-#pragma unroll
-            for (int i = 0; i < DPL - 1; ++i) win[kFirst + i] = w[i];
-        } else {
-            const Word *sl = (const Word *)&tile[0][0] + li * kSlotR + idx0;
-#pragma unroll
-            for (int i = 0; i < DPL - 1; ++i) win[kFirst + i] = sl[i];
-        }
-        win[HDIR > 0 ? 0 : DPL - 1] = 0;
-    }
-
-    for (int c = 0; c < nchunks; ++c) {
-        const int buf = c % 3;
-        const int c0 = c * kChunk;
-        const bool ahead = c + 2 < nchunks;
-        {
-            // issue priority from the block's remaining work relative to the
-            // launch's largest block: the blocks sharing a SIMD then drain in
-            // order of remaining work and tend to finish together, instead of the
-            // last one running on alone (measured: 8-path 1280x720 D=128 pass
-            // 386 -> 357 us)
-            const int rem100 = (g.clocks - c0) * agg_step_cost(DPL, LPL) * 100;
-            if (rem100 > 43 * a.max_work) __builtin_amdgcn_s_setprio(3);
-            else if (rem100 > 21 * a.max_work) __builtin_amdgcn_s_setprio(2);
-            else if (rem100 > 7 * a.max_work) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
-        }
-        if (ahead) stage(c0 + 2 * kChunk, (c + 2) % 3);
-        // the chunk's output window: the image rows its pixels lie in (at most
-        // 16), as a buffer resource, and the lane's byte offset in it at clock c0
-        int rlo, nrows, off;
-        if (HORIZ) {
-            rlo = g.r0;
-            nrows = g.nvalid;
-            off = (li * W + g.xs + c0 * g.dx) * kDpad + d0;
-        } else {
-            const int ra = row0 + c0 * g.dy, rb = row0 + (c0 + kChunk - 1) * g.dy;
-            rlo = max(min(ra, rb), 0);
-            nrows = min(max(ra, rb), H - 1) - rlo + 1;
-            off = ((ra - rlo) * W + xm0 + c0 * g.dx + xlane) * kDpad + d0;
-        }
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(out + (size_t)rlo * W * kDpad, 0, nrows * W * kDpad, kBufferWord3);
-        // census words of clock K of the chunk.  Lines sharing an image row read
-        // tile slot K at a fixed column of the lane, so the LDS addresses are two
-        // per-chunk registers plus immediate offsets.
-        uint32_t aL = 0, aR = 0;
-        if constexpr (!HORIZ && !WIDE) {
-            const uint32_t tb = lds_addr(&tile[buf][0]);
-            aL = tb + (uint32_t)(kSlots * kSlotR + xlane) * 4;
-            aR = tb + (uint32_t)(xlane + kDpad - d0 - DPL) * 4;
-        } else if constexpr (HORIZ && !WIDE) {
-            // the line's slot; clock K reads cL at window column xo(K) and the one
-            // new cR word (dx > 0: column x - d0; dx < 0: x - d0 - DPL + 1)
-            const uint32_t tb = lds_addr(&tile[buf][0]);
-            aL = tb + (uint32_t)(kSlots * kSlotR + li * kChunk) * 4;
-            aR = tb + (uint32_t)(li * kSlotR + (HDIR > 0 ? kDpad - 1 - d0 : kDpad - d0 - DPL)) * 4;
-        }
-        // horizontal lines: cL and the new cR word of clock K
-        auto fetch_slide = [&](auto kc, Word &wl, Word(&wn)[1]) {
-            constexpr int K = decltype(kc)::value;
-            constexpr int XO = HDIR > 0 ? K : kChunk - 1 - K;  // window column of clock K
-            if constexpr (!WIDE) {
-                wl = ds_read_at<XO * 4>(aL);
-                wn[0] = ds_read_at<XO * 4>(aR);
-            } else {
-                const Word *sl = (const Word *)&tile[buf][0] + kSlots * kSlotR + li * kChunk;
-                const Word *sr = (const Word *)&tile[buf][0] + li * kSlotR;
-                wl = sl[XO];
-                wn[0] = sr[(HDIR > 0 ? kDpad - 1 - d0 : kDpad - d0 - DPL) + XO];
-            }
-        };
-        auto fetch_clock = [&](auto kc, Word &wl, Word(&wr)[DPL]) {
-            constexpr int K = decltype(kc)::value;
-            if constexpr (!HORIZ && !WIDE) {
-                wl = ds_read_at<K * kChunk * 4>(aL);
-                ds_read_run<DPL, K * kSlotR * 4>(aR, wr);
-            } else {
-                int x, row, xm, slot;
-                locate(c0, K, x, row, xm, slot);
-                fetch(buf, slot, x - xm, wl, wr);
-            }
-        };
-        Word wl_n, wr_n[DPL], wn_n[1];
-        if constexpr (HORIZ) fetch_slide(std::integral_constant<int, 0>{}, wl_n, wn_n);
-        else fetch_clock(std::integral_constant<int, 0>{}, wl_n, wr_n);
-        static_for<kChunk>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            const int t = c0 + k;
-            const int s = t - skew;
-            int x, row, xm, slot;
-            locate(c0, k, x, row, xm, slot);
-            Word wl;
-            Word wr[DPL];
-            if constexpr (HORIZ) {
-                if constexpr (!WIDE) lds_wait<1>(wl_n, wn_n);
-                wl = wl_n;
-                // slide the window one column and take in the new word
-                if constexpr (HDIR > 0) {
-#pragma unroll
-                    for (int j = 0; j < DPL - 1; ++j) win[j] = win[j + 1];
-                    win[DPL - 1] = wn_n[0];
-                } else {
-#pragma unroll
-                    for (int j = DPL - 1; j > 0; --j) win[j] = win[j - 1];
-                    win[0] = wn_n[0];
-                }
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) wr[j] = win[j];
-                if constexpr (k + 1 < kChunk) fetch_slide(std::integral_constant<int, k + 1>{}, wl_n, wn_n);
-            } else {
-                ready(wl_n, wr_n);
-                wl = wl_n;
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) wr[j] = wr_n[j];
-                // next clock's census words are read while this clock computes
-                if constexpr (k + 1 < kChunk) fetch_clock(std::integral_constant<int, k + 1>{}, wl_n, wr_n);
-            }
-            // (horizontal lines all span the image width: a per-lane constant and a
-            // uniform test, so the check stays on the scalar unit)
-            const bool active = HORIZ ? (len > 0 && t < W) : (uint32_t)s < (uint32_t)len;
-            const uint32_t um_edge = LO::from_prev(U[DPL - 1], first);
-            const uint32_t up_edge = LO::from_next(U[0], last);
-            const uint32_t cap = u + p2;
-            uint32_t Un[DPL];
-            uint32_t m = kNone;
-            // the block's leftmost column decides whether any lane sees x - d < 0;
-            // the first chunk of skewed lines has lines that have not started
-            const bool clip = (HORIZ ? x : xm) < kDpad - 1;
-            const bool border = padded || clip || (skewed && c == 0);
-            if (!border) {
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    const uint32_t um = j > 0 ? U[j - 1] : um_edge;
-                    const uint32_t up = j < DPL - 1 ? U[j + 1] : up_edge;
-                    const uint32_t tt = min(min(U[j], min(um, up) + p1), cap);
-                    Un[j] = tt + CW::hamming(wl, wr[DPL - 1 - j]);
-                    m = min(m, Un[j]);
-                }
-            } else if (!padded && !(skewed && c == 0)) {
-                // only x - d < 0 occurs: those disparities compare cL with a word at
-                // Hamming distance `bits` from it (cL ^ mask), which costs exactly
-                // `bits`, so the update keeps its fused form
-                const Word wfix = wl ^ bits_mask;
-                const int xd = x - d0;
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    const Word wrj = j <= xd ? wr[DPL - 1 - j] : wfix;
-                    const uint32_t um = j > 0 ? U[j - 1] : um_edge;
-                    const uint32_t up = j < DPL - 1 ? U[j + 1] : up_edge;
-                    const uint32_t tt = min(min(U[j], min(um, up) + p1), cap);
-                    Un[j] = tt + CW::hamming(wl, wrj);
-                    m = min(m, Un[j]);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) {
-                    const int d = d0 + j;
-                    const uint32_t cst = CW::hamming(wl, wr[DPL - 1 - j]);
-                    uint32_t C = d < D ? (x - d >= 0 ? cst : bits) : kPadCost;
-                    C = s < 0 ? 0u : C;  // a line that has not started stays at U = 0
-                    const uint32_t um = j > 0 ? U[j - 1] : um_edge;
-                    const uint32_t up = j < DPL - 1 ? U[j + 1] : up_edge;
-                    const uint32_t tt = min(min(U[j], min(um, up) + p1), cap);
-                    Un[j] = tt + C;
-                    m = min(m, Un[j]);
-                }
-            }
-            store_path<DPL>(rs, active ? (uint32_t)off : kNoStore, Un, u);
-            off += step_off;
-            u = LO::line_min(m);
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) U[j] = Un[j];
+    if constexpr (WIDE) {
+        static_for<S / 2>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, at * 8 + 16 * i, 0, 0);
+            w[2 * i] = ((uint64_t)v[1] << 32) | v[0];
+            w[2 * i + 1] = ((uint64_t)v[3] << 32) | v[2];
         });
-        // the next chunk's tile must have landed: only this chunk's look-ahead
-        // loads and its kChunk stores may still be in flight.  The tile is written
-        // by the loads themselves, so a bare s_barrier (no release fence, which
-        // would also wait for every global store) orders the waves; the empty asm
-        // statements keep the compiler from moving LDS reads across it.
-        if (ahead) __builtin_amdgcn_s_waitcnt(vmcnt_encoding(kLoads + store_ops<DPL>() * kChunk));
-        else __builtin_amdgcn_s_waitcnt(vmcnt_encoding(0));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+    } else {
+        static_for<S / 4>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, at * 4 + 16 * i, 0, 0);
+            w[4 * i] = v[0]; w[4 * i + 1] = v[1]; w[4 * i + 2] = v[2]; w[4 * i + 3] = v[3];
+        });
     }
+}
+// the same one word at a time, each at its own clamped position (segments that
+// touch the image's ends)
+template <bool WIDE, int S>
+__device__ __forceinline__ void load_words_clamped(__amdgpu_buffer_rsrc_t rs, int at, int last,
+                                                   typename CensusWord<WIDE>::T (&w)[S])
+{
+    static_for<S>([&](auto i) {
+        const int p = min(max(at + i, 0), last);
+        if constexpr (WIDE) {
+            const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(rs, p * 8, 0, 0);
+            w[i] = ((uint64_t)v[1] << 32) | v[0];
+        } else {
+            w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, p * 4, 0, 0);
+        }
+    });
+}
+
+// Horizontal lines (rows), HDIR +1 left to right, -1 right to left.  At column x a
+// lane needs the right words of columns x - d0 - j, j < DPL: one new word per step,
+// at columns that advance with x, so a segment's S new words are S consecutive
+// words of the row.
+template <int DPAD, int DPL, int LPL, bool WIDE, int HDIR>
+__device__ __forceinline__ void run_horizontal(const void *cl, const void *cr, uint8_t *out, int wave, int W, int H, int D,
+                                               uint32_t bits, uint32_t p1, uint32_t p2, int cost, int max_work)
+{
+    using LV = Lane<DPL, false>;
+    using L = Line<DPL, LPL, DPAD / DPL, false>;
+    using CW = CensusWord<WIDE>;
+    using Word = typename CW::T;
+    constexpr int S = kLoadSeg, R = kLoadRing, N = LV::N, kDpad = DPAD, kLines = 64 / LPL;
+    const int lane = (int)threadIdx.x % LPL, d0 = lane * DPL;
+    const WaveLines g = wave_lines<LPL, kDpad>(HDIR, 0, wave, W, H, lane * DPL);
+    const int y0 = wave * kLines, y = min(y0 + (int)(threadIdx.x & 63) / LPL, H - 1);
+    // resources from the wave's first row on (a lane's offset stays below 4 rows)
+    const __amdgpu_buffer_rsrc_t rl = open_buffer((const Word *)cl + (int64_t)y0 * W);
+    const __amdgpu_buffer_rsrc_t rr = open_buffer((const Word *)cr + (int64_t)y0 * W);
+    const int row = (y - y0) * W, last = (H - y0) * W - 1;  // the lane's row, the map's last word
+    const int nseg = (W + S - 1) / S;
+    // left words of segment k: columns lx .. lx + S - 1 in memory order; right words:
+    // the S columns that enter the lane's window, in memory order
+    auto lcol = [&](int k) { return HDIR > 0 ? k * S : W - S - k * S; };
+    auto rcol = [&](int k) { return HDIR > 0 ? k * S - d0 : W - S - k * S - d0 - (DPL - 1); };
+    // (uniform: true when no lane reads outside its row and no pixel of the segment
+    // has x - d < 0)
+    auto inside = [&](int k) { return HDIR > 0 ? k * S >= kDpad - 1 && (k + 1) * S <= W : W - (k + 1) * S >= kDpad - 1; };
+    auto load = [&](auto wc, int k, Word (&wl)[S], Word (&wr)[S]) {
+        if constexpr (decltype(wc)::value) {
+            load_words<WIDE, S>(rl, row + lcol(k), wl);
+            load_words<WIDE, S>(rr, row + rcol(k), wr);
+        } else {
+            load_words_clamped<WIDE, S>(rl, row + lcol(k), last, wl);
+            load_words_clamped<WIDE, S>(rr, row + rcol(k), last, wr);
+        }
+    };
+    L line;
+    line.clear();
+    // window: entry i of the S + DPL - 1 words a segment uses, in the order they
+    // enter; the last DPL - 1 of a segment are the first of the next
+    Word carry[DPL];
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) carry[i] = 0;
+    if constexpr (HDIR < 0) {
+        // columns W - 1 - d0 - i, i < DPL - 1, have entered before the first step
+#pragma unroll
+        for (int i = 0; i < DPL - 1; ++i) {
+            Word v[1];
+            load_words_clamped<WIDE, 1>(rr, row + W - 1 - d0 - i, last, v);
+            carry[i] = v[0];
+        }
+    }
+    const bool padded = D < kDpad;
+    Word left[R][S], rights[R][S];
+    auto run = [&](auto wc, int k, const Word (&wl)[S], const Word (&wr)[S]) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        // words in the order they enter the lane's window
+        Word win[S + DPL - 1];
+#pragma unroll
+        for (int i = 0; i < DPL - 1; ++i) win[i] = carry[i];
+#pragma unroll
+        for (int s = 0; s < S; ++s) win[DPL - 1 + s] = HDIR > 0 ? wr[s] : wr[S - 1 - s];
+#pragma unroll
+        for (int i = 0; i < DPL - 1; ++i) carry[i] = win[S + i];
+        const Segment o = segment<S, kDpad>(out, g, k, false);
+        static_for<S>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            const int x = HDIR > 0 ? k * S + s : W - 1 - k * S - s;
+            const Word l = HDIR > 0 ? wl[s] : wl[S - 1 - s];
+            // the lane's disparity j compares with window entry: HDIR > 0, newest is
+            // column x - d0 (j = 0); HDIR < 0, newest is x - d0 - (DPL - 1)
+            auto hamming = [&](int j) -> uint32_t {
+                const uint32_t c = CW::hamming(l, HDIR > 0 ? win[s + DPL - 1 - j] : win[s + j]);
+                if constexpr (!WHOLE) return d0 + j < D ? (j <= x - d0 ? c : bits) : 255u;
+                return c;
+            };
+            const uint32_t ub = both(line.u);
+            line.step(p1, p2, lane, [&](auto j, uint32_t t) {
+                // (each half takes its own count: no carry between them)
+                t += hamming(j);
+                if constexpr (DPL > 1) t += hamming(j + N) << 16;
+                return t;
+            });
+            uint32_t v[N], m[LV::NW];
+#pragma unroll
+            for (int j = 0; j < N; ++j) v[j] = pk_sub(line.U[j], ub);
+            LV::pack(v, m);
+            LV::template store<kStoreAux>(o.rs, WHOLE || k * S + s < W ? g.off : kOff, at_step<S>(o, s), m);
+        });
+    };
+    auto block = [&](auto wc, int k) {
+        constexpr bool WHOLE = decltype(wc)::value;
+        static_for<R>([&](auto r) {
+            if (!WHOLE && k + r >= nseg) return;
+            constexpr int next = (r + R - 1) % R;
+            load(wc, k + r + R - 1, left[next], rights[next]);
+            run(wc, k + r, left[r], rights[r]);
+        });
+        line.rebase();
+    };
+    static_for<R - 1>([&](auto r) { load(std::false_type{}, r, left[r], rights[r]); });
+    for (int k = 0; k < nseg; k += R) {
+        set_priority((W - k * S) * cost, max_work);
+        if (!padded && inside(k) && inside(k + 2 * R - 2)) block(std::true_type{}, k);
+        else block(std::false_type{}, k);
+    }
+}
+
+// ---------------------------------------------------------------- matching costs
+// The cost volume: byte popcount(cL(x) ^ cR(x - d)) per pixel and disparity, d
+// fastest; `bits` where x - d < 0 and 255 (above every path value a real one can be
+// compared with) where d >= D.  A thread makes 16 disparities of two adjacent
+// pixels (17 right words from LDS for 32 values) and stores 16 bytes for each.
+// Bound by the volume's stores, which keep the default cache policy: the
+// aggregation reads the volume several times, from the last-level cache when it
+// fits there.
+constexpr int kCostDisp = 16;
+__host__ __device__ constexpr int cost_pairs(int dpad) { return 256 / (dpad / kCostDisp); }  // pixel pairs per block
+constexpr int cost_tiles(int dpad, int W) { return (W + 2 * cost_pairs(dpad) - 1) / (2 * cost_pairs(dpad)); }  // per row
+
+template <int DPL, bool WIDE>
+__device__ __forceinline__ void cost_tile(const AggregateArgs &a, int y, int tile, typename CensusWord<WIDE>::T *lds)
+{
+    using CW = CensusWord<WIDE>;
+    using Word = typename CW::T;
+    constexpr int kDpad = kLanesPerLine * DPL, kChunks = kDpad / kCostDisp, kPairs = cost_pairs(kDpad), kPx = 2 * kPairs;
+    const int W = uniform(a.W), D = uniform(a.D);
+    const int x0 = tile * kPx;
+    if (x0 >= W) return;  // (the widest image of a batch sets the grid)
+    const Word *cl = uniform((const Word *)a.census_l) + (int64_t)y * W;
+    const Word *cr = uniform((const Word *)a.census_r) + (int64_t)y * W;
+    // right words of columns x0 - (Dpad - 1) .. x0 + kPx - 1
+    for (int i = threadIdx.x; i < kDpad - 1 + kPx; i += 256) lds[i] = cr[min(max(x0 - (kDpad - 1) + i, 0), W - 1)];
+    __syncthreads();
+    const int c = (int)threadIdx.x % kChunks, p = (int)threadIdx.x / kChunks;
+    const int x = x0 + 2 * p, d0 = c * kCostDisp;
+    if (p >= kPairs || x >= W) return;
+    const Word l0 = cl[x], l1 = cl[min(x + 1, W - 1)];
+    // window word i: column x + 1 - d0 - i; pixel 0 uses 1 + j, pixel 1 uses j
+    Word r[kCostDisp + 1];
+#pragma unroll
+    for (int i = 0; i <= kCostDisp; ++i) r[i] = lds[2 * p + kDpad - d0 - i];
+    uint32_t w0[4], w1v[4];
+    const bool edge = D < kDpad || x0 < kDpad - 1;
+    const uint32_t bits = a.bits;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint32_t v0 = 0, v1 = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int j = 4 * q + b;
+            uint32_t c0 = CW::hamming(l0, r[j + 1]), c1 = CW::hamming(l1, r[j]);
+            if (edge) {
+                c0 = d0 + j < D ? (x - d0 - j >= 0 ? c0 : bits) : 255u;
+                c1 = d0 + j < D ? (x + 1 - d0 - j >= 0 ? c1 : bits) : 255u;
+            }
+            v0 |= c0 << (8 * b);
+            v1 |= c1 << (8 * b);
+        }
+        w0[q] = v0;
+        w1v[q] = v1;
+    }
+    uint8_t *o = uniform(a.cost) + ((int64_t)y * W + x) * kDpad + d0;
+    *(__attribute__((address_space(1))) u32x4_t *)o = u32x4_t{w0[0], w0[1], w0[2], w0[3]};
+    if (x + 1 < W) *(__attribute__((address_space(1))) u32x4_t *)(o + kDpad) = u32x4_t{w1v[0], w1v[1], w1v[2], w1v[3]};
+}
+
+template <int DPL>
+constexpr int cost_lds_words() { return kLanesPerLine * DPL + 2 * cost_pairs(kLanesPerLine * DPL); }
+
+template <int DPL, bool WIDE>
+__global__ __launch_bounds__(256) void cost_kernel(AggregateArgs a)
+{
+    __shared__ typename CensusWord<WIDE>::T lds[cost_lds_words<DPL>()];
+    cost_tile<DPL, WIDE>(a, (int)blockIdx.y, (int)blockIdx.x, lds);
+}
+
+// batch form: one item per (slot, row)
+template <int DPL, bool WIDE>
+__global__ __launch_bounds__(256) void cost_queue_kernel(AggregateQueue q)
+{
+    __shared__ typename CensusWord<WIDE>::T lds[cost_lds_words<DPL>()];
+    const uint32_t it = __builtin_amdgcn_readfirstlane(q.cost_items[blockIdx.x]);
+    cost_tile<DPL, WIDE>(q.slots[it >> 20], (int)(it & 0xFFFFFu), (int)blockIdx.y, lds);
+}
+
+// ---------------------------------------------------------------- the aggregation launch
+// One wave's lines: item `item` of the slot (a running number over its units).
+// Steps between two states of a pair: 8, or 4 where the forward values of 8 steps
+// would not fit the registers.
+constexpr int sum_steps(int dpl, bool v16) { return v16 && dpl >= 12 ? 4 : 8; }
+
+// One block of four waves: the lines of item `item` of the slot (a running number
+// over its units).  A block's waves have about the same work and land on the four
+// SIMDs of a unit.
+template <int DPL, bool WIDE, int HL>
+__device__ __forceinline__ void aggregate_item(const AggregateArgs &a, int item)
+{
+    constexpr int kDpad = kLanesPerLine * DPL, LD = lane_disparities(kDpad, kLanesPerLine), HD = lane_disparities(kDpad, HL);
+    const int nunits = uniform(a.nunits);
+    int unit = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) unit += (k < nunits && item >= a.item_begin[k]) ? 1 : 0;
+    unit = uniform(unit);
+    item = uniform(item - a.item_begin[unit]);
+    const int w = uniform((int)threadIdx.x >> 6);
+    const int dx = uniform(a.dx[unit]), dy = uniform(a.dy[unit]);
+    uint8_t *out = uniform(a.out[unit]);
+    const int W = uniform(a.W), H = uniform(a.H), max_work = uniform(a.max_item_work);
+    const int nlines = line_count(dx, dy, W, H);
+    const uint32_t p1 = both(uniform(a.p1)), p2 = both(uniform(a.p2));
+    if (dy == 0) {
+        constexpr int cost = agg_step_cost(HD, HL);
+        const int wave = item * kWavesPerItem + w;
+        if (wave * (64 / HL) >= nlines) return;
+        const int D = uniform(a.D);
+        const uint32_t bits = uniform(a.bits);
+        if (dx > 0)
+            run_horizontal<kDpad, HD, HL, WIDE, 1>(uniform(a.census_l), uniform(a.census_r), out, wave, W, H, D, bits, p1,
+                                                   p2, cost, max_work);
+        else
+            run_horizontal<kDpad, HD, HL, WIDE, -1>(uniform(a.census_l), uniform(a.census_r), out, wave, W, H, D, bits, p1,
+                                                    p2, cost, max_work);
+    } else {
+        constexpr int cost = agg_step_cost(LD, kLanesPerLine), kLines = 64 / kLanesPerLine;
+        const bool pair = uniform(a.pair[unit]) != 0;
+        const int wave = pair ? item * (kWavesPerItem / 2) + w / 2 : item * kWavesPerItem + w;
+        const bool live = wave * kLines < nlines;
+        const int lane = (int)threadIdx.x % kLanesPerLine;
+        const WaveLines g = wave_lines<kLanesPerLine, kDpad>(dx, dy, wave, W, H, lane * LD);
+        const uint8_t *vol = uniform(a.cost);
+        if (pair)
+            run_pair<kDpad, LD, kLanesPerLine, false, sum_steps(LD, false)>(vol, out, g, live, w & 1, p1, p2, cost, max_work);
+        else if (live)
+            run_single<kDpad, LD, kLanesPerLine, false>(vol, out, g, p1, p2, cost, max_work);
+    }
+}
+
+// Registers for two waves per SIMD: a step is a serial chain, and the scheduler fills
+// its gaps with other steps' work when it has the registers (2 waves with up to 256
+// registers beat 3 with 168).
+template <int DPL, bool WIDE, int HL>
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(2, 2))) void aggregate_kernel(AggregateArgs a, int first)
+{
+    aggregate_item<DPL, WIDE, HL>(a, first + (int)blockIdx.x);
+}
+
+// items (slot << 20 | item) in launch order, largest estimated work first
+template <int DPL, bool WIDE, int HL>
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(2, 2))) void aggregate_queue_kernel(AggregateQueue q, int first)
+{
+    const uint32_t it = __builtin_amdgcn_readfirstlane(q.items[first + (int)blockIdx.x]);
+    aggregate_item<DPL, WIDE, HL>(q.slots[it >> 20], (int)(it & 0xFFFFFu));
+}
+
+// Launches the costs (when a unit reads them) and the lines of one slot (a) or of
+// every slot of a queue (q).  Units that write over the cost volume run after
+// everything else has read it: a second launch.
+// (grid: the blocks of the first launch)
+template <int DPL, bool WIDE, int HL>
+hipError_t launch_aggregation(const AggregateArgs *a, const AggregateQueue *q, int grid, hipStream_t s)
+{
+    constexpr int kDpad = kLanesPerLine * DPL;
+    const dim3 block(64 * kWavesPerItem);
+    if (a) {
+        const int rest = a->item_begin[a->nunits] - grid;
+        if (a->cost) hipLaunchKernelGGL((cost_kernel<DPL, WIDE>), dim3(cost_tiles(kDpad, a->W), a->H), dim3(256), 0, s, *a);
+        if (grid > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(grid), block, 0, s, *a, 0);
+        if (rest > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(rest), block, 0, s, *a, grid);
+    } else {
+        if (q->ncost > 0)
+            hipLaunchKernelGGL((cost_queue_kernel<DPL, WIDE>), dim3(q->ncost, cost_tiles(kDpad, q->cost_width)), dim3(256), 0, s, *q);
+        if (grid > 0) hipLaunchKernelGGL((aggregate_queue_kernel<DPL, WIDE, HL>), dim3(grid), block, 0, s, *q, 0);
+        if (q->nlast > 0) hipLaunchKernelGGL((aggregate_queue_kernel<DPL, WIDE, HL>), dim3(q->nlast), block, 0, s, *q, grid);
+    }
+    return hipGetLastError();
 }
 
 template <int DPL, bool WIDE>
-constexpr int agg_tile_dwords()
-{
-    return (kChunk * (kLanesPerLine * DPL + 2 * kChunk - 1) * (WIDE ? 2 : 1) + kBlock - 1) / kBlock * kBlock;
-}
-
-// One block of work: 16 lines (or 256/HL horizontal lines) of one direction.
-template <int DPL, bool WIDE, int HL>
-__device__ __forceinline__ void aggregate_block(const AggregateArgs &a, int blk, uint32_t (*tile)[agg_tile_dwords<DPL, WIDE>()])
+hipError_t launch_aggregation_lanes(const AggregateArgs *a, const AggregateQueue *q, int grid, int hl, hipStream_t s)
 {
     constexpr int kDpad = kLanesPerLine * DPL;
-    static_assert(kDpad % HL == 0, "horizontal lanes must divide the padded disparity count");
-    // the direction of block blk: the number of later directions whose first block
-    // it has passed (all prefix sums loaded at once, not one load per branch)
-    const int ndirs = uniform(a.ndirs);
-    int bb[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) bb[k] = a.block_begin[k];
-    int dir = 0;
-#pragma unroll
-    for (int k = 1; k < 8; ++k) dir += (k < ndirs && blk >= bb[k]) ? 1 : 0;
-    dir = uniform(dir);
-    LineArgs la;
-    la.cl = uniform((const uint32_t *)a.census_l);
-    la.cr = uniform((const uint32_t *)a.census_r);
-    la.out = uniform(a.out[dir]);
-    la.W = uniform(a.W); la.H = uniform(a.H); la.D = uniform(a.D);
-    la.p1 = uniform(a.p1); la.p2 = uniform(a.p2); la.bits = uniform(a.bits);
-    la.max_work = uniform(max(a.max_item_work, 1));
-    const BlockGeom g = block_geometry(uniform(a.dx[dir]), uniform(a.dy[dir]), blk - uniform(a.block_begin[dir]),
-                                       la.W, la.H, kBlock / HL);
-    if (g.kind == 0) {
-        // horizontal lines: more lanes per line to shorten each step
-        if (g.dx > 0) run_lines<kDpad / HL, HL, WIDE, 1, agg_tile_dwords<DPL, WIDE>()>(la, g, tile);
-        else run_lines<kDpad / HL, HL, WIDE, -1, agg_tile_dwords<DPL, WIDE>()>(la, g, tile);
-    } else {
-        run_lines<DPL, kLanesPerLine, WIDE, 0, agg_tile_dwords<DPL, WIDE>()>(la, g, tile);
-    }
-    __builtin_amdgcn_s_setprio(0);
+    hl = effective_lanes(kDpad, hl);
+    if constexpr (effective_lanes(kDpad, 32) == 32)
+        if (hl == 32) return launch_aggregation<DPL, WIDE, 32>(a, q, grid, s);
+    if constexpr (effective_lanes(kDpad, 64) == 64)
+        if (hl == 64) return launch_aggregation<DPL, WIDE, 64>(a, q, grid, s);
+    return launch_aggregation<DPL, WIDE, 16>(a, q, grid, s);
 }
 
-template <int DPL, bool WIDE, int HL>
-__global__ __launch_bounds__(kBlock) void aggregate_kernel(AggregateArgs a)
-{
-    __shared__ uint32_t tile[3][agg_tile_dwords<DPL, WIDE>()];
-    aggregate_block<DPL, WIDE, HL>(a, (int)blockIdx.x, tile);
-}
-
-// Persistent form for batches: a grid sized to the machine takes work items
-// (pair slot << 20 | block) from a queue in order (longest first) until it is
-// empty; every block leaves once the shared counter passes the item count.
-// (4 waves per SIMD: the compiler keeps the 32-bit-census form within 128
-// VGPRs, so four blocks fit on a CU)
-template <int DPL, bool WIDE, int HL>
-__global__ __launch_bounds__(kBlock, 4) void aggregate_queue_kernel(AggregateQueue q)
-{
-    __shared__ uint32_t tile[3][agg_tile_dwords<DPL, WIDE>()];
-    __shared__ int cur;
-    for (;;) {
-        if (threadIdx.x == 0) cur = (int)atomicAdd(q.counter, 1u);
-        __syncthreads();
-        const int i = __builtin_amdgcn_readfirstlane(cur);
-        __syncthreads();
-        if (i >= q.nitems) break;
-        const uint32_t it = __builtin_amdgcn_readfirstlane(q.items[i]);
-        aggregate_block<DPL, WIDE, HL>(q.slots[it >> 20], (int)(it & 0xFFFFFu), tile);
-    }
-}
+}  // namespace
 
 }  // namespace ss

@@ -71,7 +71,8 @@ Layout layout(const simsense_params *p)
     const bool wide = census_bits(p->census_w, p->census_h, p->census_mode) > 32;
     l.census = align256(npx * (wide ? 8 : 4));
     const bool block = p->block_w * p->block_h > 1;
-    // + one spare pixel for idle lanes; 16-bit path values for block matching
+    // one buffer per direction (the aggregation fills fewer where it stores sums, and
+    // keeps its cost volume in the last); 16-bit path values for block matching
     l.paths = align256((npx + 1) * padded_disp(p->max_disp) * (block ? 2 : 1));
     l.volume = block ? align256(npx * padded_disp(p->max_disp) * 2) : 0;
     static const int px_bytes[7] = {1, 2, 2, 1, 4, 4, 1};  // dint, S1, S2, dright, dsub, masked, flags
@@ -92,9 +93,12 @@ void init_handle(simsense_handle *h, const simsense_params *params)
     h->bits = census_bits(params->census_w, params->census_h, params->census_mode);
     h->wide = h->bits > 32;
     h->Dpad = padded_disp(params->max_disp);
-    h->hlanes = horizontal_lanes(h->Dpad);
     h->ndirs = params->num_paths;
     h->sgbm = params->block_w * params->block_h > 1;
+    h->pairs = h->sgbm || h->bits + params->p2 <= 127;
+    h->nplanes = aggregate_planes(h->ndirs, h->pairs);
+    h->hlanes = default_lanes(params->width, h->Dpad,
+                              aggregate_work(params->width, params->height, h->Dpad, h->ndirs, h->pairs));
 }
 
 // Points the handle's buffers into one block of scratch laid out by layout().
@@ -191,26 +195,17 @@ void profile_mark(simsense_handle *h, int pass, bool end, hipStream_t s)
 
 // The handle's aggregation arguments (every pointer is handle scratch, so they
 // are fixed for its life).
-static AggregateArgs handle_aggregate_args(const simsense_handle *h)
+void plan_handle(simsense_handle *h)
 {
     const simsense_params &p = h->p;
-    AggregateArgs ag{};
+    AggregateArgs &ag = h->ag;
+    ag = AggregateArgs{};
     ag.census_l = h->census_l;
     ag.census_r = h->census_r;
+    ag.cost = (uint8_t *)h->volume;
     ag.W = p.width; ag.H = p.height; ag.D = p.max_disp; ag.Dpad = h->Dpad; ag.bits = h->bits;
     ag.p1 = p.p1; ag.p2 = p.p2;
-    ag.ndirs = h->ndirs;
-    ag.block_begin[0] = 0;
-    for (int r = 0; r < h->ndirs; ++r) {
-        ag.dx[r] = kPathDx[r];
-        ag.dy[r] = kPathDy[r];
-        ag.out[r] = h->paths[r];
-        ag.block_begin[r + 1] = ag.block_begin[r] + aggregate_blocks(kPathDx[r], kPathDy[r], p.width, p.height, h->hlanes);
-        for (int k = 0; k < ag.block_begin[r + 1] - ag.block_begin[r]; ++k)
-            ag.max_item_work = std::max(ag.max_item_work, aggregate_block_work(kPathDx[r], kPathDy[r], k, p.width,
-                                                                               p.height, h->hlanes, h->Dpad));
-    }
-    return ag;
+    plan_aggregation(ag, h->ndirs, h->pairs, h->sgbm, h->sgbm ? volume_horizontal_lanes(h->Dpad) : h->hlanes, h->paths);
 }
 
 // The right-referenced run is the left-referenced pass on x-flipped census maps
@@ -223,70 +218,60 @@ static AggregateArgs right_run_args(AggregateArgs ag, const simsense_handle *h)
     return ag;
 }
 
-static int launch_aggregation(simsense_handle *h, const AggregateArgs &ag, AggregateArgs *d_args, hipStream_t s)
+// The aggregation pass over the maps of `ag` (d_args: its copy on the device)
+static int launch_aggregation(simsense_handle *h, const AggregateArgs &ag, const AggregateArgs *d_args, hipStream_t s)
 {
-    if (h->tuning.blocks_per_cu > 0) {
+    if (h->sgbm) {
+        // block costs into the volume, then the lines fed from it
+        const simsense_params &p = h->p;
+        BlockCostArgs bc{};
+        bc.census_l = ag.census_l; bc.census_r = ag.census_r;
+        bc.W = p.width; bc.H = p.height; bc.D = p.max_disp; bc.bits = h->bits; bc.bw = p.block_w; bc.bh = p.block_h;
+        bc.vol = h->volume;
+        SS_TRY(launch_block_cost(bc, h->Dpad, h->wide, s));
+        SS_TRY(launch_aggregate_volume(VolumeArgs{ag}, s));
+    } else if (h->tuning.blocks_per_cu > 0) {
         AggregateQueue q{};
         q.slots = d_args;
         q.items = h->d_items;
-        q.nitems = h->nitems;
-        q.counter = h->d_counter;
-        const int grid = std::min(h->nitems, h->tuning.blocks_per_cu * h->num_cus);
-        SS_TRY(launch_zero_counters(h->d_counter, 1, s));
-        SS_TRY(launch_aggregate_queue(q, h->Dpad, h->wide, h->hlanes, grid, s));
+        q.nlast = h->nlast;
+        q.cost_items = h->d_items + h->nitems + h->nlast;
+        q.ncost = h->ncost;
+        q.cost_width = h->p.width;
+        SS_TRY(launch_aggregate_queue(q, h->Dpad, h->wide, h->hlanes, h->nitems, s));
     } else {
         SS_TRY(launch_aggregate(ag, h->wide, h->hlanes, s));
     }
     return SIMSENSE_OK;
 }
 
-// Block matching (SGBM): block costs of the given census maps into the volume,
-// then the aggregation fed from it into the path buffers (16-bit values).
-static int sgbm_aggregation(simsense_handle *h, const void *cl, const void *cr, hipStream_t s)
-{
-    const simsense_params &p = h->p;
-    BlockCostArgs bc{};
-    bc.census_l = cl; bc.census_r = cr;
-    bc.W = p.width; bc.H = p.height; bc.bits = h->bits; bc.bw = p.block_w; bc.bh = p.block_h;
-    bc.vol = h->volume;
-    SS_TRY(launch_block_cost(bc, h->Dpad, h->wide, s));
-    VolumeArgs va{};
-    va.vol = h->volume;
-    va.W = p.width; va.H = p.height; va.D = p.max_disp; va.Dpad = h->Dpad; va.p1 = p.p1; va.p2 = p.p2;
-    va.ndirs = h->ndirs;
-    va.block_begin[0] = 0;
-    for (int r = 0; r < h->ndirs; ++r) {
-        va.dx[r] = kPathDx[r];
-        va.dy[r] = kPathDy[r];
-        va.out[r] = (uint16_t *)h->paths[r];
-        va.block_begin[r + 1] = va.block_begin[r] + aggregate_blocks(kPathDx[r], kPathDy[r], p.width, p.height,
-                                                                     volume_horizontal_lanes(h->Dpad));
-    }
-    SS_TRY(launch_aggregate_volume(va, s));
-    return SIMSENSE_OK;
-}
-
-// Applies a tuning: lane count, and for the persistent form the work list of
-// line blocks sorted by estimated work, largest first (stable, so equal work
-// keeps direction order).
+// Applies a tuning: lane count, and for the sorted form the work list: items by
+// estimated work, largest first (stable, so equal work keeps unit order), the units
+// that run last, then the rows whose costs go to the volume.
 static int apply_tuning(simsense_handle *h, const simsense_batch_tuning &t)
 {
-    const int hl = t.horizontal_lanes == 0 ? horizontal_lanes(h->Dpad) : t.horizontal_lanes;
-    if (!horizontal_lanes_valid(h->Dpad, hl)) return SIMSENSE_ERR_INVALID_ARGUMENT;
-    h->hlanes = hl;
+    if (t.horizontal_lanes != 0 && !horizontal_lanes_valid(h->Dpad, t.horizontal_lanes)) return SIMSENSE_ERR_INVALID_ARGUMENT;
+    const simsense_params &p = h->p;
+    const int hl = h->hlanes = t.horizontal_lanes != 0
+                                   ? t.horizontal_lanes
+                                   : default_lanes(p.width, h->Dpad, aggregate_work(p.width, p.height, h->Dpad, h->ndirs, h->pairs));
     h->tuning = t;
-    const AggregateArgs ag = handle_aggregate_args(h);
+    plan_handle(h);
+    const AggregateArgs &ag = h->ag;
     std::vector<std::pair<int, uint32_t>> lst;
-    for (int r = 0; r < h->ndirs; ++r)
-        for (int k = 0; k < ag.block_begin[r + 1] - ag.block_begin[r]; ++k)
-            lst.push_back({aggregate_block_work(kPathDx[r], kPathDy[r], k, h->p.width, h->p.height, hl, h->Dpad),
-                           (uint32_t)(ag.block_begin[r] + k)});
+    for (int u = 0; u < ag.last_first; ++u)
+        for (int k = 0; k < ag.item_begin[u + 1] - ag.item_begin[u]; ++k)
+            lst.push_back({aggregate_item_work(ag, u, k, hl), (uint32_t)(ag.item_begin[u] + k)});
     std::stable_sort(lst.begin(), lst.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-    std::vector<uint32_t> items(lst.size());
-    for (size_t i = 0; i < lst.size(); ++i) items[i] = lst[i].second;  // pair slot 0
+    std::vector<uint32_t> items;
+    for (const auto &e : lst) items.push_back(e.second);  // pair slot 0
+    h->nitems = (int)items.size();
+    for (int i = ag.item_begin[ag.last_first]; i < ag.item_begin[ag.nunits]; ++i) items.push_back((uint32_t)i);
+    h->nlast = (int)items.size() - h->nitems;
+    h->ncost = ag.cost && !h->sgbm ? h->p.height : 0;
+    for (int y = 0; y < h->ncost; ++y) items.push_back((uint32_t)y);
     if (h->d_items) (void)hipFree(h->d_items);
     h->d_items = nullptr;
-    h->nitems = (int)items.size();
     SS_TRY(hipMalloc(&h->d_items, std::max<size_t>(items.size(), 1) * sizeof(uint32_t)));
     if (!items.empty()) SS_TRY(hipMemcpy(h->d_items, items.data(), items.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     SS_TRY(hipMemcpy(h->d_args, &ag, sizeof(ag), hipMemcpyHostToDevice));
@@ -305,45 +290,29 @@ int enqueue_match(simsense_handle *h, const uint8_t *left, const uint8_t *right,
     h->last_stream = s;
     TraceRange range("simsense match");
     profile_mark(h, SIMSENSE_PASS_CENSUS, false, s);
-    const bool queue = !h->sgbm && h->tuning.blocks_per_cu > 0;
-    // (the census launch also clears the work-queue counter)
     SS_TRY(launch_census_pair(left, right, pitch, W, H, p.census_w, p.census_h, p.census_mode, h->census_l,
-                              h->census_r, h->wide, s, queue ? h->d_counter : nullptr, queue ? 1 : 0));
+                              h->census_r, h->wide, s));
     profile_mark(h, SIMSENSE_PASS_CENSUS, true, s);
 
-    const AggregateArgs ag = handle_aggregate_args(h);
     profile_mark(h, SIMSENSE_PASS_AGGREGATE, false, s);
-    if (h->sgbm) {
-        // block costs, then the aggregation fed from them
-        const int rc = sgbm_aggregation(h, h->census_l, h->census_r, s);
-        if (rc != SIMSENSE_OK) return rc;
-    } else if (queue) {
-        AggregateQueue q{};
-        q.slots = h->d_args;
-        q.items = h->d_items;
-        q.nitems = h->nitems;
-        q.counter = h->d_counter;
-        const int grid = std::min(h->nitems, h->tuning.blocks_per_cu * h->num_cus);
-        SS_TRY(launch_aggregate_queue(q, h->Dpad, h->wide, h->hlanes, grid, s));
-    } else {
-        SS_TRY(launch_aggregate(ag, h->wide, h->hlanes, s));
-    }
+    int rc = launch_aggregation(h, h->ag, h->d_args, s);
+    if (rc != SIMSENSE_OK) return rc;
     profile_mark(h, SIMSENSE_PASS_AGGREGATE, true, s);
     if (volume_out) {
         // the summed volume of this (left-referenced) run, before a right-referenced
         // run reuses the path buffers
         PathSet ps{};
-        for (int r = 0; r < h->ndirs; ++r) ps.p[r] = h->paths[r];
-        SS_TRY(launch_volume_sum(ps, h->ndirs, h->sgbm, W, H, D, h->Dpad, volume_out, s));
+        for (int r = 0; r < h->nplanes; ++r) ps.p[r] = h->paths[r];
+        SS_TRY(launch_volume_sum(ps, h->nplanes, h->sgbm, W, H, D, h->Dpad, volume_out, s));
     }
 
     SelectArgs sa{};
-    for (int r = 0; r < h->ndirs; ++r) sa.paths[r] = h->paths[r];
-    sa.ndirs = h->ndirs;
+    for (int r = 0; r < h->nplanes; ++r) sa.paths[r] = h->paths[r];
+    sa.nplanes = h->nplanes;
     sa.W = W; sa.H = H; sa.D = D; sa.Dpad = h->Dpad;
     sa.uniqueness_pct = p.uniqueness_pct; sa.lr_max_diff = p.lr_max_diff; sa.subpixel = p.subpixel;
     sa.values16 = h->sgbm;
-    sa.small_values = !h->sgbm && h->bits + p.p2 <= 127;
+    sa.small_values = !h->sgbm && h->pairs;
     sa.disp_int = h->disp_int; sa.cost_best = h->cost_best; sa.cost_second = h->cost_second;
     sa.disp_right = h->disp_right; sa.disp_sub = h->disp_sub; sa.masked = h->masked; sa.flags = h->flags_pre;
     sa.no_right = !need_right;
@@ -353,8 +322,7 @@ int enqueue_match(simsense_handle *h, const uint8_t *left, const uint8_t *right,
         // full right-referenced run into the second per-pixel set, then the check
         SS_TRY(launch_flip_census(h->census_r, h->census_ml, W, H, h->wide, s));
         SS_TRY(launch_flip_census(h->census_l, h->census_mr, W, H, h->wide, s));
-        const int rc = h->sgbm ? sgbm_aggregation(h, h->census_ml, h->census_mr, s)
-                               : launch_aggregation(h, right_run_args(ag, h), h->d_args_m, s);
+        rc = launch_aggregation(h, right_run_args(h->ag, h), h->d_args_m, s);
         if (rc != SIMSENSE_OK) return rc;
         SelectArgs sm = sa;
         sm.uniqueness_pct = 0;
@@ -425,15 +393,9 @@ int simsense_create(const simsense_params *params, simsense_handle **out)
     simsense_handle *h = new (std::nothrow) simsense_handle();
     if (!h) return SIMSENSE_ERR_OUT_OF_MEMORY;
     init_handle(h, params);
-    if (hipDeviceGetAttribute(&h->num_cus, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        h->num_cus = 256;
-    }
-    if (hipMalloc(&h->block, l.total) != hipSuccess || hipMalloc(&h->d_counter, 256) != hipSuccess ||
-        hipMalloc(&h->d_args, 2 * sizeof(AggregateArgs)) != hipSuccess) {
+    if (hipMalloc(&h->block, l.total) != hipSuccess || hipMalloc(&h->d_args, 2 * sizeof(AggregateArgs)) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(h->block);
-        (void)hipFree(h->d_counter);
         delete h;
         return SIMSENSE_ERR_OUT_OF_MEMORY;
     }
@@ -463,7 +425,6 @@ int simsense_destroy(simsense_handle *h)
     if (hipStreamSynchronize(h->last_stream) != hipSuccess) rc = SIMSENSE_ERR_DEVICE;
     if (hipFree(h->block) != hipSuccess) rc = SIMSENSE_ERR_DEVICE;
     if (hipFree(h->d_items) != hipSuccess) rc = SIMSENSE_ERR_DEVICE;
-    if (hipFree(h->d_counter) != hipSuccess) rc = SIMSENSE_ERR_DEVICE;
     if (hipFree(h->d_args) != hipSuccess) rc = SIMSENSE_ERR_DEVICE;
     prof_free(h);
     delete h;

@@ -2,9 +2,9 @@
 // launch.  Per pair slot the batch owns the same scratch a handle owns; the
 // argument blocks of every slot live in device tables, and each pass of the path
 // is one launch over all slots:
-//   counter reset -> census (every image) -> aggregation (a persistent kernel per
-//   padded-disparity group, pulling line blocks from a longest-first queue) ->
-//   selection (per group) -> median/depth.
+//   census (every image) -> aggregation (per padded-disparity group: costs, then
+//   the line blocks of all slots, largest first) -> selection (per group) ->
+//   median/depth.
 // The slots are split into phases of consecutive slots; each phase runs the pass
 // sequence on its own, on one of two streams in turn, and a phase's aggregation
 // starts when the previous phase's has finished, so that it runs while that phase
@@ -29,7 +29,7 @@ namespace {
 struct Slot {
     simsense_params p;
     int bits, Dpad, ndirs, hl;
-    bool wide;
+    bool wide, small;
     size_t off_census_l, off_census_r, off_paths[8], off_dint, off_s1, off_s2, off_dright, off_dsub, off_masked,
         off_flags;
 };
@@ -37,11 +37,8 @@ struct Slot {
 size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // phases the plain form of a batch of n slots is split into (consecutive slots, as
-// equal in number as can be; one phase for a single slot).  Measured on 256 sensor
-// pairs in 64-pair batches: 2271 pairs/s with 1 phase, 2392 with 4, 2453 with 8; at
-// most 7 padded-disparity groups per phase keep 8 phases within the 64 work-queue
-// counters.  The learned form, whose fused-net blocks need a whole unit, runs as
-// one phase (4 phases: 4% fewer pairs/s).
+// equal in number as can be; one phase for a single slot).  The learned form, whose
+// fused-net blocks need a whole unit, runs as one phase.
 constexpr int kBatchPhases = 8;
 int batch_phases(int n) { return std::min(n, kBatchPhases); }
 
@@ -51,7 +48,6 @@ struct simsense_batch {
     int n;
     std::vector<Slot> slots;
     simsense_batch_tuning tuning;
-    int num_cus;
     uint8_t *scratch;  // per-slot scratch
     size_t scratch_bytes;
     // device tables
@@ -60,7 +56,6 @@ struct simsense_batch {
     SelectArgs *d_sel;
     PostArgs *d_post;
     uint32_t *d_items;  // all item lists
-    unsigned *d_counters;
     // pinned staging of the pointer-dependent tables (double-buffered)
     CensusJob *h_cjobs[2];
     PostArgs *h_post[2];
@@ -68,8 +63,9 @@ struct simsense_batch {
     unsigned *h_uncertain;  // pinned: the learned form's per-pair counts, read back for the fallback
     int stage_idx;
     // launch plan
-    struct AggGroup { int dpad, hl; bool wide; size_t item_off; int nitems; int counter; };
-    struct SelGroup { int dpad, ndirs; bool small; size_t item_off; int nitems; };
+    // items: nitems longest first, then nlast, then the ncost cost rows
+    struct AggGroup { int dpad, hl; bool wide; size_t item_off; int nitems, nlast, ncost, cost_width; };
+    struct SelGroup { int dpad, nplanes; bool small; size_t item_off; int nitems; };
     // a phase: slots s0 .. s1-1, their item lists and groups (ranges of the vectors)
     struct Phase {
         int s0, s1;
@@ -125,9 +121,19 @@ int build_plan(simsense_batch *b)
         b->max_ch = std::max(b->max_ch, sl.p.census_h);
         b->max_w = std::max(b->max_w, sl.p.width);
     }
+    // lanes per horizontal line: the tuning's, else by each disparity range's widest
+    // slot (the slots of one range share a launch)
+    int64_t work = 0;
+    std::map<int, int> widest;
+    for (const Slot &sl : b->slots) {
+        work += aggregate_work(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.small);
+        widest[sl.Dpad] = std::max(widest[sl.Dpad], sl.p.width);
+    }
+    for (Slot &sl : b->slots)
+        sl.hl = horizontal_lanes_valid(sl.Dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
+                                                                            : default_lanes(widest[sl.Dpad], sl.Dpad, work);
     std::vector<AggregateArgs> agg(n);
     std::vector<SelectArgs> sel(n);
-    int counter = 0;
     b->lphases.clear();
     auto add_phase = [&](int s0, int s1, std::vector<simsense_batch::Phase> &dest) {
         simsense_batch::Phase P{};
@@ -143,67 +149,76 @@ int build_plan(simsense_batch *b)
         }
         P.census_nitems = (int)(items.size() - P.census_item_off);
         // aggregation: group slots by (Dpad, wide); items largest estimated work first
-        std::map<std::pair<int, bool>, std::vector<std::pair<int, uint32_t>>> groups;
+        struct Lists {
+            std::vector<std::pair<int, uint32_t>> first;
+            std::vector<uint32_t> last, cost;
+            int width = 0, hl = 0;
+        };
+        std::map<std::pair<int, bool>, Lists> groups;
         for (int s = P.s0; s < P.s1; ++s) {
             Slot &sl = b->slots[s];
-            sl.hl = horizontal_lanes_valid(sl.Dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
-                                                                                  : horizontal_lanes(sl.Dpad);
             AggregateArgs &a = agg[s];
             const int scale = a.max_item_work;  // set by an earlier plan, if any
             a = AggregateArgs{};
-            a.max_item_work = scale;
             a.census_l = b->scratch + sl.off_census_l;
             a.census_r = b->scratch + sl.off_census_r;
             a.W = sl.p.width; a.H = sl.p.height; a.D = sl.p.max_disp; a.Dpad = sl.Dpad; a.bits = sl.bits;
-            a.p1 = sl.p.p1; a.p2 = sl.p.p2; a.ndirs = sl.ndirs;
-            a.block_begin[0] = 0;
+            a.p1 = sl.p.p1; a.p2 = sl.p.p2;
+            uint8_t *buffers[8];
+            for (int r = 0; r < sl.ndirs; ++r) buffers[r] = b->scratch + sl.off_paths[r];
+            plan_aggregation(a, sl.ndirs, sl.small, false, sl.hl, buffers);
+            if (scale > 0) a.max_item_work = scale;
             auto &lst = groups[{sl.Dpad, sl.wide}];
-            for (int r = 0; r < sl.ndirs; ++r) {
-                a.dx[r] = kPathDx[r];
-                a.dy[r] = kPathDy[r];
-                a.out[r] = b->scratch + sl.off_paths[r];
-                const int nb = aggregate_blocks(kPathDx[r], kPathDy[r], a.W, a.H, sl.hl);
-                for (int k = 0; k < nb; ++k) {
-                    const int work = aggregate_block_work(kPathDx[r], kPathDy[r], k, a.W, a.H, sl.hl, sl.Dpad);
-                    lst.push_back({work, ((uint32_t)s << 20) | (uint32_t)(a.block_begin[r] + k)});
+            lst.hl = sl.hl;
+            const uint32_t tag = (uint32_t)s << 20;
+            for (int u = 0; u < a.nunits; ++u)
+                for (int k = a.item_begin[u]; k < a.item_begin[u + 1]; ++k) {
+                    if (u < a.last_first)
+                        lst.first.push_back({aggregate_item_work(a, u, k - a.item_begin[u], sl.hl), tag | (uint32_t)k});
+                    else
+                        lst.last.push_back(tag | (uint32_t)k);
                 }
-                a.block_begin[r + 1] = a.block_begin[r] + nb;
+            if (a.cost) {
+                for (int y = 0; y < a.H; ++y) lst.cost.push_back(tag | (uint32_t)y);
+                lst.width = std::max(lst.width, a.W);
             }
         }
         P.agg0 = (int)b->agg_groups.size();
         for (auto &kv : groups) {
-            auto &lst = kv.second;
-            std::stable_sort(lst.begin(), lst.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-            // the group's blocks run in one launch: its largest block sets the scale
-            // of every slot's issue priorities
-            const int gmax = lst.empty() ? 0 : lst.front().first;
+            Lists &lst = kv.second;
+            std::stable_sort(lst.first.begin(), lst.first.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+            // the group's items run in one launch: its largest sets the scale of
+            // every slot's issue priorities
             // (the plain form's phases set the scale; slots of equal size get the
             // same one in every plan)
             if (&dest == &b->phases)
-                for (auto &e : lst) agg[e.second >> 20].max_item_work = gmax;
+                for (auto &e : lst.first) agg[e.second >> 20].max_item_work = lst.first.front().first;
             simsense_batch::AggGroup gr{};
             gr.dpad = kv.first.first;
             gr.wide = kv.first.second;
-            gr.hl = horizontal_lanes_valid(gr.dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
-                                                                                : horizontal_lanes(gr.dpad);
+            gr.hl = lst.hl;
             gr.item_off = items.size();
-            gr.nitems = (int)lst.size();
-            gr.counter = counter++;
-            for (auto &e : lst) items.push_back(e.second);
+            gr.nitems = (int)lst.first.size();
+            gr.nlast = (int)lst.last.size();
+            gr.ncost = (int)lst.cost.size();
+            gr.cost_width = lst.width;
+            for (auto &e : lst.first) items.push_back(e.second);
+            items.insert(items.end(), lst.last.begin(), lst.last.end());
+            items.insert(items.end(), lst.cost.begin(), lst.cost.end());
             b->agg_groups.push_back(gr);
         }
         P.nagg = (int)b->agg_groups.size() - P.agg0;
-        // selection: group by (Dpad, ndirs, small)
+        // selection: group by (Dpad, planes, small)
         std::map<std::tuple<int, int, bool>, std::vector<uint32_t>> sgroups;
         for (int s = P.s0; s < P.s1; ++s) {
             const Slot &sl = b->slots[s];
             SelectArgs &a = sel[s];
             a = SelectArgs{};
-            for (int r = 0; r < sl.ndirs; ++r) a.paths[r] = b->scratch + sl.off_paths[r];
-            a.ndirs = sl.ndirs;
+            a.nplanes = aggregate_planes(sl.ndirs, sl.small);
+            for (int r = 0; r < a.nplanes; ++r) a.paths[r] = b->scratch + sl.off_paths[r];
             a.W = sl.p.width; a.H = sl.p.height; a.D = sl.p.max_disp; a.Dpad = sl.Dpad;
             a.uniqueness_pct = sl.p.uniqueness_pct; a.lr_max_diff = sl.p.lr_max_diff; a.subpixel = sl.p.subpixel;
-            a.small_values = sl.bits + sl.p.p2 <= 127;
+            a.small_values = sl.small;
             a.disp_int = b->scratch + sl.off_dint;
             a.cost_best = (uint16_t *)(b->scratch + sl.off_s1);
             a.cost_second = (uint16_t *)(b->scratch + sl.off_s2);
@@ -211,14 +226,14 @@ int build_plan(simsense_batch *b)
             a.disp_sub = (float *)(b->scratch + sl.off_dsub);
             a.masked = (float *)(b->scratch + sl.off_masked);
             a.flags = b->scratch + sl.off_flags;
-            auto &lst = sgroups[{sl.Dpad, sl.ndirs, a.small_values != 0}];
+            auto &lst = sgroups[{sl.Dpad, a.nplanes, sl.small}];
             for (int y = 0; y < sl.p.height; ++y) lst.push_back(((uint32_t)s << 20) | (uint32_t)y);
         }
         P.sel0 = (int)b->sel_groups.size();
         for (auto &kv : sgroups) {
             simsense_batch::SelGroup gr{};
             gr.dpad = std::get<0>(kv.first);
-            gr.ndirs = std::get<1>(kv.first);
+            gr.nplanes = std::get<1>(kv.first);
             gr.small = std::get<2>(kv.first);
             gr.item_off = items.size();
             gr.nitems = (int)kv.second.size();
@@ -240,7 +255,6 @@ int build_plan(simsense_batch *b)
     for (int ph = 0; ph < nph; ++ph)
         add_phase((int)((int64_t)n * ph / nph), (int)((int64_t)n * (ph + 1) / nph), b->phases);
     add_phase(0, n, b->lphases);
-    if (counter > 64) return SIMSENSE_ERR_UNSUPPORTED;  // the work-queue counters one batch holds
     b->census_wide = b->slots[0].wide;
 
     if (b->d_items) (void)hipFree(b->d_items);
@@ -257,12 +271,10 @@ __global__ void zero_words(unsigned *c, int n)
     for (int i = threadIdx.x; i < n; i += blockDim.x) c[i] = 0u;
 }
 
-// census of one phase's images (the launch also clears its work-queue counters)
+// census of one phase's images
 int enqueue_census_phase(simsense_batch *b, const simsense_batch::Phase &P, hipStream_t s)
 {
     CensusBatch cb{};
-    cb.zero = P.nagg > 0 ? b->d_counters + b->agg_groups[P.agg0].counter : nullptr;
-    cb.nzero = P.nagg;
     cb.jobs = b->d_cjobs;
     cb.items = b->d_items + P.census_item_off;
     cb.nitems = P.census_nitems;
@@ -279,10 +291,11 @@ int enqueue_aggregate_phase(simsense_batch *b, const simsense_batch::Phase &P, h
         AggregateQueue q{};
         q.slots = b->d_agg;
         q.items = b->d_items + g.item_off;
-        q.nitems = g.nitems;
-        q.counter = b->d_counters + g.counter;
-        const int grid = std::min(g.nitems, std::max(1, b->tuning.blocks_per_cu) * b->num_cus);
-        B_TRY(launch_aggregate_queue(q, g.dpad, g.wide, g.hl, grid, s));
+        q.nlast = g.nlast;
+        q.cost_items = q.items + g.nitems + g.nlast;
+        q.ncost = g.ncost;
+        q.cost_width = g.cost_width;
+        B_TRY(launch_aggregate_queue(q, g.dpad, g.wide, g.hl, g.nitems, s));
     }
     return SIMSENSE_OK;
 }
@@ -297,7 +310,7 @@ int enqueue_select_phase(simsense_batch *b, const simsense_batch::Phase &P, hipS
         sb.nitems = g.nitems;
         sb.max_width = b->max_w;
         sb.no_right = !need_right;
-        B_TRY(launch_select_batch(sb, g.dpad, g.ndirs, g.small, s));
+        B_TRY(launch_select_batch(sb, g.dpad, g.nplanes, g.small, s));
     }
     return SIMSENSE_OK;
 }
@@ -498,7 +511,6 @@ void free_batch(simsense_batch *b)
     (void)hipFree(b->d_sel);
     (void)hipFree(b->d_post);
     (void)hipFree(b->d_items);
-    (void)hipFree(b->d_counters);
     delete b;
 }
 
@@ -527,13 +539,13 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
     b->tuning.struct_size = sizeof(simsense_batch_tuning);
     b->tuning.horizontal_lanes = 0;
     b->tuning.blocks_per_cu = 2;
-    if (hipDeviceGetAttribute(&b->num_cus, hipDeviceAttributeMultiprocessorCount, 0) != hipSuccess) b->num_cus = 256;
     size_t total = 0;
     for (int s = 0; s < n; ++s) {
         Slot &sl = b->slots[s];
         sl.p = params[s];
         sl.bits = census_bits(sl.p.census_w, sl.p.census_h, sl.p.census_mode);
         sl.wide = sl.bits > 32;
+        sl.small = sl.bits + sl.p.p2 <= 127;
         sl.Dpad = padded_disp(sl.p.max_disp);
         sl.ndirs = sl.p.num_paths;
         const size_t npx = (size_t)sl.p.width * sl.p.height;
@@ -554,8 +566,7 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
     if (hipMalloc(&b->scratch, total) != hipSuccess || hipMalloc(&b->d_cjobs, 2 * n * sizeof(CensusJob)) != hipSuccess ||
         hipMalloc(&b->d_agg, n * sizeof(AggregateArgs)) != hipSuccess ||
         hipMalloc(&b->d_sel, n * sizeof(SelectArgs)) != hipSuccess ||
-        hipMalloc(&b->d_post, n * sizeof(PostArgs)) != hipSuccess ||
-        hipMalloc(&b->d_counters, 64 * sizeof(unsigned)) != hipSuccess)
+        hipMalloc(&b->d_post, n * sizeof(PostArgs)) != hipSuccess)
         rc = SIMSENSE_ERR_OUT_OF_MEMORY;
     for (int i = 0; i < 2 && rc == SIMSENSE_OK; ++i) {
         if (hipHostMalloc((void **)&b->h_cjobs[i], 2 * n * sizeof(CensusJob), 0) != hipSuccess ||

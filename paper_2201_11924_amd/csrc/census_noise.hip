@@ -167,8 +167,6 @@ template <typename Word>
 __global__ __launch_bounds__(256) void census_batch_kernel(CensusBatch b)
 {
     extern __shared__ uint8_t tile[];
-    const int tid = threadIdx.y * kCensusTx + threadIdx.x;
-    if (blockIdx.x == 0 && tid < b.nzero) b.zero[tid] = 0u;
     const uint32_t it = b.items[blockIdx.x];
     const CensusJob &j = b.jobs[it >> 20];
     const int t = (int)(it & 0xFFFFFu), tx = (j.W + kCensusTx - 1) / kCensusTx;
@@ -178,7 +176,6 @@ __global__ __launch_bounds__(256) void census_batch_kernel(CensusBatch b)
 hipError_t launch_census_batch(const CensusBatch &b, bool out64, hipStream_t s)
 {
     if (b.nitems == 0) return hipSuccess;
-    if (b.nzero < 0 || b.nzero > kCensusTx * kCensusTy) return hipErrorInvalidValue;
     const size_t lds = (size_t)(kCensusTx + b.max_cw - 1) * (kCensusTy + b.max_ch - 1);
     if (out64)
         hipLaunchKernelGGL(census_batch_kernel<uint64_t>, dim3(b.nitems), dim3(kCensusTx, kCensusTy), lds, s, b);

@@ -11,8 +11,6 @@ namespace ss {
 // Lanes that cooperate on one scanline: exactly one DPP row of a wave64, so
 // every cross-lane step of the path recurrence is a row-local DPP operation.
 constexpr int kLanesPerLine = 16;
-constexpr int kLinesPerBlock = 16;  // 256-thread blocks
-constexpr int kBlock = kLanesPerLine * kLinesPerBlock;
 
 // Disparities held by each lane; the padded disparity count is 16 * dpl.
 int pick_dpl(int max_disp);
@@ -24,35 +22,63 @@ int census_bits(int cw, int ch, int mode);
 extern const int kPathDx[8];
 extern const int kPathDy[8];
 int path_lines(int dx, int dy, int W, int H);
-// Default lanes per horizontal line.  Horizontal lines are the longest chains of
-// the aggregation, so they get more lanes than the other lines (fewer
-// instructions per step, a shorter chain) when the disparity count allows; 32
-// lanes measured fastest for single 1280x720 pairs with 2 and with 8 paths.
-constexpr int horizontal_lanes(int dpad) { return dpad % 32 == 0 ? 32 : 16; }
+// Default lanes per horizontal line of a slot W pixels wide, in a launch of total_work
+// (the sum of aggregate_work over its slots).  More lanes shorten the chain of a row's
+// steps, fewer spend less on the steps' cross-lane part.  Measured aggregation passes,
+// 16 / 32 / 64 lanes, at the launch's work per SIMD over a row's work (16 lanes):
+//   0.23 (640x480, D = 128, 2 paths) 99 / 72 / 65 us;  0.66 (960x540, D = 96, 4) 160 / 122;
+//   1.3 (848x480, D = 128, 8) 169 / 143 / 187;  1.9 (1280x720, D = 128, 8) 271 / 308 / 334;
+//   16 pairs of 1280x720, 2 paths, with the net: 2805 / 3043 / 3685.
+int default_lanes(int W, int dpad, int64_t total_work);
+int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool pairs);
 bool horizontal_lanes_valid(int dpad, int hl);
-// blocks of work of one direction, and the clocks block `blk` runs
-int aggregate_blocks(int dx, int dy, int W, int H, int hl);
-int aggregate_block_clocks(int dx, int dy, int blk, int W, int H, int hl);
-// Estimated VALU instructions per clock of a wave of a line block: about 7 per
-// disparity a lane holds, plus the per-step line overhead (larger for lines
-// spread over more than one DPP row).  The work of a block is clocks x this.
-constexpr int agg_step_cost(int dpl, int lanes_per_line) { return 7 * dpl + (lanes_per_line == 16 ? 10 : 18); }
-int aggregate_block_work(int dx, int dy, int blk, int W, int H, int hl, int dpad);
+// Disparities a lane of a line of `lanes` lanes holds: a whole number of words in
+// memory (lanes past the padded count idle), or 1 or 2.
+__host__ __device__ constexpr int lane_disparities(int dpad, int lanes)
+{
+    return dpad <= lanes ? 1 : dpad <= 2 * lanes ? 2 : dpad <= 4 * lanes ? 4 : dpad <= 8 * lanes ? 8 : dpad <= 12 * lanes ? 12 : 16;
+}
+// lanes a horizontal line runs with when hl are asked for: as many as hold two or more
+// disparities each, most of them in use
+__host__ __device__ constexpr int effective_lanes(int dpad, int hl)
+{
+    return hl == 64 && dpad >= 96 ? 64 : hl >= 32 && dpad >= 64 ? 32 : kLanesPerLine;
+}
+// Estimated instructions per step of a line: about 4 per disparity a lane holds,
+// plus the per-step line overhead (larger for lines spread over more than one DPP
+// row).
+__host__ __device__ constexpr int agg_step_cost(int dpl, int lanes_per_line) { return 4 * dpl + (lanes_per_line == 16 ? 12 : 18); }
 
+// One slot's aggregation: its units in launch order.  A unit is one direction, or a
+// direction with its opposite (pair: the buffer receives the sum of both path
+// values); item i of a unit is the lines of one block: four waves' (one per SIMD of a
+// compute unit), or for a pair two waves', each walked by two waves.
+constexpr int kWavesPerItem = 4;
 struct AggregateArgs {
     const void *census_l, *census_r;  // uint32 words, or uint64 when bits > 32
+    uint8_t *cost;       // cost volume the vertical and diagonal units read (null: none of them); for
+                         // block matching the 16-bit block costs of every unit
     int W, H, D, Dpad, bits, p1, p2;
-    int ndirs;
-    int dx[8], dy[8];
-    int block_begin[9];  // first block index of each direction, prefix sums
-    uint8_t *out[8];     // per-direction path values, W*H*Dpad bytes, d fastest
-    int max_item_work;   // largest block work of the launch (issue priorities)
+    int nunits;
+    int last_first;      // units from here on run after all others (they write over `cost`)
+    int dx[8], dy[8], pair[8];
+    int item_begin[9];   // first item index of each unit, prefix sums
+    uint8_t *out[8];     // per-unit path values, W*H*Dpad values, d fastest
+    int max_item_work;   // largest item work of the launch (issue priorities)
 };
+// Buffers the units of num_paths directions fill (consecutive ones of the path
+// buffers, from the first).  pairs: opposite directions, but the horizontal ones, are
+// stored as their sums; two path values must fit one value of the buffer.
+constexpr int aggregate_planes(int num_paths, bool pairs) { return pairs && num_paths > 2 ? num_paths / 2 + 1 : num_paths; }
+// Fills a's units for `buffers` (num_paths of them) and hl lanes per horizontal line,
+// from W, H and Dpad.  block: a.cost is the caller's and every unit reads it.
+void plan_aggregation(AggregateArgs &a, int num_paths, bool pairs, bool block, int hl, uint8_t *const *buffers);
+int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl);
 
 struct SelectArgs {
-    const uint8_t *paths[8];  // 8-bit path values, or 16-bit when values16
+    const uint8_t *paths[8];  // path values or sums of two, 8-bit, or 16-bit when values16
     int values16;
-    int ndirs;
+    int nplanes;              // buffers to sum (aggregate_planes)
     int W, H, D, Dpad;
     int uniqueness_pct, lr_max_diff, subpixel;
     int small_values;     // every path value < 128 (bits + P2 <= 127)
@@ -78,23 +104,23 @@ struct PostArgs {
 
 hipError_t launch_ir_noise(const uint8_t *in, const float *gamma, const float *n, uint8_t *out,
                            int64_t count, hipStream_t s);
-// (zero, nzero: counters the census launch clears on the way, so the work-queue
-// launch that follows needs no kernel of its own for that)
+// (zero, nzero: words the census launch clears on the way, if a caller has any)
 hipError_t launch_census(const uint8_t *img, int pitch, int W, int H, int cw, int ch, int mode,
                          void *out, bool out64, hipStream_t s, unsigned *zero = nullptr, int nzero = 0);
 // both images of a pair in one launch (img1 may be null: img0 alone)
 hipError_t launch_census_pair(const uint8_t *img0, const uint8_t *img1, int pitch, int W, int H, int cw, int ch,
                               int mode, void *out0, void *out1, bool out64, hipStream_t s, unsigned *zero = nullptr,
                               int nzero = 0);
+// every slot of a batch phase, or a handle's own single slot
 struct AggregateQueue {
     const AggregateArgs *slots;  // per pair slot (device)
-    const uint32_t *items;       // slot << 20 | block, longest first (device)
-    int nitems;
-    unsigned *counter;           // zero before the launch
+    const uint32_t *items;       // slot << 20 | item, largest work first (device), then the nlast
+    int nlast;                   // items of the units that run after the others
+    const uint32_t *cost_items;  // slot << 20 | row of the slots whose costs go to a volume (device)
+    int ncost, cost_width;       // their number, and the widest image among them
 };
 hipError_t launch_aggregate(const AggregateArgs &a, bool wide, int hl, hipStream_t s);
-// zeroes n <= 64 queue counters (a kernel, so that it may sit in a captured graph)
-hipError_t launch_zero_counters(unsigned *c, int n, hipStream_t s);
+// grid: the items before the last ones (one block each)
 hipError_t launch_aggregate_queue(const AggregateQueue &q, int dpad, bool wide, int hl, int grid, hipStream_t s);
 hipError_t launch_select(const SelectArgs &a, hipStream_t s);
 hipError_t launch_post(const PostArgs &a, hipStream_t s);
@@ -104,20 +130,18 @@ constexpr int kMaxBlockHalf = 15;  // SGBM blocks are at most 31 x 31
 // lanes per horizontal line of the block-cost-fed aggregation
 __host__ __device__ constexpr int volume_horizontal_lanes(int dpad)
 {
-    return dpad == 128 || dpad == 256 ? 64 : dpad == 64 ? 32 : kLanesPerLine;
+    return effective_lanes(dpad, dpad == 128 || dpad == 256 ? 64 : 32);
 }
 struct BlockCostArgs {
     const void *census_l, *census_r;  // uint32 words, or uint64 when bits > 32
-    int W, H, bits, bw, bh;
+    int W, H, D, bits, bw, bh;
     uint16_t *vol;                    // W*H*Dpad, d fastest
 };
+// cost of the padding disparities of a block-cost volume: no block cost plus P2
+// exceeds it
+constexpr int kBlockPadCost = 8191;
 struct VolumeArgs {
-    const uint16_t *vol;
-    int W, H, D, Dpad, p1, p2;
-    int ndirs;
-    int dx[8], dy[8];
-    int block_begin[9];  // 16-line blocks, prefix sums per direction
-    uint16_t *out[8];    // per-direction path values, (W*H + 1)*Dpad
+    AggregateArgs a;  // cost: the block-cost volume; 16-bit path values
 };
 hipError_t launch_block_cost(const BlockCostArgs &a, int dpad, bool wide, hipStream_t s);
 hipError_t launch_aggregate_volume(const VolumeArgs &a, hipStream_t s);
@@ -148,8 +172,6 @@ struct CensusBatch {
     const CensusJob *jobs;
     const uint32_t *items;
     int nitems, max_cw, max_ch;
-    unsigned *zero;  // counters cleared by the first block (nzero of them)
-    int nzero;
 };
 struct SelectBatch {
     const SelectArgs *slots;
@@ -163,13 +185,13 @@ struct PostBatch {
     int nitems;
 };
 hipError_t launch_census_batch(const CensusBatch &b, bool out64, hipStream_t s);
-hipError_t launch_select_batch(const SelectBatch &b, int dpad, int ndirs, bool small, hipStream_t s);
+hipError_t launch_select_batch(const SelectBatch &b, int dpad, int nplanes, bool small, hipStream_t s);
 hipError_t launch_post_batch(const PostBatch &b, hipStream_t s);
 int census_tiles(int W, int H);
 struct PathSet {
     const uint8_t *p[8];
 };
-hipError_t launch_volume_sum(const PathSet &paths, int ndirs, bool values16, int W, int H, int D, int Dpad,
+hipError_t launch_volume_sum(const PathSet &paths, int nplanes, bool values16, int W, int H, int D, int Dpad,
                              uint16_t *out, hipStream_t s);
 
 // ---------------------------------------------------------------- handle
@@ -187,6 +209,8 @@ Layout layout(const simsense_params *p);
 // fields derived from the parameters; the buffers carved from `base` (l.total bytes)
 void init_handle(simsense_handle *h, const simsense_params *params);
 void carve_scratch(simsense_handle *h, uint8_t *base, const Layout &l);
+// the handle's aggregation units for its lane count (its buffers are set)
+void plan_handle(simsense_handle *h);
 // Work common to the compute entry points; each returns a simsense_status.
 //  enqueue_match: census, aggregation and selection into the handle's scratch
 //                 (d*, S1, S2, dR, sub-pixel, masked disparity, flags bits 0..2);
@@ -209,13 +233,15 @@ struct simsense_handle {  // opaque to callers
     int bits, Dpad, ndirs;
     int hlanes;  // lanes per horizontal scanline
     bool wide;
-    // launch shape of the aggregation; for the persistent form, the work list
-    // (line blocks longest first), its counter and the argument block on the device
+    // launch shape of the aggregation; for the sorted form, the work list (items
+    // largest first, then the cost rows) and the argument block on the device
     simsense_batch_tuning tuning;
-    int num_cus, nitems;
+    int nitems, nlast, ncost;
     uint32_t *d_items;
-    unsigned *d_counter;
+    ss::AggregateArgs ag;  // the aggregation's units, set with the tuning
     ss::AggregateArgs *d_args;
+    bool pairs;    // two path values fit one of the path buffers' (bits + P2 <= 127, or 16 bits)
+    int nplanes;   // buffers the aggregation fills
     // full right-referenced run (lr_mode 1): x-flipped census maps (the right
     // image's as the reference), that run's per-pixel results and its arguments
     void *census_ml, *census_mr;

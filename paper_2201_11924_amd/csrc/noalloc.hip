@@ -2,7 +2,7 @@
 // and without any device allocation.  The scratch a handle would allocate (census
 // maps, per-direction path values, per-pixel results) lives in one file-scope
 // device array of fixed size; the kernels are the handle path's own, with the
-// aggregation launched one block per line block (no work list to upload).
+// aggregation's items in the order of its units (no work list to upload).
 #include <mutex>
 
 #include "internal.h"
@@ -60,7 +60,7 @@ extern "C" int simsense_compute_noalloc(const simsense_params *params, const uin
     if (rc != SIMSENSE_OK) return rc;
 
     // a handle on the stack: its buffers point into the static scratch, the
-    // aggregation runs one block per line block, profiling is off
+    // aggregation runs unsorted, profiling is off
     simsense_handle h{};
     init_handle(&h, params);
     carve_scratch(&h, base, l);
@@ -68,6 +68,7 @@ extern "C" int simsense_compute_noalloc(const simsense_params *params, const uin
     h.tuning.horizontal_lanes = 0;
     h.tuning.blocks_per_cu = 0;
     h.profiling = false;
+    plan_handle(&h);
     // every scratch byte a call reads is written earlier in the same call, so
     // nothing needs clearing between calls
     hipStream_t s = (hipStream_t)stream;

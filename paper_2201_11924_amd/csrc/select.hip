@@ -85,7 +85,7 @@ constexpr int kBufferWord3 = 0x00020000;
 constexpr int kLoadAux = 2;
 
 // The path values of one pixel come through raw buffer loads: one resource per
-// direction covers the block's image row, so all directions share one 32-bit
+// plane covers the block's image row, so all planes share one 32-bit
 // offset register instead of a 64-bit address each.
 template <int DPL>
 __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t off, Words<DPL, true> &o)
@@ -111,9 +111,10 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t o
 }
 
 // 16-bit path values: a sum of 8 directions stays below 2^16 (the parameters
-// bound each value by 8191), so packed pairs add as whole words
-template <int DPL, int NDIR>
-__device__ __forceinline__ void sum_paths16(const Words<DPL, true> (&v)[NDIR], uint32_t (&S)[DPL])
+// bound each value by 8191), so packed pairs add as whole words (a carry out of a
+// padding disparity only reaches other padding disparities, which are above it)
+template <int DPL, int NPL>
+__device__ __forceinline__ void sum_paths16(const Words<DPL, true> (&v)[NPL], uint32_t (&S)[DPL])
 {
     constexpr int N = Words<DPL, true>::N;
     uint32_t acc[N];
@@ -121,7 +122,7 @@ __device__ __forceinline__ void sum_paths16(const Words<DPL, true> (&v)[NDIR], u
     for (int k = 0; k < N; ++k) {
         acc[k] = 0;
 #pragma unroll
-        for (int r = 0; r < NDIR; ++r) acc[k] += v[r].w[k];
+        for (int r = 0; r < NPL; ++r) acc[k] += v[r].w[k];
     }
 #pragma unroll
     for (int j = 0; j < DPL; ++j) S[j] = (j & 1) ? (acc[j / 2] >> 16) : (acc[j / 2] & 0xFFFFu);
@@ -162,36 +163,28 @@ __device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, uint32_t o
     }
 }
 
-// S(d) = sum over directions of the path bytes.  Bytes are split into two
+// S(d) = sum over the planes of the path bytes.  Bytes are split into two
 // 16-bit lanes per word (bytes 0,2 and bytes 1,3) and summed there; no lane
-// can carry into the next because a sum of 8 bytes is below 2^16.  When every
-// path value is below 128 (bits + P2 <= 127) two directions are first added as
-// whole words, since no byte of such a sum can carry.
-template <int DPL, int NDIR, bool SMALL>
-__device__ __forceinline__ void sum_paths(const Words<DPL> (&v)[NDIR], uint32_t (&S)[DPL])
+// can carry into the next because a sum of 8 bytes is below 2^16.  SMALL: every
+// path value is below 128, and single ones (all planes, or the first two of an odd
+// number, whose others hold sums of two already) are first added as whole words in
+// twos, since no byte of such a sum can carry.
+template <int DPL, int NPL, bool SMALL>
+__device__ __forceinline__ void sum_paths(const Words<DPL> (&v)[NPL], uint32_t (&S)[DPL])
 {
     constexpr int N = Words<DPL>::N;
+    constexpr int kTwos = !SMALL ? 0 : NPL % 2 == 0 ? NPL : 2;
     uint32_t lo[N], hi[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) lo[k] = hi[k] = 0;
-    if constexpr (SMALL) {
 #pragma unroll
-        for (int r = 0; r < NDIR; r += 2)
+    for (int r = 0; r < NPL; r += r < kTwos ? 2 : 1)
 #pragma unroll
-            for (int k = 0; k < N; ++k) {
-                const uint32_t w = v[r].w[k] + v[r + 1].w[k];
-                lo[k] += w & 0x00FF00FFu;
-                hi[k] += (w >> 8) & 0x00FF00FFu;
-            }
-    } else {
-#pragma unroll
-        for (int r = 0; r < NDIR; ++r)
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                lo[k] += v[r].w[k] & 0x00FF00FFu;
-                hi[k] += (v[r].w[k] >> 8) & 0x00FF00FFu;
-            }
-    }
+        for (int k = 0; k < N; ++k) {
+            const uint32_t w = r < kTwos ? v[r].w[k] + v[r + 1].w[k] : v[r].w[k];
+            lo[k] += w & 0x00FF00FFu;
+            hi[k] += (w >> 8) & 0x00FF00FFu;
+        }
 #pragma unroll
     for (int j = 0; j < DPL; ++j) {
         const int k = j / 4, b = j % 4;
@@ -228,7 +221,7 @@ constexpr size_t select_lds_bytes(int W)
     return ((size_t)kLanesPerLine * DPL + W) * 4 + (size_t)W * 10;
 }
 
-template <int DPL, int NDIR, bool SMALL, bool V16 = false>
+template <int DPL, int NPL, bool SMALL, bool V16 = false>
 __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t *smem, bool right)
 {
     constexpr int kValBytes = V16 ? 2 : 1;
@@ -257,22 +250,22 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
     // wait for it), and look-ahead loads are unconditional (clamped to the row's
     // last pixel) so every wait counts the same loads
     constexpr int kRing = sel_ring(DPL, V16, SMALL);
-    __amdgpu_buffer_rsrc_t rs[NDIR];
+    __amdgpu_buffer_rsrc_t rs[NPL];
 #pragma unroll
-    for (int r = 0; r < NDIR; ++r) {
+    for (int r = 0; r < NPL; ++r) {
         const uint8_t *base = uniform_ptr(a.paths[r]) + row * kDpad * kValBytes;
         rs[r] = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, W * kDpad * kValBytes, kBufferWord3);
     }
-    Words<DPL, V16> ring[kRing][NDIR];
-    auto load_px = [&](int x, Words<DPL, V16>(&v)[NDIR]) {
+    Words<DPL, V16> ring[kRing][NPL];
+    auto load_px = [&](int x, Words<DPL, V16>(&v)[NPL]) {
         const uint32_t off = (uint32_t)((min(x, W - 1) * kDpad + d0) * kValBytes);
 #pragma unroll
-        for (int r = 0; r < NDIR; ++r) load_words<DPL>(rs[r], off, v[r]);
+        for (int r = 0; r < NPL; ++r) load_words<DPL>(rs[r], off, v[r]);
     };
-    auto process = [&](int x, const Words<DPL, V16>(&v)[NDIR]) {
+    auto process = [&](int x, const Words<DPL, V16>(&v)[NPL]) {
         uint32_t S[DPL];
-        if constexpr (V16) sum_paths16<DPL, NDIR>(v, S);
-        else sum_paths<DPL, NDIR, SMALL>(v, S);
+        if constexpr (V16) sum_paths16<DPL, NPL>(v, S);
+        else sum_paths<DPL, NPL, SMALL>(v, S);
         if (D < kDpad) {
             // padding disparities: a cost above every real one (real S < 2^16 - 8)
 #pragma unroll
@@ -356,56 +349,68 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
     }
 }
 
-template <int DPL, int NDIR, bool SMALL, bool V16>
+template <int DPL, int NPL, bool SMALL, bool V16>
 __global__ __launch_bounds__(kSelBlock, sel_waves_per_simd(DPL, V16, SMALL)) void select_kernel(SelectArgs a)
 {
     extern __shared__ uint32_t smem[];
-    select_row<DPL, NDIR, SMALL, V16>(a, (int)blockIdx.x, smem, !a.no_right);
+    select_row<DPL, NPL, SMALL, V16>(a, (int)blockIdx.x, smem, !a.no_right);
 }
 
 // batch form: one block per (pair slot, row) item
-template <int DPL, int NDIR, bool SMALL>
+template <int DPL, int NPL, bool SMALL>
 __global__ __launch_bounds__(kSelBlock, sel_waves_per_simd(DPL, false, SMALL)) void select_batch_kernel(SelectBatch b)
 {
     extern __shared__ uint32_t smem[];
     const uint32_t it = b.items[blockIdx.x];
     const SelectArgs &a = b.slots[it >> 20];
-    select_row<DPL, NDIR, SMALL>(a, (int)(it & 0xFFFFFu), smem, !(b.no_right || a.no_right));
+    select_row<DPL, NPL, SMALL>(a, (int)(it & 0xFFFFFu), smem, !(b.no_right || a.no_right));
 }
 
 namespace {
-template <int DPL, int NDIR>
-void launch_sel3(const SelectArgs *a, const SelectBatch *b, bool small, hipStream_t s)
+template <int DPL, int NPL, bool SMALL, bool V16>
+void launch_sel3(const SelectArgs *a, const SelectBatch *b, hipStream_t s)
 {
     dim3 block(kSelBlock);
-    if (a) {
-        const size_t lds = select_lds_bytes<DPL>(a->W);
-        if (a->values16) hipLaunchKernelGGL((select_kernel<DPL, NDIR, false, true>), dim3(a->H), block, lds, s, *a);
-        else if (small) hipLaunchKernelGGL((select_kernel<DPL, NDIR, true, false>), dim3(a->H), block, lds, s, *a);
-        else hipLaunchKernelGGL((select_kernel<DPL, NDIR, false, false>), dim3(a->H), block, lds, s, *a);
-    } else {
-        const size_t lds = select_lds_bytes<DPL>(b->max_width);
-        if (small) hipLaunchKernelGGL((select_batch_kernel<DPL, NDIR, true>), dim3(b->nitems), block, lds, s, *b);
-        else hipLaunchKernelGGL((select_batch_kernel<DPL, NDIR, false>), dim3(b->nitems), block, lds, s, *b);
+    if (a)
+        hipLaunchKernelGGL((select_kernel<DPL, NPL, SMALL, V16>), dim3(a->H), block, select_lds_bytes<DPL>(a->W), s, *a);
+    else if constexpr (!V16)
+        hipLaunchKernelGGL((select_batch_kernel<DPL, NPL, SMALL>), dim3(b->nitems), block,
+                           select_lds_bytes<DPL>(b->max_width), s, *b);
+}
+
+// planes: one per direction (2, 4, 8), or the two horizontal ones and the sums of the
+// others' pairs (3, 5; byte sums only of small values)
+template <int DPL, bool SMALL, bool V16>
+void launch_sel2(const SelectArgs *a, const SelectBatch *b, int nplanes, hipStream_t s)
+{
+    switch (nplanes) {
+    case 2: return launch_sel3<DPL, 2, SMALL, V16>(a, b, s);
+    case 4: return launch_sel3<DPL, 4, SMALL, V16>(a, b, s);
+    case 8: return launch_sel3<DPL, 8, SMALL, V16>(a, b, s);
+    default: break;
+    }
+    if constexpr (SMALL || V16) {
+        if (nplanes == 3) launch_sel3<DPL, 3, SMALL, V16>(a, b, s);
+        else launch_sel3<DPL, 5, SMALL, V16>(a, b, s);
     }
 }
 template <int DPL>
-void launch_sel2(const SelectArgs *a, const SelectBatch *b, int ndirs, bool small, hipStream_t s)
+void launch_sel1(const SelectArgs *a, const SelectBatch *b, int nplanes, bool small, hipStream_t s)
 {
-    if (ndirs == 2) launch_sel3<DPL, 2>(a, b, small, s);
-    else if (ndirs == 4) launch_sel3<DPL, 4>(a, b, small, s);
-    else launch_sel3<DPL, 8>(a, b, small, s);
+    if (a && a->values16) launch_sel2<DPL, false, true>(a, b, nplanes, s);
+    else if (small) launch_sel2<DPL, true, false>(a, b, nplanes, s);
+    else launch_sel2<DPL, false, false>(a, b, nplanes, s);
 }
-hipError_t launch_sel(const SelectArgs *a, const SelectBatch *b, int dpad, int ndirs, bool small, hipStream_t s)
+hipError_t launch_sel(const SelectArgs *a, const SelectBatch *b, int dpad, int nplanes, bool small, hipStream_t s)
 {
     switch (dpad / kLanesPerLine) {
-    case 1: launch_sel2<1>(a, b, ndirs, small, s); break;
-    case 2: launch_sel2<2>(a, b, ndirs, small, s); break;
-    case 4: launch_sel2<4>(a, b, ndirs, small, s); break;
-    case 6: launch_sel2<6>(a, b, ndirs, small, s); break;
-    case 8: launch_sel2<8>(a, b, ndirs, small, s); break;
-    case 12: launch_sel2<12>(a, b, ndirs, small, s); break;
-    case 16: launch_sel2<16>(a, b, ndirs, small, s); break;
+    case 1: launch_sel1<1>(a, b, nplanes, small, s); break;
+    case 2: launch_sel1<2>(a, b, nplanes, small, s); break;
+    case 4: launch_sel1<4>(a, b, nplanes, small, s); break;
+    case 6: launch_sel1<6>(a, b, nplanes, small, s); break;
+    case 8: launch_sel1<8>(a, b, nplanes, small, s); break;
+    case 12: launch_sel1<12>(a, b, nplanes, small, s); break;
+    case 16: launch_sel1<16>(a, b, nplanes, small, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -414,13 +419,13 @@ hipError_t launch_sel(const SelectArgs *a, const SelectBatch *b, int dpad, int n
 
 hipError_t launch_select(const SelectArgs &a, hipStream_t s)
 {
-    return launch_sel(&a, nullptr, a.Dpad, a.ndirs, a.small_values != 0, s);
+    return launch_sel(&a, nullptr, a.Dpad, a.nplanes, a.small_values != 0, s);
 }
 
-hipError_t launch_select_batch(const SelectBatch &b, int dpad, int ndirs, bool small, hipStream_t s)
+hipError_t launch_select_batch(const SelectBatch &b, int dpad, int nplanes, bool small, hipStream_t s)
 {
     if (b.nitems == 0) return hipSuccess;
-    return launch_sel(nullptr, &b, dpad, ndirs, small, s);
+    return launch_sel(nullptr, &b, dpad, nplanes, small, s);
 }
 
 // ---------------------------------------------------------------- median + depth
@@ -490,26 +495,26 @@ hipError_t launch_post_batch(const PostBatch &b, hipStream_t s)
 }
 
 // ---------------------------------------------------------------- debug volume
-__global__ __launch_bounds__(256) void volume_sum_kernel(PathSet paths, int ndirs, int values16,
+__global__ __launch_bounds__(256) void volume_sum_kernel(PathSet paths, int nplanes, int values16,
                                                          size_t npix, int D, int Dpad, uint16_t *out)
 {
     const size_t total = npix * D;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
         const size_t p = i / D, d = i - p * D;
         uint32_t s = 0;
-        for (int r = 0; r < ndirs; ++r)
+        for (int r = 0; r < nplanes; ++r)
             s += values16 ? ((const uint16_t *)paths.p[r])[p * Dpad + d] : paths.p[r][p * Dpad + d];
         out[i] = (uint16_t)s;
     }
 }
 
-hipError_t launch_volume_sum(const PathSet &paths, int ndirs, bool values16, int W, int H, int D, int Dpad,
+hipError_t launch_volume_sum(const PathSet &paths, int nplanes, bool values16, int W, int H, int D, int Dpad,
                              uint16_t *out, hipStream_t s)
 {
     size_t total = (size_t)W * H * D;
     size_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(volume_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s, paths, ndirs, (int)values16,
+    hipLaunchKernelGGL(volume_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s, paths, nplanes, (int)values16,
                        (size_t)W * H, D, Dpad, out);
     return hipGetLastError();
 }

@@ -5,10 +5,8 @@
 //
 // Two kernels: block_cost_kernel writes the block-cost volume (16-bit, d
 // fastest, the path buffers' layout); aggregate_volume_kernel runs the path
-// recurrence of every scanline of every direction from that volume.  The
-// recurrence, the line layout of a block and the cross-lane steps are those of
-// the census-fed aggregation; the cost source, the value width and the load
-// schedule differ.
+// recurrence of every line from that volume, with the lines, steps and pairs of
+// the census-fed aggregation.
 #include "aggregate_impl.h"
 
 namespace ss {
@@ -69,7 +67,7 @@ __global__ __launch_bounds__(256) void block_cost_kernel(BlockCostArgs a)
                 __builtin_amdgcn_global_load_lds(src, &tile[256 * k + (tid & ~63)], 4, 0, 0);
             }
         }
-        __builtin_amdgcn_s_waitcnt(vmcnt_encoding(0));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         for (int rr = 0; rr < nrows; ++rr) {
             const Word *sl = (const Word *)tile + rr * kRowWords, *sr = sl + kLeftWords;
@@ -91,182 +89,40 @@ __global__ __launch_bounds__(256) void block_cost_kernel(BlockCostArgs a)
     if (x < W) {
         uint16_t *o = a.vol + ((size_t)y * W + x) * kDpad + lane;
 #pragma unroll
-        for (int j = 0; j < DPL; ++j) o[16 * j] = (uint16_t)acc[j];
+        for (int j = 0; j < DPL; ++j) o[16 * j] = (uint16_t)(lane + 16 * j < a.D ? acc[j] : (uint32_t)kBlockPadCost);
     }
 }
 
 // ---------------------------------------------------------------- aggregation
-// A lane's DPL 16-bit costs as loaded: packed two per word (one word for DPL 1)
+// The units' lines from the block-cost volume (16-bit path values): the horizontal
+// ones singly, with volume_horizontal_lanes() lanes each (the longest chains: fewer
+// disparities per lane shorten every step), the others in pairs.
 template <int DPL>
-constexpr int packed_words() { return DPL == 1 ? 1 : DPL / 2; }
-
-template <int DPL>
-__device__ __forceinline__ void load_packed(const uint16_t *src, uint32_t (&w)[packed_words<DPL>()])
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(2, 2))) void aggregate_volume_kernel(VolumeArgs v)
 {
-    constexpr int NW = packed_words<DPL>();
-    if constexpr (DPL == 1) {
-        w[0] = *src;
+    constexpr int kDpad = kLanesPerLine * DPL, HL = volume_horizontal_lanes(kDpad);
+    constexpr int HD = lane_disparities(kDpad, HL), LD = lane_disparities(kDpad, kLanesPerLine);
+    const AggregateArgs &a = v.a;
+    int item = (int)blockIdx.x, unit = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) unit += (k < a.nunits && item >= a.item_begin[k]) ? 1 : 0;
+    item -= a.item_begin[unit];
+    const int w = uniform((int)threadIdx.x >> 6);
+    const uint32_t p1 = both(a.p1), p2 = both(a.p2);
+    const int dx = a.dx[unit], dy = a.dy[unit], nlines = line_count(dx, dy, a.W, a.H);
+    if (dy == 0) {
+        const int wave = item * kWavesPerItem + w;
+        if (wave * (64 / HL) >= nlines) return;
+        const WaveLines g = wave_lines<HL, 2 * kDpad>(dx, dy, wave, a.W, a.H, (int)threadIdx.x % HL * (2 * HD));
+        run_single<kDpad, HD, HL, true>(a.cost, a.out[unit], g, p1, p2, agg_step_cost(HD, HL), a.max_item_work);
     } else {
-        const uint32_t *p = (const uint32_t *)src;
-        if constexpr (NW % 4 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 4) {
-                const uint4 q = *(const uint4 *)(p + i);
-                w[i] = q.x; w[i + 1] = q.y; w[i + 2] = q.z; w[i + 3] = q.w;
-            }
-        } else if constexpr (NW % 2 == 0) {
-#pragma unroll
-            for (int i = 0; i < NW; i += 2) {
-                const uint2 q = *(const uint2 *)(p + i);
-                w[i] = q.x; w[i + 1] = q.y;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NW; ++i) w[i] = p[i];
-        }
+        const int wave = item * (kWavesPerItem / 2) + w / 2;
+        const WaveLines g = wave_lines<kLanesPerLine, 2 * kDpad>(dx, dy, wave, a.W, a.H,
+                                                                 (int)threadIdx.x % kLanesPerLine * (2 * LD));
+        run_pair<kDpad, LD, kLanesPerLine, true, sum_steps(LD, true)>(a.cost, a.out[unit], g,
+                                                                      wave * (64 / kLanesPerLine) < nlines, w & 1, p1, p2,
+                                                                      agg_step_cost(LD, kLanesPerLine), a.max_item_work);
     }
-}
-
-template <int DPL>
-__device__ __forceinline__ uint32_t packed_cost(const uint32_t (&w)[packed_words<DPL>()], int j)
-{
-    if constexpr (DPL == 1) return w[0];
-    else return (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu;
-}
-
-// The lines of one block of one direction (LPL lanes per line, kBlock / LPL
-// lines), fed from the block-cost volume; the costs of a clock are loaded
-// several clocks ahead (the ring below).
-template <int DPL, bool HORIZ, int LPL = kLanesPerLine>
-__device__ __forceinline__ void run_lines_volume(const VolumeArgs &a, const BlockGeom &g, uint16_t *out)
-{
-    using LO = LineOps<LPL>;
-    constexpr int kDpad = LPL * DPL;
-    const int W = a.W, H = a.H, D = a.D;
-    const int lane = threadIdx.x % LPL, li = threadIdx.x / LPL;
-    const bool first = lane == 0, last = lane == LPL - 1;
-    const int d0 = lane * DPL;
-    const uint32_t p1 = a.p1, p2 = a.p2;
-    const size_t trash = (size_t)W * H * kDpad + d0;
-
-    int row0 = 0, xm0 = 0, xlane = 0, len = 0, skew = 0;
-    if (HORIZ) {
-        if (li < g.nvalid) len = W;
-    } else if (g.kind == 1) {
-        row0 = g.ye;
-        xm0 = g.g0;
-        xlane = li;
-        if (li < g.nvalid) {
-            const int x0 = g.g0 + li;
-            len = g.dx == 0 ? H : min(g.dx > 0 ? W - x0 : x0 + 1, H);
-        }
-    } else {
-        row0 = g.ye + g.dy * (g.j0 + 1);
-        xm0 = g.dx > 0 ? g.xe - (kChunk - 1) : g.xe;
-        xlane = g.dx > 0 ? kChunk - 1 - li : li;
-        skew = li;
-        if (li < g.nvalid) len = min(W, H - g.j0 - li - 1);
-    }
-    auto locate = [&](int t, int &row, int &x) {
-        if (HORIZ) {
-            row = g.r0 + li;
-            x = g.xs + t * g.dx;
-        } else {
-            row = row0 + t * g.dy;
-            x = xm0 + t * g.dx + xlane;
-        }
-    };
-    constexpr int NP = packed_words<DPL>();
-    auto load = [&](int t, uint32_t (&c)[NP]) {
-        int row, x;
-        locate(t, row, x);
-        row = min(max(row, 0), H - 1);
-        x = min(max(x, 0), W - 1);
-        load_packed<DPL>(a.vol + ((size_t)row * W + x) * kDpad + d0, c);
-    };
-
-    // costs come through a ring of kRing clocks (packed as loaded), loaded
-    // kRing - 1 clocks ahead: a launch of these lines holds about one wave per
-    // SIMD, so each wave must keep many loads in flight to cover the memory
-    // latency; the clock loop is unrolled over the ring so the slots stay in
-    // fixed registers
-    constexpr int kRing = DPL <= 8 ? 12 : 8;
-    uint32_t Q[DPL], ring[kRing][NP];
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) Q[j] = 0;
-    auto step = [&](int t, const uint32_t (&cw)[NP]) {
-        const int s = t - skew;
-        int row, x;
-        locate(t, row, x);
-        const bool active = s >= 0 && s < len;
-        const uint32_t qm_edge = LO::from_prev(Q[DPL - 1], first);
-        const uint32_t qp_edge = LO::from_next(Q[0], last);
-        uint32_t L[DPL];
-        uint32_t m = 0xFFFFFFFFu;
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) {
-            uint32_t c = d0 + j < D ? packed_cost<DPL>(cw, j) : kPadCost;
-            c = s < 0 ? 0u : c;  // a line that has not started stays at Q = 0
-            const uint32_t qm = j > 0 ? Q[j - 1] : qm_edge;
-            const uint32_t qp = j < DPL - 1 ? Q[j + 1] : qp_edge;
-            L[j] = min(min(Q[j], min(qm, qp) + p1), p2) + c;
-            m = min(m, L[j]);
-        }
-        m = LO::line_min(m);
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) Q[j] = L[j] - m;
-        const size_t o = active ? ((size_t)row * W + x) * kDpad + d0 : trash;
-        store_u16<DPL>(out + o, L);
-    };
-    // clock t sits in slot t % kRing; clocks 0..kRing-2 are loaded up front
-    // and clock t + kRing - 1 while clock t is computed
-    static_for<kRing - 1>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        load(k, ring[k]);  // clamped position when k >= clocks
-    });
-    auto group = [&](int t0) {
-        static_for<kRing>([&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            const int t = t0 + r;
-            // (past the last clock the load is of a clamped, unused position:
-            // unconditional, so every wait counts a fixed number of loads)
-            load(t + kRing - 1, ring[(r + kRing - 1) % kRing]);
-            step(t, ring[r]);
-        });
-    };
-    // the first group runs ahead of the loop, so the loop is entered with the
-    // loads in flight that each of its iterations leaves (the waits inside it
-    // can then count exactly)
-    int t0 = 0;
-    if (g.clocks >= kRing) {
-        group(0);
-        for (t0 = kRing; t0 + kRing <= g.clocks; t0 += kRing) group(t0);
-    }
-    // the last clocks (fewer than kRing), already loaded
-    static_for<kRing - 1>([&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-        if (t0 + r < g.clocks) step(t0 + r, ring[r]);
-    });
-}
-
-// Horizontal lines (the longest, W clocks) run with volume_horizontal_lanes()
-// lanes each, so fewer disparities per lane shorten every clock and the launch
-// holds more waves; the other directions keep 16 lanes per line.
-template <int DPL>
-__global__ __launch_bounds__(kBlock) void aggregate_volume_kernel(VolumeArgs a)
-{
-    constexpr int kDpad = kLanesPerLine * DPL;
-    constexpr int kHL = volume_horizontal_lanes(kDpad);
-    const int blk = (int)blockIdx.x;
-    int dir = 0;
-#pragma unroll
-    for (int k = 1; k < 8; ++k)
-        if (k < a.ndirs && blk >= a.block_begin[k]) dir = k;
-    const bool horiz = a.dy[dir] == 0;
-    const BlockGeom g = block_geometry(a.dx[dir], a.dy[dir], blk - a.block_begin[dir], a.W, a.H,
-                                       horiz ? kBlock / kHL : kLinesPerBlock);
-    if (horiz) run_lines_volume<kDpad / kHL, true, kHL>(a, g, a.out[dir]);
-    else run_lines_volume<DPL, false>(a, g, a.out[dir]);
 }
 
 template <int DPL>
@@ -277,8 +133,7 @@ hipError_t launch_sgbm_dpl(const BlockCostArgs *bc, const VolumeArgs *va, bool w
         if (wide) hipLaunchKernelGGL((block_cost_kernel<DPL, true>), grid, block, 0, s, *bc);
         else hipLaunchKernelGGL((block_cost_kernel<DPL, false>), grid, block, 0, s, *bc);
     } else {
-        if (va->block_begin[va->ndirs] == 0) return hipSuccess;
-        hipLaunchKernelGGL((aggregate_volume_kernel<DPL>), dim3(va->block_begin[va->ndirs]), dim3(kBlock), 0, s, *va);
+        hipLaunchKernelGGL((aggregate_volume_kernel<DPL>), dim3(va->a.item_begin[va->a.nunits]), dim3(64 * kWavesPerItem), 0, s, *va);
     }
     return hipGetLastError();
 }
@@ -307,7 +162,7 @@ hipError_t launch_block_cost(const BlockCostArgs &a, int dpad, bool wide, hipStr
 
 hipError_t launch_aggregate_volume(const VolumeArgs &a, hipStream_t s)
 {
-    return launch_sgbm(nullptr, &a, a.Dpad, false, s);
+    return launch_sgbm(nullptr, &a, a.a.Dpad, false, s);
 }
 
 }  // namespace ss
