@@ -51,9 +51,9 @@ bool horizontal_lanes_valid(int dpad, int hl)
     return (hl == 16 || hl == 32 || hl == 64) && dpad % hl == 0;
 }
 
-int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool pairs)
+int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums)
 {
-    const int walks = pairs ? 2 * 2 + 3 * (num_paths - 2) : 2 * num_paths;  // twice the walks over the image
+    const int walks = sums ? 2 * 2 + 3 * (num_paths - 2) : 2 * num_paths;  // twice the walks over the image
     return (int64_t)W * H / 4 * walks / 2 * agg_step_cost(lane_disparities(dpad, kLanesPerLine), kLanesPerLine);
 }
 
@@ -65,18 +65,28 @@ int default_lanes(int W, int dpad, int64_t total_work)
     return 10 * per_simd >= 16 * row ? 16 : 10 * per_simd >= 5 * row ? 32 : 64;
 }
 
-// Units.  Horizontal directions are units of their own (their lines are the longest
-// chains: walking them one and a half times would hold up the launch).  The cost
-// volume takes the last path buffer: pairs leave it free; otherwise the direction that
-// fills it runs after all others and replaces each cost by its path value (each is
-// read once, before it is overwritten), so the scratch stays one buffer per direction.
-void plan_aggregation(AggregateArgs &a, int num_paths, bool pairs, bool block, int hl, uint8_t *const *buffers)
+bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl)
 {
-    if (!block) a.cost = num_paths > 2 ? buffers[num_paths - 1] : nullptr;
+    return num_paths > 2 && row_pairs_built(effective_lanes(dpad, hl), wide) && (int64_t)W * H * dpad > (int64_t)256 << 20;
+}
+
+// Units.  Horizontal directions are units of their own unless row_sums (their lines
+// are the longest chains: walking them one and a half times holds up the launch).  They
+// count census bits themselves where that is one word a pixel, and read the volume where
+// it is two (641x479, D = 100, full census: aggregation 215 -> 176 us; one word,
+// 1280x720: 277 -> 289 us).  The cost
+// volume takes the last path buffer: sums leave it free; otherwise, without a spare
+// one, the direction that fills it runs after all others and replaces each cost by its
+// path value (each is read once, before it is overwritten).
+void plan_aggregation(AggregateArgs &a, int num_paths, bool sums, bool row_sums, bool block, int hl, uint8_t *const *buffers,
+                      int nbuffers)
+{
+    if (!block) a.cost = num_paths > 2 ? buffers[nbuffers - 1] : nullptr;
+    a.row_costs = a.cost && (block || a.bits > 32);
     a.nunits = 0;
     for (int r = 0; r < num_paths; ++r) {
-        const bool pair = pairs && kPathDy[r] != 0;
-        if (pair && kPathDy[r] < 0) continue;  // stored with its opposite
+        const bool pair = sums && (kPathDy[r] != 0 || row_sums);
+        if (pair && (kPathDy[r] < 0 || (kPathDy[r] == 0 && kPathDx[r] < 0))) continue;  // stored with its opposite
         const int u = a.nunits++;
         a.dx[u] = kPathDx[r];
         a.dy[u] = kPathDy[r];

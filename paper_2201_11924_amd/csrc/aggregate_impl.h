@@ -27,10 +27,7 @@
 // No LDS; a wave owns its lines alone, or shares them with one other (below).
 //
 // Two kinds of unit:
-//  * single: one direction, its path values stored as bytes, one buffer per
-//    direction.  The horizontal directions run this way from the census words
-//    (a lane's right words slide by one column per step, so a segment of 8 steps
-//    needs 8 new words per lane: four 16-byte loads in all).
+//  * single: one direction, its path values stored as bytes.
 //  * pair: a direction and its opposite, whose lines are the same pixels; the SUM of
 //    both path values is stored, so that one byte per pixel and disparity is written,
 //    and read by the selection, instead of two (both passes are bound by that
@@ -41,7 +38,9 @@
 // cost_kernel wrote (1 byte per pixel and disparity, in the path buffers' layout):
 // recomputing them from the census words costs 4.7 SIMD cycles more per disparity
 // and step than unpacking a byte.  Costs where x - d < 0 are `bits`, and 255 where
-// d >= D, so the steps need no border case.
+// d >= D, so the steps need no border case.  Horizontal units count the bits of
+// 32-bit census words themselves (a lane's right words slide by one column per step:
+// the pixels of a segment share all but a few), which saves the reads.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -460,49 +459,188 @@ __device__ __forceinline__ int index_of(int q, int s, bool back)
     return q * S + (back ? S - 1 - s : s);
 }
 
-// the costs of segment q, in walking order: all S pixels (WHOLE: the caller knows
-// that every line has them), or those that exist (the others read as zero cost,
-// which leaves a line's state before its first pixel as it is)
-template <bool WHOLE, int DPAD, int DPL, bool V16, int S>
-__device__ __forceinline__ void load_segment(const uint8_t *vol, const WaveLines &g, int q, bool back,
-                                             uint32_t (&w)[S][Lane<DPL, V16>::NW])
-{
+// ---------------------------------------------------------------- where costs come from
+// A source loads what S pixels' costs need (Raw) and adds a register's costs to a step.
+// WHOLE: every pixel of the segment exists on every line of the wave, and its costs
+// need no care; otherwise pixels that do not exist cost nothing, which leaves a line's
+// state before its first pixel as it is.
+
+// A cost volume in the path buffers' layout.
+template <int DPAD, int DPL, bool V16>
+struct VolumeSource {
     using LV = Lane<DPL, V16>;
-    const Segment b = segment<S, DPAD * (V16 ? 2 : 1)>(vol, g, q, back);
-    static_for<S>([&](auto s) {
-        LV::load(b.rs, WHOLE || (uint32_t)index_of<S>(q, s, back) < (uint32_t)g.len ? g.off : kOff, at_step<S>(b, s), w[s]);
+    static constexpr int kSeg = 4, kRing = 4;
+    const uint8_t *vol;
+    template <int S>
+    struct Raw {
+        uint32_t w[S][LV::NW];  // in walking order
+    };
+    template <int S>
+    __device__ __forceinline__ bool whole(const WaveLines &g, int qa, int qb) const
+    {
+        return min(qa, qb) >= 0 && (max(qa, qb) + 1) * S <= g.minlen;
+    }
+    template <bool WHOLE, int S, class B>
+    __device__ __forceinline__ void load(const WaveLines &g, int q, B back, Raw<S> &raw) const
+    {
+        const Segment b = segment<S, DPAD * (V16 ? 2 : 1)>(vol, g, q, back);
+        static_for<S>([&](auto s) {
+            LV::load(b.rs, WHOLE || (uint32_t)index_of<S>(q, s, back) < (uint32_t)g.len ? g.off : kOff, at_step<S>(b, s), raw.w[s]);
+        });
+    }
+    template <bool WHOLE, int S, int J, class B>
+    __device__ __forceinline__ uint32_t add(const Raw<S> &raw, int s, int, B, uint32_t t) const
+    {
+        return pk_add(t, LV::template get<J>(raw.w[s]));
+    }
+};
+
+template <bool WIDE>
+struct CensusWord;
+template <>
+struct CensusWord<false> {
+    using T = uint32_t;
+    static __device__ __forceinline__ uint32_t hamming(T a, T b) { return __popc(a ^ b); }
+};
+template <>
+struct CensusWord<true> {
+    using T = uint64_t;
+    static __device__ __forceinline__ uint32_t hamming(T a, T b) { return __popcll(a ^ b); }
+};
+
+// N consecutive words of a census map from word `at` on, 16 bytes per load (as many
+// whole loads as hold them; the words after are other words of the scratch)
+template <bool WIDE, int N>
+__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, int at, typename CensusWord<WIDE>::T (&w)[N])
+{
+    constexpr int kPer = WIDE ? 2 : 4;
+    static_for<(N + kPer - 1) / kPer>([&](auto ic) {
+        constexpr int i = decltype(ic)::value * kPer;
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, (at + i) * (16 / kPer), 0, 0);
+        static_for<kPer>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (i + k < N) {
+                if constexpr (WIDE) w[i + k] = ((uint64_t)v[2 * k + 1] << 32) | v[2 * k];
+                else w[i + k] = v[k];
+            }
+        });
+    });
+}
+// the same one word at a time, each at its own clamped position (segments that
+// touch the image's ends)
+template <bool WIDE, int N>
+__device__ __forceinline__ void load_words_clamped(__amdgpu_buffer_rsrc_t rs, int at, int last,
+                                                   typename CensusWord<WIDE>::T (&w)[N])
+{
+    static_for<N>([&](auto i) {
+        const int p = min(max(at + i, 0), last);
+        if constexpr (WIDE) {
+            const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(rs, p * 8, 0, 0);
+            w[i] = ((uint64_t)v[1] << 32) | v[0];
+        } else {
+            w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, p * 4, 0, 0);
+        }
     });
 }
 
-// Costs are loaded in segments of 4 steps into a ring of 4 segments, 12 steps
-// ahead: vector loads and stores complete in issue order, so waiting for a load
-// also waits for the stores issued before it, and stores take longer.  The ring is
-// unrolled (16 steps a block, each slot in fixed registers); longer rings cost more
-// instruction cache than they gain (32 steps a block: 54 -> 72 us at 320x240).
-constexpr int kLoadSeg = 4, kLoadRing = 4;
+// Horizontal lines from the census words: the S pixels of a segment need S left words
+// and, per lane, the S + DPL - 1 right words of columns x - d0 - j, consecutive words
+// of a row.  The walk's direction is a constant (B: std::integral_constant): words sit
+// in registers in memory order.  (wave: as wave_lines)
+template <int DPAD, int DPL, int LPL, bool WIDE>
+struct RowSource {
+    using CW = CensusWord<WIDE>;
+    using Word = typename CW::T;
+    // (8 pixels of a lane with many disparities share more words: 24 loaded for 8
+    // steps instead of 16 for 4; 1280x720, D = 128: 429 -> 423 us a call)
+    static constexpr int kSeg = DPL <= 4 ? 4 : 8, kRing = DPL <= 4 ? 4 : 2;
+    __amdgpu_buffer_rsrc_t rl, rr;  // from the wave's first row on
+    int row, last;                  // the lane's row (words), the maps' last word
+    int W, D, d0;
+    uint32_t bits;
+    template <int S>
+    struct Raw {
+        Word l[S], r[S + DPL - 1];
+    };
+    __device__ __forceinline__ RowSource(const void *cl, const void *cr, int wave, int W_, int H, int D_, uint32_t bits_)
+        : W(W_), D(D_), bits(bits_)
+    {
+        constexpr int kLines = 64 / LPL;
+        const int y0 = wave * kLines, y = min(y0 + (int)(threadIdx.x & 63) / LPL, H - 1);
+        rl = open_buffer((const Word *)cl + (int64_t)y0 * W);
+        rr = open_buffer((const Word *)cr + (int64_t)y0 * W);
+        row = (y - y0) * W;
+        last = (H - y0) * W - 1;
+        d0 = (int)threadIdx.x % LPL * DPL;
+    }
+    template <int S>
+    __device__ __forceinline__ bool whole(const WaveLines &, int qa, int qb) const
+    {
+        return D == DPAD && min(qa, qb) * S >= DPAD - 1 && (max(qa, qb) + 1) * S <= W;
+    }
+    template <bool WHOLE, int S, class B>
+    __device__ __forceinline__ void load(const WaveLines &, int q, B, Raw<S> &raw) const
+    {
+        const int left = row + q * S, right = left - d0 - (DPL - 1);
+        if constexpr (WHOLE) {
+            load_words<WIDE>(rl, left, raw.l);
+            load_words<WIDE>(rr, right, raw.r);
+        } else {
+            load_words_clamped<WIDE>(rl, left, last, raw.l);
+            load_words_clamped<WIDE>(rr, right, last, raw.r);
+        }
+    }
+    template <bool WHOLE, int S, int J, class B>
+    __device__ __forceinline__ uint32_t add(const Raw<S> &raw, int s, int q, B, uint32_t t) const
+    {
+        const int i = B::value ? S - 1 - s : s;  // the pixel within the segment
+        auto cost = [&](int j) -> uint32_t {
+            const uint32_t c = CW::hamming(raw.l[i], raw.r[i + DPL - 1 - j]);
+            if constexpr (WHOLE) {
+                return c;
+            } else {
+                const int x = q * S + i;
+                return x >= W ? 0u : d0 + j >= D ? 255u : d0 + j <= x ? c : bits;
+            }
+        };
+        // (each half takes its own count: no carry between them)
+        t += cost(J);
+        if constexpr (DPL > 1) t += cost(J + DPL / 2) << 16;
+        return t;
+    }
+};
+
+// A wave keeps a ring of kRing segments of kSeg steps' costs, loaded kRing - 1 ahead:
+// vector loads and stores complete in issue order, so waiting for a load also waits for
+// the stores issued before it, and stores take longer.  The ring is unrolled (16 steps a
+// block, each slot in fixed registers); longer rings cost more instruction cache than
+// they gain (32 steps a block: 54 -> 72 us at 320x240, 24 steps: no change).
 
 // ---------------------------------------------------------------- one direction from the cost volume
 template <int DPAD, int DPL, int LPL, bool V16>
-__device__ __forceinline__ void run_single(const uint8_t *vol, uint8_t *out, const WaveLines &g, uint32_t p1, uint32_t p2,
+__device__ __forceinline__ void run_single(const VolumeSource<DPAD, DPL, V16> &src, uint8_t *out, const WaveLines &g, uint32_t p1, uint32_t p2,
                                            int cost, int max_work)
 {
     using LV = Lane<DPL, V16>;
     using L = Line<DPL, LPL, DPAD / DPL, V16>;
-    constexpr int S = kLoadSeg, R = kLoadRing, kDpadB = DPAD * (V16 ? 2 : 1), N = LV::N;
+    using SRC = VolumeSource<DPAD, DPL, V16>;
+    constexpr int S = SRC::kSeg, R = SRC::kRing, kDpadB = DPAD * (V16 ? 2 : 1), N = LV::N;
     const int lane = (int)threadIdx.x % LPL;
     L line;
     line.clear();
     const int nseg = (g.maxlen + S - 1) / S;
-    uint32_t ring[R][S][LV::NW];
+    typename SRC::template Raw<S> ring[R];
     auto block = [&](auto wc, int k) {
         constexpr bool WHOLE = decltype(wc)::value;
         static_for<R>([&](auto r) {
             if (!WHOLE && k + r >= nseg) return;
-            load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, k + r + R - 1, false, ring[(r + R - 1) % R]);
+            src.template load<WHOLE>(g, k + r + R - 1, false, ring[(r + R - 1) % R]);
             const Segment o = segment<S, kDpadB>(out, g, k + r, false);
             static_for<S>([&](auto s) {
                 const uint32_t ub = both(L::base(line.u));
-                line.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(ring[r][s])); });
+                line.step(p1, p2, lane, [&](auto j, uint32_t t) {
+                    return src.template add<WHOLE, S, decltype(j)::value>(ring[r], s, 0, false, t);
+                });
                 uint32_t v[N], m[LV::NW];
 #pragma unroll
                 for (int j = 0; j < N; ++j) v[j] = V16 ? line.U[j] : pk_sub(line.U[j], ub);
@@ -512,7 +650,7 @@ __device__ __forceinline__ void run_single(const uint8_t *vol, uint8_t *out, con
         });
         line.rebase();
     };
-    static_for<R - 1>([&](auto r) { load_segment<false, DPAD, DPL, V16, S>(vol, g, r, false, ring[r]); });
+    static_for<R - 1>([&](auto r) { src.template load<false>(g, r, false, ring[r]); });
     for (int k = 0; k < nseg; k += R) {
         set_priority((g.maxlen - k * S) * cost, max_work);
         if ((k + 2 * R - 1) * S <= g.minlen) block(std::true_type{}, k);
@@ -529,9 +667,9 @@ __device__ __forceinline__ void run_single(const uint8_t *vol, uint8_t *out, con
 // registers, walks the segment itself and stores the sums.  Three steps of work per
 // pixel in all, one and a half per wave in a row.
 // (live: the wave has lines; all waves of a block meet at the barrier)
-template <int DPAD, int DPL, int LPL, bool V16, int SUMS>
-__device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const WaveLines &g, bool live, bool back,
-                                         uint32_t p1, uint32_t p2, int cost, int max_work)
+template <int DPAD, int DPL, int LPL, bool V16, int SUMS, class SRC, class B>
+__device__ __forceinline__ void run_pair(const SRC &src, uint8_t *out, const WaveLines &g, bool live, B back, uint32_t p1,
+                                         uint32_t p2, int cost, int max_work)
 {
     using LV = Lane<DPL, V16>;
     using L = Line<DPL, LPL, DPAD / DPL, V16>;
@@ -542,18 +680,21 @@ __device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const
     L mine;
     mine.clear();
     if (live) {
-        constexpr int S = kLoadSeg, R = kLoadRing, kPer = SUMS / S;
+        constexpr int S = SRC::kSeg, R = SRC::kRing, kPer = SUMS / S;
         static_assert(SUMS % S == 0 && (R * S) % SUMS == 0, "states fall on load segments");
-        uint32_t ring[R][S][NW];
+        typename SRC::template Raw<S> ring[R];
         const int nall = nseg * kPer, nload = half * kPer;
         auto seg = [&](int k) { return back ? nall - 1 - k : k; };  // load segment k of the walk
         auto block = [&](auto wc, int k) {
             constexpr bool WHOLE = decltype(wc)::value;
             static_for<R>([&](auto r) {
                 if (!WHOLE && k + r >= nload) return;
-                load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, seg(k + r + R - 1), back, ring[(r + R - 1) % R]);
+                src.template load<WHOLE>(g, seg(k + r + R - 1), back, ring[(r + R - 1) % R]);
+                const int here = seg(k + r);
                 static_for<S>([&](auto s) {
-                    mine.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(ring[r][s])); });
+                    mine.step(p1, p2, lane, [&](auto j, uint32_t t) {
+                        return src.template add<WHOLE, S, decltype(j)::value>(ring[r], s, here, back, t);
+                    });
                 });
                 if constexpr ((r + 1) * S % SUMS == 0) {
                     // the state before the walk's next segment.  (Values of padding
@@ -577,11 +718,11 @@ __device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const
                 }
             });
         };
-        static_for<R - 1>([&](auto r) { load_segment<false, DPAD, DPL, V16, S>(vol, g, seg(r), back, ring[r]); });
+        static_for<R - 1>([&](auto r) { src.template load<false>(g, seg(r), back, ring[r]); });
         for (int k = 0; k < nload; k += R) {
             set_priority((3 * nseg * SUMS / 2 - k * S) * cost, max_work);
             const int ahead = k + 2 * R - 2;  // the block's last load
-            if (k + R <= nload && ahead < nall && (max(seg(k), seg(ahead)) + 1) * S <= g.minlen) block(std::true_type{}, k);
+            if (k + R <= nload && ahead < nall && src.template whole<S>(g, seg(k), seg(ahead))) block(std::true_type{}, k);
             else block(std::false_type{}, k);
         }
     }
@@ -592,18 +733,21 @@ __device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const
 
     constexpr int S = SUMS;
     auto seg = [&](int k) { return back ? nseg - 1 - k : k; };  // segment k of the walk
-    uint32_t ring[2][S][NW], states[2][NW];
-    auto load = [&](auto wc, int k, uint32_t (&w)[S][NW], uint32_t (&m)[NW]) {
+    using Raw = typename SRC::template Raw<S>;
+    Raw ring[2];
+    uint32_t states[2][NW];
+    auto load = [&](auto wc, int k, Raw &w, uint32_t (&m)[NW]) {
         constexpr bool WHOLE = decltype(wc)::value;
         if (!WHOLE && k >= nseg) return;
         const int q = seg(k);
-        load_segment<WHOLE, DPAD, DPL, V16, S>(vol, g, q, back, w);
+        src.template load<WHOLE>(g, q, back, w);
         // (the other wave starts from zeros in its first segment, this walk's last)
         const Segment o = segment<S, kDpadB>(out, g, q, false);
         LV::load(o.rs, WHOLE || (k < nseg - 1 && q * S < g.len) ? g.off : kOff, at_step<S>(o, 0), m);
     };
-    auto sums = [&](auto wc, int k, const uint32_t (&w)[S][NW], const uint32_t (&state)[NW]) {
+    auto sums = [&](auto wc, int k, const Raw &w, const uint32_t (&state)[NW]) {
         constexpr bool WHOLE = decltype(wc)::value;
+        const int q = seg(k);
         L other;
         uint32_t F[S][N], fu[S];
         static_for<N>([&](auto j) { other.U[j] = LV::template get<j>(state); });
@@ -611,15 +755,18 @@ __device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const
         static_for<S>([&](auto sc) {
             constexpr int s = S - 1 - decltype(sc)::value;
             fu[s] = L::base(other.u);
-            other.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(w[s])); });
+            other.step(p1, p2, lane, [&](auto j, uint32_t t) {
+                return src.template add<WHOLE, S, decltype(j)::value>(w, s, q, back, t);
+            });
 #pragma unroll
             for (int j = 0; j < N; ++j) F[s][j] = other.U[j];
         });
-        const int q = seg(k);
         const Segment o = segment<S, kDpadB>(out, g, q, back);
         static_for<S>([&](auto s) {
             const uint32_t sub = both(L::base(mine.u) + fu[s]);
-            mine.step(p1, p2, lane, [&](auto j, uint32_t t) { return pk_add(t, LV::template get<j>(w[s])); });
+            mine.step(p1, p2, lane, [&](auto j, uint32_t t) {
+                return src.template add<WHOLE, S, decltype(j)::value>(w, s, q, back, t);
+            });
             uint32_t v[N], m[NW];
 #pragma unroll
             for (int j = 0; j < N; ++j) v[j] = V16 ? pk_add(mine.U[j], F[s][j]) : pk_sub(pk_add(mine.U[j], F[s][j]), sub);
@@ -639,63 +786,12 @@ __device__ __forceinline__ void run_pair(const uint8_t *vol, uint8_t *out, const
     load(std::false_type{}, half, ring[0], states[0]);
     for (int k = half; k < nseg; k += 2) {
         set_priority(2 * (nseg - k) * S * cost, max_work);
-        if (k + 2 < nseg - 1 && (max(seg(k), seg(k + 2)) + 1) * S <= g.minlen) block(std::true_type{}, k);
+        if (k + 2 < nseg - 1 && src.template whole<S>(g, seg(k), seg(k + 2))) block(std::true_type{}, k);
         else block(std::false_type{}, k);
     }
 }
 
-// ---------------------------------------------------------------- horizontal lines from census words
-template <bool WIDE>
-struct CensusWord;
-template <>
-struct CensusWord<false> {
-    using T = uint32_t;
-    static __device__ __forceinline__ uint32_t hamming(T a, T b) { return __popc(a ^ b); }
-};
-template <>
-struct CensusWord<true> {
-    using T = uint64_t;
-    static __device__ __forceinline__ uint32_t hamming(T a, T b) { return __popcll(a ^ b); }
-};
-
-// S consecutive words from word `at` of a census map, 16 bytes per load.  Words outside the map's rows are other words of the scratch
-// (they only reach disparities with x - d < 0 or pixels past the line's end); the
-// caller keeps `at` >= 0.
-template <bool WIDE, int S>
-__device__ __forceinline__ void load_words(__amdgpu_buffer_rsrc_t rs, int at, typename CensusWord<WIDE>::T (&w)[S])
-{
-    if constexpr (WIDE) {
-        static_for<S / 2>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, at * 8 + 16 * i, 0, 0);
-            w[2 * i] = ((uint64_t)v[1] << 32) | v[0];
-            w[2 * i + 1] = ((uint64_t)v[3] << 32) | v[2];
-        });
-    } else {
-        static_for<S / 4>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, at * 4 + 16 * i, 0, 0);
-            w[4 * i] = v[0]; w[4 * i + 1] = v[1]; w[4 * i + 2] = v[2]; w[4 * i + 3] = v[3];
-        });
-    }
-}
-// the same one word at a time, each at its own clamped position (segments that
-// touch the image's ends)
-template <bool WIDE, int S>
-__device__ __forceinline__ void load_words_clamped(__amdgpu_buffer_rsrc_t rs, int at, int last,
-                                                   typename CensusWord<WIDE>::T (&w)[S])
-{
-    static_for<S>([&](auto i) {
-        const int p = min(max(at + i, 0), last);
-        if constexpr (WIDE) {
-            const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(rs, p * 8, 0, 0);
-            w[i] = ((uint64_t)v[1] << 32) | v[0];
-        } else {
-            w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, p * 4, 0, 0);
-        }
-    });
-}
-
+// ---------------------------------------------------------------- one horizontal direction from census words
 // Horizontal lines (rows), HDIR +1 left to right, -1 right to left.  At column x a
 // lane needs the right words of columns x - d0 - j, j < DPL: one new word per step,
 // at columns that advance with x, so a segment's S new words are S consecutive
@@ -708,7 +804,7 @@ __device__ __forceinline__ void run_horizontal(const void *cl, const void *cr, u
     using L = Line<DPL, LPL, DPAD / DPL, false>;
     using CW = CensusWord<WIDE>;
     using Word = typename CW::T;
-    constexpr int S = kLoadSeg, R = kLoadRing, N = LV::N, kDpad = DPAD, kLines = 64 / LPL;
+    constexpr int S = 4, R = 4, N = LV::N, kDpad = DPAD, kLines = 64 / LPL;
     const int lane = (int)threadIdx.x % LPL, d0 = lane * DPL;
     const WaveLines g = wave_lines<LPL, kDpad>(HDIR, 0, wave, W, H, lane * DPL);
     const int y0 = wave * kLines, y = min(y0 + (int)(threadIdx.x & 63) / LPL, H - 1);
@@ -726,11 +822,11 @@ __device__ __forceinline__ void run_horizontal(const void *cl, const void *cr, u
     auto inside = [&](int k) { return HDIR > 0 ? k * S >= kDpad - 1 && (k + 1) * S <= W : W - (k + 1) * S >= kDpad - 1; };
     auto load = [&](auto wc, int k, Word (&wl)[S], Word (&wr)[S]) {
         if constexpr (decltype(wc)::value) {
-            load_words<WIDE, S>(rl, row + lcol(k), wl);
-            load_words<WIDE, S>(rr, row + rcol(k), wr);
+            load_words<WIDE>(rl, row + lcol(k), wl);
+            load_words<WIDE>(rr, row + rcol(k), wr);
         } else {
-            load_words_clamped<WIDE, S>(rl, row + lcol(k), last, wl);
-            load_words_clamped<WIDE, S>(rr, row + rcol(k), last, wr);
+            load_words_clamped<WIDE>(rl, row + lcol(k), last, wl);
+            load_words_clamped<WIDE>(rr, row + rcol(k), last, wr);
         }
     };
     L line;
@@ -745,7 +841,7 @@ __device__ __forceinline__ void run_horizontal(const void *cl, const void *cr, u
 #pragma unroll
         for (int i = 0; i < DPL - 1; ++i) {
             Word v[1];
-            load_words_clamped<WIDE, 1>(rr, row + W - 1 - d0 - i, last, v);
+            load_words_clamped<WIDE>(rr, row + W - 1 - d0 - i, last, v);
             carry[i] = v[0];
         }
     }
@@ -908,30 +1004,42 @@ __device__ __forceinline__ void aggregate_item(const AggregateArgs &a, int item)
     const int W = uniform(a.W), H = uniform(a.H), max_work = uniform(a.max_item_work);
     const int nlines = line_count(dx, dy, W, H);
     const uint32_t p1 = both(uniform(a.p1)), p2 = both(uniform(a.p2));
+    const bool pair = uniform(a.pair[unit]) != 0;
+    const int wave = pair ? item * (kWavesPerItem / 2) + w / 2 : item * kWavesPerItem + w;
     if (dy == 0) {
         constexpr int cost = agg_step_cost(HD, HL);
-        const int wave = item * kWavesPerItem + w;
-        if (wave * (64 / HL) >= nlines) return;
+        const bool live = wave * (64 / HL) < nlines;
+        const void *cl = uniform(a.census_l), *cr = uniform(a.census_r);
         const int D = uniform(a.D);
         const uint32_t bits = uniform(a.bits);
-        if (dx > 0)
-            run_horizontal<kDpad, HD, HL, WIDE, 1>(uniform(a.census_l), uniform(a.census_r), out, wave, W, H, D, bits, p1,
-                                                   p2, cost, max_work);
-        else
-            run_horizontal<kDpad, HD, HL, WIDE, -1>(uniform(a.census_l), uniform(a.census_r), out, wave, W, H, D, bits, p1,
-                                                    p2, cost, max_work);
+        if constexpr (row_pairs_built(HL, WIDE))
+            if (pair) {
+                const WaveLines g = wave_lines<HL, kDpad>(1, 0, wave, W, H, (int)threadIdx.x % HL * HD);
+                const RowSource<kDpad, HD, HL, WIDE> src(cl, cr, wave, W, H, D, bits);
+                constexpr int kSums = sum_steps(HD, false);
+                if (w & 1) run_pair<kDpad, HD, HL, false, kSums>(src, out, g, live, std::true_type{}, p1, p2, cost, max_work);
+                else run_pair<kDpad, HD, HL, false, kSums>(src, out, g, live, std::false_type{}, p1, p2, cost, max_work);
+                return;
+            }
+        if (!live) return;
+        if constexpr (WIDE)
+            if (uniform(a.row_costs)) {
+                const WaveLines g = wave_lines<HL, kDpad>(dx, 0, wave, W, H, (int)threadIdx.x % HL * HD);
+                return run_single<kDpad, HD, HL, false>(VolumeSource<kDpad, HD, false>{uniform(a.cost)}, out, g, p1, p2, cost,
+                                                        max_work);
+            }
+        if (dx > 0) run_horizontal<kDpad, HD, HL, WIDE, 1>(cl, cr, out, wave, W, H, D, bits, p1, p2, cost, max_work);
+        else run_horizontal<kDpad, HD, HL, WIDE, -1>(cl, cr, out, wave, W, H, D, bits, p1, p2, cost, max_work);
     } else {
         constexpr int cost = agg_step_cost(LD, kLanesPerLine), kLines = 64 / kLanesPerLine;
-        const bool pair = uniform(a.pair[unit]) != 0;
-        const int wave = pair ? item * (kWavesPerItem / 2) + w / 2 : item * kWavesPerItem + w;
         const bool live = wave * kLines < nlines;
         const int lane = (int)threadIdx.x % kLanesPerLine;
         const WaveLines g = wave_lines<kLanesPerLine, kDpad>(dx, dy, wave, W, H, lane * LD);
-        const uint8_t *vol = uniform(a.cost);
+        const VolumeSource<kDpad, LD, false> src{uniform(a.cost)};
         if (pair)
-            run_pair<kDpad, LD, kLanesPerLine, false, sum_steps(LD, false)>(vol, out, g, live, w & 1, p1, p2, cost, max_work);
+            run_pair<kDpad, LD, kLanesPerLine, false, sum_steps(LD, false)>(src, out, g, live, (w & 1) != 0, p1, p2, cost, max_work);
         else if (live)
-            run_single<kDpad, LD, kLanesPerLine, false>(vol, out, g, p1, p2, cost, max_work);
+            run_single<kDpad, LD, kLanesPerLine, false>(src, out, g, p1, p2, cost, max_work);
     }
 }
 

@@ -64,21 +64,27 @@ int validate(const simsense_params *p)
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-Layout layout(const simsense_params *p)
+bool stores_sums(const simsense_params *p)
+{
+    return p->block_w * p->block_h > 1 || census_bits(p->census_w, p->census_h, p->census_mode) + p->p2 <= 127;
+}
+
+Layout layout(const simsense_params *p, bool spare)
 {
     Layout l{};
     const size_t npx = (size_t)p->width * p->height;
     const bool wide = census_bits(p->census_w, p->census_h, p->census_mode) > 32;
     l.census = align256(npx * (wide ? 8 : 4));
     const bool block = p->block_w * p->block_h > 1;
-    // one buffer per direction (the aggregation fills fewer where it stores sums, and
+    // (the aggregation fills fewer buffers than directions where it stores sums, and
     // keeps its cost volume in the last); 16-bit path values for block matching
     l.paths = align256((npx + 1) * padded_disp(p->max_disp) * (block ? 2 : 1));
     l.volume = block ? align256(npx * padded_disp(p->max_disp) * 2) : 0;
     static const int px_bytes[7] = {1, 2, 2, 1, 4, 4, 1};  // dint, S1, S2, dright, dsub, masked, flags
     l.right_run = p->lr_mode == 1;
     const int sets = l.right_run ? 2 : 1;
-    l.total = 2 * sets * l.census + (size_t)p->num_paths * l.paths + l.volume;
+    l.buffers = path_buffers(p->num_paths, stores_sums(p), spare);
+    l.total = 2 * sets * l.census + (size_t)l.buffers * l.paths + l.volume;
     for (int i = 0; i < 7; ++i) {
         l.per_px[i] = align256(npx * px_bytes[i]);
         l.total += sets * l.per_px[i];
@@ -95,10 +101,9 @@ void init_handle(simsense_handle *h, const simsense_params *params)
     h->Dpad = padded_disp(params->max_disp);
     h->ndirs = params->num_paths;
     h->sgbm = params->block_w * params->block_h > 1;
-    h->pairs = h->sgbm || h->bits + params->p2 <= 127;
-    h->nplanes = aggregate_planes(h->ndirs, h->pairs);
+    h->sums = stores_sums(params);
     h->hlanes = default_lanes(params->width, h->Dpad,
-                              aggregate_work(params->width, params->height, h->Dpad, h->ndirs, h->pairs));
+                              aggregate_work(params->width, params->height, h->Dpad, h->ndirs, h->sums));
 }
 
 // Points the handle's buffers into one block of scratch laid out by layout().
@@ -107,7 +112,8 @@ void carve_scratch(simsense_handle *h, uint8_t *base, const Layout &l)
     uint8_t *cur = base;
     h->census_l = cur; cur += l.census;
     h->census_r = cur; cur += l.census;
-    for (int r = 0; r < h->ndirs; ++r) { h->paths[r] = cur; cur += l.paths; }
+    h->nbuffers = l.buffers;
+    for (int r = 0; r < l.buffers; ++r) { h->paths[r] = cur; cur += l.paths; }
     h->disp_int = cur; cur += l.per_px[0];
     h->cost_best = (uint16_t *)cur; cur += l.per_px[1];
     h->cost_second = (uint16_t *)cur; cur += l.per_px[2];
@@ -205,7 +211,9 @@ void plan_handle(simsense_handle *h)
     ag.cost = (uint8_t *)h->volume;
     ag.W = p.width; ag.H = p.height; ag.D = p.max_disp; ag.Dpad = h->Dpad; ag.bits = h->bits;
     ag.p1 = p.p1; ag.p2 = p.p2;
-    plan_aggregation(ag, h->ndirs, h->pairs, h->sgbm, h->sgbm ? volume_horizontal_lanes(h->Dpad) : h->hlanes, h->paths);
+    h->row_sums = h->sums && !h->sgbm && default_row_sums(p.width, p.height, h->Dpad, h->ndirs, h->wide, h->hlanes);
+    plan_aggregation(ag, h->ndirs, h->sums, h->row_sums, h->sgbm,
+                     h->sgbm ? volume_horizontal_lanes(h->Dpad) : h->hlanes, h->paths, h->nbuffers);
 }
 
 // The right-referenced run is the left-referenced pass on x-flipped census maps
@@ -254,7 +262,7 @@ static int apply_tuning(simsense_handle *h, const simsense_batch_tuning &t)
     const simsense_params &p = h->p;
     const int hl = h->hlanes = t.horizontal_lanes != 0
                                    ? t.horizontal_lanes
-                                   : default_lanes(p.width, h->Dpad, aggregate_work(p.width, p.height, h->Dpad, h->ndirs, h->pairs));
+                                   : default_lanes(p.width, h->Dpad, aggregate_work(p.width, p.height, h->Dpad, h->ndirs, h->sums));
     h->tuning = t;
     plan_handle(h);
     const AggregateArgs &ag = h->ag;
@@ -302,17 +310,17 @@ int enqueue_match(simsense_handle *h, const uint8_t *left, const uint8_t *right,
         // the summed volume of this (left-referenced) run, before a right-referenced
         // run reuses the path buffers
         PathSet ps{};
-        for (int r = 0; r < h->nplanes; ++r) ps.p[r] = h->paths[r];
-        SS_TRY(launch_volume_sum(ps, h->nplanes, h->sgbm, W, H, D, h->Dpad, volume_out, s));
+        for (int r = 0; r < h->ag.nunits; ++r) ps.p[r] = h->paths[r];
+        SS_TRY(launch_volume_sum(ps, h->ag.nunits, h->sgbm, W, H, D, h->Dpad, volume_out, s));
     }
 
     SelectArgs sa{};
-    for (int r = 0; r < h->nplanes; ++r) sa.paths[r] = h->paths[r];
-    sa.nplanes = h->nplanes;
+    for (int r = 0; r < h->ag.nunits; ++r) sa.paths[r] = h->paths[r];
+    sa.nplanes = h->ag.nunits;
     sa.W = W; sa.H = H; sa.D = D; sa.Dpad = h->Dpad;
     sa.uniqueness_pct = p.uniqueness_pct; sa.lr_max_diff = p.lr_max_diff; sa.subpixel = p.subpixel;
     sa.values16 = h->sgbm;
-    sa.small_values = !h->sgbm && h->pairs;
+    sa.small_values = !h->sgbm && h->sums && !h->row_sums;
     sa.disp_int = h->disp_int; sa.cost_best = h->cost_best; sa.cost_second = h->cost_second;
     sa.disp_right = h->disp_right; sa.disp_sub = h->disp_sub; sa.masked = h->masked; sa.flags = h->flags_pre;
     sa.no_right = !need_right;
@@ -381,7 +389,7 @@ int64_t simsense_scratch_bytes(const simsense_params *params)
 {
     int rc = validate(params);
     if (rc != SIMSENSE_OK) return rc;
-    return (int64_t)layout(params).total;
+    return (int64_t)layout(params, true).total;
 }
 
 int simsense_create(const simsense_params *params, simsense_handle **out)
@@ -389,11 +397,16 @@ int simsense_create(const simsense_params *params, simsense_handle **out)
     if (!out) return SIMSENSE_ERR_NULL_POINTER;
     int rc = validate(params);
     if (rc != SIMSENSE_OK) return rc;
-    Layout l = layout(params);
+    Layout l = layout(params, true);
     simsense_handle *h = new (std::nothrow) simsense_handle();
     if (!h) return SIMSENSE_ERR_OUT_OF_MEMORY;
     init_handle(h, params);
-    if (hipMalloc(&h->block, l.total) != hipSuccess || hipMalloc(&h->d_args, 2 * sizeof(AggregateArgs)) != hipSuccess) {
+    if (hipMalloc(&h->block, l.total) != hipSuccess) {
+        (void)hipGetLastError();
+        h->block = nullptr;
+        l = layout(params, false);  // where memory is short, without the spare buffer
+    }
+    if ((!h->block && hipMalloc(&h->block, l.total) != hipSuccess) || hipMalloc(&h->d_args, 2 * sizeof(AggregateArgs)) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(h->block);
         delete h;

@@ -28,9 +28,9 @@ namespace {
 
 struct Slot {
     simsense_params p;
-    int bits, Dpad, ndirs, hl;
-    bool wide, small;
-    size_t off_census_l, off_census_r, off_paths[8], off_dint, off_s1, off_s2, off_dright, off_dsub, off_masked,
+    int bits, Dpad, ndirs, hl, nbuffers;
+    bool wide, small, row_sums;
+    size_t off_census_l, off_census_r, off_paths[9], off_dint, off_s1, off_s2, off_dright, off_dsub, off_masked,
         off_flags;
 };
 
@@ -129,9 +129,11 @@ int build_plan(simsense_batch *b)
         work += aggregate_work(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.small);
         widest[sl.Dpad] = std::max(widest[sl.Dpad], sl.p.width);
     }
-    for (Slot &sl : b->slots)
+    for (Slot &sl : b->slots) {
         sl.hl = horizontal_lanes_valid(sl.Dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
                                                                             : default_lanes(widest[sl.Dpad], sl.Dpad, work);
+        sl.row_sums = sl.small && default_row_sums(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.wide, sl.hl);
+    }
     std::vector<AggregateArgs> agg(n);
     std::vector<SelectArgs> sel(n);
     b->lphases.clear();
@@ -164,9 +166,9 @@ int build_plan(simsense_batch *b)
             a.census_r = b->scratch + sl.off_census_r;
             a.W = sl.p.width; a.H = sl.p.height; a.D = sl.p.max_disp; a.Dpad = sl.Dpad; a.bits = sl.bits;
             a.p1 = sl.p.p1; a.p2 = sl.p.p2;
-            uint8_t *buffers[8];
-            for (int r = 0; r < sl.ndirs; ++r) buffers[r] = b->scratch + sl.off_paths[r];
-            plan_aggregation(a, sl.ndirs, sl.small, false, sl.hl, buffers);
+            uint8_t *buffers[9];
+            for (int r = 0; r < sl.nbuffers; ++r) buffers[r] = b->scratch + sl.off_paths[r];
+            plan_aggregation(a, sl.ndirs, sl.small, sl.row_sums, false, sl.hl, buffers, sl.nbuffers);
             if (scale > 0) a.max_item_work = scale;
             auto &lst = groups[{sl.Dpad, sl.wide}];
             lst.hl = sl.hl;
@@ -214,11 +216,11 @@ int build_plan(simsense_batch *b)
             const Slot &sl = b->slots[s];
             SelectArgs &a = sel[s];
             a = SelectArgs{};
-            a.nplanes = aggregate_planes(sl.ndirs, sl.small);
+            a.nplanes = agg[s].nunits;
             for (int r = 0; r < a.nplanes; ++r) a.paths[r] = b->scratch + sl.off_paths[r];
             a.W = sl.p.width; a.H = sl.p.height; a.D = sl.p.max_disp; a.Dpad = sl.Dpad;
             a.uniqueness_pct = sl.p.uniqueness_pct; a.lr_max_diff = sl.p.lr_max_diff; a.subpixel = sl.p.subpixel;
-            a.small_values = sl.small;
+            a.small_values = sl.small && !sl.row_sums;
             a.disp_int = b->scratch + sl.off_dint;
             a.cost_best = (uint16_t *)(b->scratch + sl.off_s1);
             a.cost_second = (uint16_t *)(b->scratch + sl.off_s2);
@@ -226,7 +228,7 @@ int build_plan(simsense_batch *b)
             a.disp_sub = (float *)(b->scratch + sl.off_dsub);
             a.masked = (float *)(b->scratch + sl.off_masked);
             a.flags = b->scratch + sl.off_flags;
-            auto &lst = sgroups[{sl.Dpad, a.nplanes, sl.small}];
+            auto &lst = sgroups[{sl.Dpad, a.nplanes, a.small_values != 0}];
             for (int y = 0; y < sl.p.height; ++y) lst.push_back(((uint32_t)s << 20) | (uint32_t)y);
         }
         P.sel0 = (int)b->sel_groups.size();
@@ -539,20 +541,23 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
     b->tuning.struct_size = sizeof(simsense_batch_tuning);
     b->tuning.horizontal_lanes = 0;
     b->tuning.blocks_per_cu = 2;
-    size_t total = 0;
-    for (int s = 0; s < n; ++s) {
+    // (spare: with the cost-volume buffers of slots whose directions fill all others)
+    auto lay_out = [&](bool spare) {
+      size_t total = 0;
+      for (int s = 0; s < n; ++s) {
         Slot &sl = b->slots[s];
         sl.p = params[s];
         sl.bits = census_bits(sl.p.census_w, sl.p.census_h, sl.p.census_mode);
         sl.wide = sl.bits > 32;
-        sl.small = sl.bits + sl.p.p2 <= 127;
+        sl.small = stores_sums(&sl.p);
         sl.Dpad = padded_disp(sl.p.max_disp);
         sl.ndirs = sl.p.num_paths;
         const size_t npx = (size_t)sl.p.width * sl.p.height;
         auto take = [&](size_t bytes) { size_t o = total; total += a256(bytes); return o; };
         sl.off_census_l = take(npx * (sl.wide ? 8 : 4));
         sl.off_census_r = take(npx * (sl.wide ? 8 : 4));
-        for (int r = 0; r < sl.ndirs; ++r) sl.off_paths[r] = take((npx + 1) * sl.Dpad);
+        sl.nbuffers = path_buffers(sl.ndirs, sl.small, spare);
+        for (int r = 0; r < sl.nbuffers; ++r) sl.off_paths[r] = take((npx + 1) * sl.Dpad);
         sl.off_dint = take(npx);
         sl.off_s1 = take(npx * 2);
         sl.off_s2 = take(npx * 2);
@@ -560,10 +565,17 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
         sl.off_dsub = take(npx * 4);
         sl.off_masked = take(npx * 4);
         sl.off_flags = take(npx);
-    }
-    b->scratch_bytes = total;
+      }
+      b->scratch_bytes = total;
+    };
     int rc = SIMSENSE_OK;
-    if (hipMalloc(&b->scratch, total) != hipSuccess || hipMalloc(&b->d_cjobs, 2 * n * sizeof(CensusJob)) != hipSuccess ||
+    lay_out(true);
+    if (hipMalloc(&b->scratch, b->scratch_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        b->scratch = nullptr;
+        lay_out(false);  // where memory is short, without the spare buffers
+    }
+    if ((!b->scratch && hipMalloc(&b->scratch, b->scratch_bytes) != hipSuccess) || hipMalloc(&b->d_cjobs, 2 * n * sizeof(CensusJob)) != hipSuccess ||
         hipMalloc(&b->d_agg, n * sizeof(AggregateArgs)) != hipSuccess ||
         hipMalloc(&b->d_sel, n * sizeof(SelectArgs)) != hipSuccess ||
         hipMalloc(&b->d_post, n * sizeof(PostArgs)) != hipSuccess)

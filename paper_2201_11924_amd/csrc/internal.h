@@ -30,7 +30,12 @@ int path_lines(int dx, int dy, int W, int H);
 //   1.3 (848x480, D = 128, 8) 169 / 143 / 187;  1.9 (1280x720, D = 128, 8) 271 / 308 / 334;
 //   16 pairs of 1280x720, 2 paths, with the net: 2805 / 3043 / 3685.
 int default_lanes(int W, int dpad, int64_t total_work);
-int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool pairs);
+int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums);
+// Whether the horizontal directions are stored as sums by default: where the cost volume
+// does not fit the 256 MB last-level cache, so that the aggregation waits for HBM, one
+// buffer less is worth a third walk over the rows (1920x1080, D = 256: whole call 1762 ->
+// 1682 us; 1280x720, D = 128: 423 -> 429; 16 pairs in a batch: no change).
+bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl);
 bool horizontal_lanes_valid(int dpad, int hl);
 // Disparities a lane of a line of `lanes` lanes holds: a whole number of words in
 // memory (lanes past the padded count idle), or 1 or 2.
@@ -58,6 +63,7 @@ struct AggregateArgs {
     const void *census_l, *census_r;  // uint32 words, or uint64 when bits > 32
     uint8_t *cost;       // cost volume the vertical and diagonal units read (null: none of them); for
                          // block matching the 16-bit block costs of every unit
+    int row_costs;       // the horizontal units read it too (else the census words)
     int W, H, D, Dpad, bits, p1, p2;
     int nunits;
     int last_first;      // units from here on run after all others (they write over `cost`)
@@ -66,22 +72,27 @@ struct AggregateArgs {
     uint8_t *out[8];     // per-unit path values, W*H*Dpad values, d fastest
     int max_item_work;   // largest item work of the launch (issue priorities)
 };
-// Buffers the units of num_paths directions fill (consecutive ones of the path
-// buffers, from the first).  pairs: opposite directions, but the horizontal ones, are
-// stored as their sums; two path values must fit one value of the buffer.
-constexpr int aggregate_planes(int num_paths, bool pairs) { return pairs && num_paths > 2 ? num_paths / 2 + 1 : num_paths; }
-// Fills a's units for `buffers` (num_paths of them) and hl lanes per horizontal line,
-// from W, H and Dpad.  block: a.cost is the caller's and every unit reads it.
-void plan_aggregation(AggregateArgs &a, int num_paths, bool pairs, bool block, int hl, uint8_t *const *buffers);
+// Whether horizontal directions may be stored as sums too: 16 lanes per line and
+// 32-bit census words (64-bit ones take more registers than a wave has).
+__host__ __device__ constexpr bool row_pairs_built(int lanes, bool wide) { return lanes == kLanesPerLine && !wide; }
+// Path buffers of a slot: one per direction, and one more for the cost volume where the
+// directions need them all (no sums) and the caller can spare it.
+constexpr int path_buffers(int num_paths, bool sums, bool spare) { return num_paths + (spare && !sums && num_paths > 2 ? 1 : 0); }
+// Fills a's units for the nbuffers `buffers` and hl lanes per horizontal line, from W, H
+// and Dpad.  sums: opposite directions are stored as their sums (two path
+// values must fit one value of the buffer); row_sums: the horizontal ones too.  Unit u
+// fills buffers[u].  block: a.cost is the caller's and every unit reads it.
+void plan_aggregation(AggregateArgs &a, int num_paths, bool sums, bool row_sums, bool block, int hl, uint8_t *const *buffers,
+                      int nbuffers);
 int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl);
 
 struct SelectArgs {
     const uint8_t *paths[8];  // path values or sums of two, 8-bit, or 16-bit when values16
     int values16;
-    int nplanes;              // buffers to sum (aggregate_planes)
+    int nplanes;              // buffers to sum (the aggregation's units)
     int W, H, D, Dpad;
     int uniqueness_pct, lr_max_diff, subpixel;
-    int small_values;     // every path value < 128 (bits + P2 <= 127)
+    int small_values;     // every path value < 128 (bits + P2 <= 127), the first two buffers single ones
     uint8_t *disp_int;    // W*H
     uint16_t *cost_best;  // W*H
     uint16_t *cost_second;
@@ -202,10 +213,14 @@ hipError_t launch_volume_sum(const PathSet &paths, int nplanes, bool values16, i
 int validate(const simsense_params *p);
 struct Layout {
     size_t census, paths, per_px[7], total;
+    int buffers;       // path buffers
     bool right_run;  // lr_mode 1: two more census maps and a second per-pixel set
     size_t volume;   // SGBM: the block-cost volume (16-bit, d fastest)
 };
-Layout layout(const simsense_params *p);
+// (spare: with a buffer for the cost volume where the directions fill all others)
+Layout layout(const simsense_params *p, bool spare);
+bool stores_sums(const simsense_params *p);  // two path values fit one of the path buffers'
+
 // fields derived from the parameters; the buffers carved from `base` (l.total bytes)
 void init_handle(simsense_handle *h, const simsense_params *params);
 void carve_scratch(simsense_handle *h, uint8_t *base, const Layout &l);
@@ -240,8 +255,8 @@ struct simsense_handle {  // opaque to callers
     uint32_t *d_items;
     ss::AggregateArgs ag;  // the aggregation's units, set with the tuning
     ss::AggregateArgs *d_args;
-    bool pairs;    // two path values fit one of the path buffers' (bits + P2 <= 127, or 16 bits)
-    int nplanes;   // buffers the aggregation fills
+    bool sums;     // two path values fit one of the path buffers' (bits + P2 <= 127, or 16 bits)
+    bool row_sums; // the horizontal directions are stored as their sum
     // full right-referenced run (lr_mode 1): x-flipped census maps (the right
     // image's as the reference), that run's per-pixel results and its arguments
     void *census_ml, *census_mr;
@@ -254,7 +269,8 @@ struct simsense_handle {  // opaque to callers
     uint16_t *volume;
     void *block;
     void *census_l, *census_r;
-    uint8_t *paths[8];
+    uint8_t *paths[9];
+    int nbuffers;
     uint8_t *disp_int, *disp_right, *flags_pre;
     uint16_t *cost_best, *cost_second;
     float *disp_sub, *masked;

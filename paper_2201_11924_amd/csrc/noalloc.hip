@@ -53,7 +53,7 @@ extern "C" int simsense_compute_noalloc(const simsense_params *params, const uin
     if (rc != SIMSENSE_OK) return rc;
     if (!left || !right || !depth) return SIMSENSE_ERR_NULL_POINTER;
     if (pitch < params->width) return SIMSENSE_ERR_INVALID_ARGUMENT;
-    const Layout l = layout(params);
+    const Layout l = layout(params, false);
     if (l.total > kScratchBytes) return SIMSENSE_ERR_TOO_LARGE;
     uint8_t *base = nullptr;
     rc = scratch_for_current_device(&base);

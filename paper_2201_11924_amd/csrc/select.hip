@@ -379,7 +379,7 @@ void launch_sel3(const SelectArgs *a, const SelectBatch *b, hipStream_t s)
 }
 
 // planes: one per direction (2, 4, 8), or the two horizontal ones and the sums of the
-// others' pairs (3, 5; byte sums only of small values)
+// others' pairs (3, 5; byte sums only of small values), or sums only (2, 4)
 template <int DPL, bool SMALL, bool V16>
 void launch_sel2(const SelectArgs *a, const SelectBatch *b, int nplanes, hipStream_t s)
 {
@@ -389,6 +389,7 @@ void launch_sel2(const SelectArgs *a, const SelectBatch *b, int nplanes, hipStre
     case 8: return launch_sel3<DPL, 8, SMALL, V16>(a, b, s);
     default: break;
     }
+
     if constexpr (SMALL || V16) {
         if (nplanes == 3) launch_sel3<DPL, 3, SMALL, V16>(a, b, s);
         else launch_sel3<DPL, 5, SMALL, V16>(a, b, s);

@@ -114,14 +114,15 @@ __global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per
         const int wave = item * kWavesPerItem + w;
         if (wave * (64 / HL) >= nlines) return;
         const WaveLines g = wave_lines<HL, 2 * kDpad>(dx, dy, wave, a.W, a.H, (int)threadIdx.x % HL * (2 * HD));
-        run_single<kDpad, HD, HL, true>(a.cost, a.out[unit], g, p1, p2, agg_step_cost(HD, HL), a.max_item_work);
+        run_single<kDpad, HD, HL, true>(VolumeSource<kDpad, HD, true>{a.cost}, a.out[unit], g, p1, p2, agg_step_cost(HD, HL),
+                                        a.max_item_work);
     } else {
         const int wave = item * (kWavesPerItem / 2) + w / 2;
         const WaveLines g = wave_lines<kLanesPerLine, 2 * kDpad>(dx, dy, wave, a.W, a.H,
                                                                  (int)threadIdx.x % kLanesPerLine * (2 * LD));
-        run_pair<kDpad, LD, kLanesPerLine, true, sum_steps(LD, true)>(a.cost, a.out[unit], g,
-                                                                      wave * (64 / kLanesPerLine) < nlines, w & 1, p1, p2,
-                                                                      agg_step_cost(LD, kLanesPerLine), a.max_item_work);
+        run_pair<kDpad, LD, kLanesPerLine, true, sum_steps(LD, true)>(
+            VolumeSource<kDpad, LD, true>{a.cost}, a.out[unit], g, wave * (64 / kLanesPerLine) < nlines, (w & 1) != 0, p1, p2,
+            agg_step_cost(LD, kLanesPerLine), a.max_item_work);
     }
 }
 

@@ -67,7 +67,9 @@ def test_block_costs(orc, nat, D, paths):
     check(orc, nat, 33, 18, D, num_paths=paths, block_w=3, block_h=1, p1=0, p2=8191 - 93)
 
 
-def test_wide_stores_under_load(orc, nat):
-    """16-byte path-value stores with the memory pipe busy (every pixel of a
-    sensor-size volume with 16 disparities per lane)."""
-    check(orc, nat, 1280, 720, 256, tunings=((16, 3),))
+@pytest.mark.parametrize("W,H,D", [(1411, 771, 256), (1410, 770, 250), (1280, 720, 256)])
+def test_large_volumes(orc, nat, W, H, D):
+    """Cost volumes over and under the size from which the horizontal directions are
+    stored as their sum, whole and with padding disparities; 16-byte path-value stores
+    with the memory pipe busy."""
+    check(orc, nat, W, H, D, tunings=((16, 3),))
