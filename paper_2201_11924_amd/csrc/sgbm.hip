@@ -3,8 +3,9 @@
 // costs summed over a block centred on the pixel (samples clamped to the image),
 // aggregated by the same SGM recurrence with 16-bit path values.
 //
-// Two kernels: block_cost_kernel writes the block-cost volume (16-bit, d
-// fastest, the path buffers' layout); aggregate_volume_kernel runs the path
+// Two passes: block_cost_rows_kernel (square blocks of 3 and 5) or block_cost_kernel
+// writes the block-cost volume (16-bit, d fastest, the path buffers' layout);
+// aggregate_volume_kernel runs the path
 // recurrence of every line from that volume, with the lines, steps and pairs of
 // the census-fed aggregation.
 #include "aggregate_impl.h"
@@ -93,6 +94,141 @@ __global__ __launch_bounds__(256) void block_cost_kernel(BlockCostArgs a)
     }
 }
 
+// Square blocks of 3 and 5, in images at least that wide: a lane takes DPL consecutive
+// disparities of one pixel and walks down the image rows, keeping the sums over the
+// block's columns of the last B rows in registers, so a row of a block is counted once
+// instead of B times, and the words of the next row are in flight while this one is
+// counted.  Words come straight from the census maps (a few MB, in cache): the
+// DPL + B - 1 right words under a lane's block row are consecutive.  The tile form
+// above reads every sample from LDS and is bound by that; this one is near the rate
+// at which its volume can be written: 960x540, D = 128, 3x3 blocks 117 -> 36.6 us
+// (133 MB, 3.6 TB/s).  Whole calls, 3x3 / 5x5: 1280x720 D = 128 1.31x / 1.64x,
+// 640x480 D = 64 1.28x / 1.60x.
+template <int DPL, bool WIDE, int B>
+__global__ __launch_bounds__(256) void block_cost_rows_kernel(BlockCostArgs a, int seg)
+{
+    using CW = CensusWord<WIDE>;
+    using Word = typename CW::T;
+    constexpr int kDpad = kLanesPerLine * DPL, hw = B / 2, kRight = DPL - 1 + B;
+    const int lane = threadIdx.x & 15, d0 = lane * DPL, W = a.W, H = a.H;
+    // the last column of blocks first, then the others from the left: walks at the
+    // image's sides take longest
+    const int bx = blockIdx.y == 0 ? (int)gridDim.y - 1 : (int)blockIdx.y - 1;
+    const int xw = bx * 16 + 4 * uniform((int)threadIdx.x >> 6);  // the wave's first pixel
+    const int x = xw + (((int)threadIdx.x & 63) >> 4), y0 = (int)blockIdx.x * seg, y1 = min(y0 + seg, H);
+    if (xw >= W) return;
+    const Word *cl = (const Word *)a.census_l, *cr = (const Word *)a.census_r;
+    uint32_t keep[DPL / 2 + DPL % 2], fill[DPL / 2 + DPL % 2];  // the padding disparities' cost
+#pragma unroll
+    for (int j = 0; j < DPL; j += 2) {
+        const bool k0 = d0 + j < a.D, k1 = d0 + j + 1 < a.D;
+        keep[j / 2] = (k0 ? 0xFFFFu : 0u) | (k1 ? 0xFFFF0000u : 0u);
+        fill[j / 2] = (k0 ? 0u : (uint32_t)kBlockPadCost) | (k1 ? 0u : (uint32_t)kBlockPadCost << 16);
+    }
+    uint32_t sum[B][DPL];
+    auto put = [&](int y) {
+        uint32_t acc[DPL + 1];
+        acc[DPL] = 0;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) {
+            acc[j] = sum[0][j];
+#pragma unroll
+            for (int r = 1; r < B; ++r) acc[j] += sum[r][j];
+        }
+        uint16_t *o = a.vol + ((size_t)y * W + x) * kDpad + d0;
+        if constexpr (DPL == 1) {
+            *o = (uint16_t)((acc[0] & keep[0]) | fill[0]);
+        } else {
+            uint32_t v[DPL / 2];
+#pragma unroll
+            for (int j = 0; j < DPL; j += 2) v[j / 2] = ((acc[j] | acc[j + 1] << 16) & keep[j / 2]) | fill[j / 2];
+            __builtin_memcpy(__builtin_assume_aligned(o, DPL % 8 == 0 ? 16 : DPL % 4 == 0 ? 8 : 4), v, sizeof(v));
+        }
+    };
+    // rows y0 - hw .. y1 + hw - 1 in turn: load(y) gives a row's words, count() its sums
+    auto walk = [&](auto load, auto count) {
+        auto next = load(y0 - hw);
+#pragma unroll
+        for (int k = 0; k < B - 1; ++k) {
+            const auto w = next;
+            next = load(y0 - hw + k + 1);
+            count(w, sum[k]);
+        }
+        for (int y = y0; y < y1; y += B) {
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                if (y + k >= y1) return;
+                const auto w = next;
+                next = load(y + k + hw + 1);
+                count(w, sum[(k + B - 1) % B]);
+                if (x < W) put(y + k);
+            }
+        }
+    };
+    auto row_of = [&](int y) { return (size_t)min(max(y, 0), H - 1) * W; };
+    struct Row { Word l[B], r[kRight]; };
+    // first of the B image columns that hold the window's samples, and column of r[0]
+    const int xc = min(x, W - 1), xs = min(max(xc - hw, 0), W - B), c0 = xs - d0 - (DPL - 1);
+    if (xw - hw >= kDpad - 1 && xw + 3 + hw < W) {  // every sample inside the image
+        walk(
+            [&](int y) {
+                Row w;
+                __builtin_memcpy(w.l, cl + row_of(y) + xs, sizeof(w.l));
+                __builtin_memcpy(w.r, cr + row_of(y) + c0, sizeof(w.r));
+                return w;
+            },
+            [&](const Row &w, uint32_t (&s)[DPL]) {
+#pragma unroll
+                for (int j = 0; j < DPL; ++j) {
+                    s[j] = CW::hamming(w.l[0], w.r[DPL - 1 - j]);
+#pragma unroll
+                    for (int u = 1; u < B; ++u) s[j] += CW::hamming(w.l[u], w.r[u + DPL - 1 - j]);
+                }
+            });
+    } else {
+        // samples beyond a side repeat its column: each column counts as often as the
+        // clamped window holds it; a right word left of the image differs in every bit
+        uint32_t times[B];
+#pragma unroll
+        for (int c = 0; c < B; ++c) {
+            times[c] = 0;
+#pragma unroll
+            for (int u = -hw; u <= hw; ++u) times[c] += min(max(xc + u, 0), W - 1) == xs + c ? 1u : 0u;
+        }
+        const Word all = (Word)~(Word)0 >> (8 * (int)sizeof(Word) - a.bits);
+        Word left[kRight];
+#pragma unroll
+        for (int k = 0; k < kRight; ++k) left[k] = c0 + k < 0 ? all : 0;
+        walk(
+            [&](int y) {
+                Row w;
+                const size_t at = row_of(y);
+                __builtin_memcpy(w.l, cl + at + xs, sizeof(w.l));
+                if (at >= (size_t)kDpad) {  // left of the image lie words of the rows above
+                    __builtin_memcpy(w.r, cr + at + c0, sizeof(w.r));
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kRight; ++k) {
+                        w.r[k] = cr[max((int)at + c0 + k, 0)];
+                        asm volatile("" : "+v"(w.r[k]));  // keeps the two forms of load apart
+                    }
+                }
+                return w;
+            },
+            [&](const Row &w, uint32_t (&s)[DPL]) {
+#pragma unroll
+                for (int j = 0; j < DPL; ++j) {
+                    s[j] = 0;
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        const int k = u + DPL - 1 - j;
+                        s[j] += __umul24(times[u], CW::hamming((w.l[u] ^ w.r[k]) | left[k], 0));
+                    }
+                }
+            });
+    }
+}
+
 // ---------------------------------------------------------------- aggregation
 // The units' lines from the block-cost volume (16-bit path values): the horizontal
 // ones singly, with volume_horizontal_lanes() lanes each (the longest chains: fewer
@@ -126,12 +262,25 @@ __global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per
     }
 }
 
+// blocks of row walks a launch aims at
+constexpr int kRowWalks = 2048;
+
 template <int DPL>
 hipError_t launch_sgbm_dpl(const BlockCostArgs *bc, const VolumeArgs *va, bool wide, hipStream_t s)
 {
     if (bc) {
         dim3 grid((bc->W + 15) / 16, bc->H), block(256);
-        if (wide) hipLaunchKernelGGL((block_cost_kernel<DPL, true>), grid, block, 0, s, *bc);
+        if (bc->bw == bc->bh && (bc->bw == 3 || bc->bw == 5) && bc->W >= bc->bw) {
+            // rows per walk: enough walks to fill the chip, few enough that the B - 1
+            // rows a walk begins with stay a small part (960x540: 1024 blocks 64 us,
+            // 2048 59 us, 4096 62 us)
+            const int seg = std::min(std::max((int)((int64_t)grid.x * bc->H / kRowWalks), 4), 64);
+            grid = dim3((bc->H + seg - 1) / seg, grid.x);
+            if (bc->bw == 3 && wide) hipLaunchKernelGGL((block_cost_rows_kernel<DPL, true, 3>), grid, block, 0, s, *bc, seg);
+            else if (bc->bw == 3) hipLaunchKernelGGL((block_cost_rows_kernel<DPL, false, 3>), grid, block, 0, s, *bc, seg);
+            else if (wide) hipLaunchKernelGGL((block_cost_rows_kernel<DPL, true, 5>), grid, block, 0, s, *bc, seg);
+            else hipLaunchKernelGGL((block_cost_rows_kernel<DPL, false, 5>), grid, block, 0, s, *bc, seg);
+        } else if (wide) hipLaunchKernelGGL((block_cost_kernel<DPL, true>), grid, block, 0, s, *bc);
         else hipLaunchKernelGGL((block_cost_kernel<DPL, false>), grid, block, 0, s, *bc);
     } else {
         hipLaunchKernelGGL((aggregate_volume_kernel<DPL>), dim3(va->a.item_begin[va->a.nunits]), dim3(64 * kWavesPerItem), 0, s, *va);
