@@ -16,6 +16,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "internal.h"
 #include "net_internal.h"
 
@@ -57,12 +59,18 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v)
 // sub-strip it stages the 6 input rows x 66 columns it reads in LDS (pixel-major,
 // as in memory; positions outside the image are zeros), so every input pixel is
 // loaded once per sub-strip instead of once per tap, and a B fragment (8
-// channels of one pixel and tap) is one aligned 16-byte LDS read.  Each output's
+// channels of one pixel and tap) is one aligned 16-byte LDS read.  The layers are bound
+// by memory: the next sub-strip's input is in flight while one is computed, and the rows
+// of a weight block are ordered so that a lane stores its eight channels at once (a
+// wave's store is one run of memory, not halves of 64-byte pixels).  16 x 640x480,
+// before / with the loads ahead / with the wide stores as well: 32 -> 32 forward 194 /
+// 170 / 146 us (650 MB, 4.5 TB/s), its backward 182 / 154 / 149, 8 -> 32 114 / 114 / 94,
+// 16 -> 32 backward 128 / 122 / 97, 32 -> 2 114 / 88 / 90.  Three blocks a unit: with two
+// the 32 -> 32 layers take 5-10 us more.  Each output's
 // products are summed onto its starting value in k order.  A 32-channel ReLU layer
 // also stores which of its stored outputs are > 0, packed 4 bytes per pixel: byte q
-// holds channels 4q .. 4q+3 (bits 0-3) and 16+4q .. 16+4q+3 (bits 4-7), the eight
-// channels lane quad q holds in the MFMA output layout; backward-data reads that
-// byte instead of the 64-byte activation.
+// holds channels 8q .. 8q+7, the eight channels lane quad q holds; backward-data reads
+// that byte instead of the 64-byte activation.
 constexpr int kConvCols = 64;   // output columns per block
 constexpr int kConvRows = 4;    // output rows per sub-strip (one per wave)
 constexpr int kConvSubs = 4;    // sub-strips per block
@@ -74,7 +82,7 @@ typedef uint32_t u32x4c __attribute__((ext_vector_type(4)));
 __host__ __device__ constexpr int conv_pitch(int cinp) { return cinp == 32 ? 40 : cinp; }
 
 template <int CINP, int COUTP, int EPI>
-__global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a)
+__global__ __launch_bounds__(256, 3) void conv3x3_kernel(ConvArgs a)
 {
     constexpr int KPAD = kpad(CINP);
     constexpr int NK = KPAD / 32;
@@ -88,18 +96,21 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a)
     const int quad = lane >> 4, col = lane & 15;
     const uint16_t *__restrict__ wk = a.weights;
 
-    // A fragments (weights): lane holds co = 16*mb + col, k = 32*c + 8*quad .. +7
+    // the output channel of row r of row block mb: a lane's MB * 4 results are consecutive
+    // channels, so it stores them at once
+    auto channel = [](int mb, int r) { return MB * 4 * (r / 4) + 4 * mb + r % 4; };
+    // A fragments (weights): lane holds co = channel(mb, col), k = 32*c + 8*quad .. +7
     bf16x8 wa[MB][NK];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int c = 0; c < NK; ++c)
-            wa[mb][c] = as_bf16x8(*(const uint4 *)(wk + (size_t)(16 * mb + col) * KPAD + 32 * c + 8 * quad));
+            wa[mb][c] = as_bf16x8(*(const uint4 *)(wk + (size_t)channel(mb, col) * KPAD + 32 * c + 8 * quad));
     float bias[MB][4];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bias[mb][i] = a.bias ? a.bias[16 * mb + 4 * quad + i] : 0.0f;
+        for (int i = 0; i < 4; ++i) bias[mb][i] = a.bias ? a.bias[channel(mb, 4 * quad + i)] : 0.0f;
 
     const int W = a.W, H = a.H;
     const int cstrips = (W + kConvCols - 1) / kConvCols;
@@ -128,28 +139,44 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a)
         tap_keep[c] = tap < 9 ? ~0u : 0u;
     }
 
+    // a sub-strip's chunks of this thread and, for the masked epilogue, the ReLU masks of
+    // this wave's four tiles (one byte per lane: the lane's 8 output channels)
+    constexpr int NLD = (NCH + 255) / 256;
+    u32x4c nx[NLD];
+    uint32_t nmk[kConvCols / 16];
+    auto fetch = [&](int sub) {
+        const int y0 = (rg * kConvSubs + sub) * kConvRows, y = y0 + wave;
+#pragma unroll
+        for (int t = 0; t < kConvCols / 16; ++t) {
+            nmk[t] = 0;
+            const int x = x0 + 16 * t + col;
+            if (EPI == EPI_MASK && y < H && x < W) nmk[t] = a.mask[(img + (int64_t)y * W + x) * 4 + quad];
+        }
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            const int e = threadIdx.x + 256 * i, ch = 8 * (e % XC), pxi = e / XC, c = pxi % SC, r = pxi / SC;
+            const int gy = y0 - 1 + r, gx = x0 - 1 + c;
+            const bool in = e < NCH && gy >= 0 && gy < H && gx >= 0 && gx < W;
+            nx[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                rs_in, in ? (uint32_t)(((gy * W + gx) * CINP + ch) * 2) : kConvDrop, 0, 0);
+        }
+    };
+
+    fetch(0);
     for (int sub = 0; sub < kConvSubs; ++sub) {
         const int y0 = (rg * kConvSubs + sub) * kConvRows;
         if (y0 >= H) break;
         __syncthreads();  // the previous sub-strip's reads of the stage are done
         const int y = y0 + wave;  // this wave's output row
-        // the masked epilogue's ReLU masks of this wave's four tiles (one byte per
-        // lane: the lane's 8 output channels), loaded while the stage is filled
         uint32_t mk[kConvCols / 16];
 #pragma unroll
-        for (int t = 0; t < kConvCols / 16; ++t) {
-            mk[t] = 0;
-            const int x = x0 + 16 * t + col;
-            if (EPI == EPI_MASK && y < H && x < W) mk[t] = a.mask[(img + (int64_t)y * W + x) * 4 + quad];
+        for (int t = 0; t < kConvCols / 16; ++t) mk[t] = nmk[t];
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            const int e = threadIdx.x + 256 * i, ch = 8 * (e % XC), pxi = e / XC;
+            if (e < NCH) *(u32x4c *)&st[pxi / SC][pxi % SC][ch] = nx[i];
         }
-        for (int e = threadIdx.x; e < NCH; e += 256) {
-            const int ch = 8 * (e % XC), pxi = e / XC, c = pxi % SC, r = pxi / SC;
-            const int gy = y0 - 1 + r, gx = x0 - 1 + c;
-            const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-            const u32x4c v = __builtin_amdgcn_raw_buffer_load_b128(
-                rs_in, in ? (uint32_t)(((gy * W + gx) * CINP + ch) * 2) : kConvDrop, 0, 0);
-            *(u32x4c *)&st[r][c][ch] = v;
-        }
+        if (sub + 1 < kConvSubs) fetch(sub + 1);
         __syncthreads();
         if (y >= H) continue;
 #pragma unroll
@@ -177,18 +204,18 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a)
                     acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[mb][c], bv, acc[mb], 0, 0, 0);
             }
             if (x >= W) continue;
-            uint32_t mbits = 0;
-            // D layout: lane holds rows (output channels) 4*quad .. +3 of column (pixel) col
+            // D layout: lane holds rows 4*quad .. +3 of column (pixel) col of each row block
+            if constexpr (EPI == EPI_LINEAR) {
+                static_assert(MB == 1, "channels 0 and 1 are rows 0 and 1");
+                if (quad == 0) {
+                    float *o = (float *)a.out + p * 2;
+                    o[0] = acc[0][0];
+                    o[1] = acc[0][1];
+                }
+            } else {
+                uint32_t mbits = 0, w[2 * MB];
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int co = 16 * mb + 4 * quad;
-                if (EPI == EPI_LINEAR) {
-                    if (co == 0) {
-                        float *o = (float *)a.out + p * 2;
-                        o[0] = acc[mb][0];
-                        o[1] = acc[mb][1];
-                    }
-                } else {
+                for (int mb = 0; mb < MB; ++mb) {
                     float h[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -197,21 +224,21 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(ConvArgs a)
                         else v = (mk[t] >> (4 * mb + i)) & 1u ? v : 0.0f;  // the forward output was > 0
                         h[i] = v;
                     }
-                    uint2 w;
-                    w.x = pack_bf16(h[0], h[1]);
-                    w.y = pack_bf16(h[2], h[3]);
-                    *(uint2 *)((uint16_t *)a.out + p * COUTP + co) = w;
-                    if (EPI == EPI_RELU && COUTP == 32) {
+                    w[2 * mb] = pack_bf16(h[0], h[1]);
+                    w[2 * mb + 1] = pack_bf16(h[2], h[3]);
+                    if (EPI == EPI_RELU) {
                         // which of the stored values are > 0 (non-zero magnitude, sign
                         // clear), as bits 4 mb + i of the lane's mask byte
-                        const uint32_t q[4] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
+                        const uint32_t q[4] = {w[2 * mb] & 0xFFFFu, w[2 * mb] >> 16, w[2 * mb + 1] & 0xFFFFu, w[2 * mb + 1] >> 16};
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             mbits |= ((q[i] & 0x7FFFu) != 0 && !(q[i] & 0x8000u) ? 1u : 0u) << (4 * mb + i);
                     }
                 }
+                static_assert(MB == 2, "16 bytes per lane");
+                *(uint4 *)((uint16_t *)a.out + p * COUTP + 8 * quad) = uint4{w[0], w[1], w[2], w[3]};
+                if (EPI == EPI_RELU && a.mask_out) a.mask_out[p * 4 + quad] = (uint8_t)mbits;
             }
-            if (EPI == EPI_RELU && COUTP == 32 && a.mask_out) a.mask_out[p * 4 + quad] = (uint8_t)mbits;
         }
     }
 }
@@ -246,20 +273,26 @@ hipError_t launch_conv(const ConvArgs &a, int cinp, int coutp, int epi, hipStrea
 // pixels x 16 k).  A block owns a 32-pixel column strip of one image over a range
 // of rows and walks down it.  Per output row it takes that row's dY segment and the
 // next input row (34 pixels: the strip and one column each side) with 16-byte
-// loads issued one row ahead, and stores them in LDS as they are (pixel-major, a
-// ring of three input rows), one 16-byte store per chunk.  The operands, which
+// loads issued two rows ahead, and stores them in LDS as they are (pixel-major, a
+// ring of four input rows and two dY rows, so one barrier a row is enough), one 16-byte
+// store per chunk.  The operands, which
 // need 8 consecutive pixels of one channel per lane, are read with the LDS
 // transpose read (ds_read_b64_tr_b16): within 16 lanes, lane 4 j + a reads
 // channels 4 a .. 4 a + 3 of pixel j, and lane n receives channel n of the four
 // pixels; a horizontal tap is a shift of the pixel index, so each input row is
-// stored once.  The bias gradient (the sum of dY over the pixels) is taken from
+// stored once.  With 32 input channels a wave takes whole columns of tiles, so a B
+// fragment is read once for all output channels.  Bound by memory latency: 16 x 640x480
+// before / now 32 x 32 211 / 153 us (630 MB), 32 x 16 137 / 117, 8 x 32 113 / 101; four
+// rows ahead cost registers for a block a unit (194 us), as did the 32 x 32 form without
+// the bound of five.  The bias gradient (the sum of dY over the pixels) is taken from
 // the same staged rows.  Per-block partial sums go out and are reduced in a fixed
 // order, so the result does not depend on the schedule.
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWgBufWord3 = 0x00020000;     // buffer resource word 3 for raw byte buffers
-constexpr uint32_t kWgDrop = 0x80000000u;   // an offset past every map here: the load returns zeros
+constexpr int kWgAhead = 2;                 // rows in flight
+constexpr uint32_t kWgDrop = 0x80000000u;   // an offset past every map here, also with a row's added: zeros
 
 // four pixels x 16 channels from a pixel-major LDS array, transposed: lane
 // 16 g + n gets channel n of the four pixels (the caller passes, for its lane
@@ -270,17 +303,22 @@ __device__ __forceinline__ bf16x4 read_tr(const uint16_t *p)
 }
 
 template <int CINP, int COUTP>
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
+__global__ __launch_bounds__(256, 5) void wgrad_kernel(WgradArgs a)
 {
     constexpr int NB = (9 * CINP + 15) / 16;    // N blocks of 16 (k = tap*CINP + ci)
     constexpr int MB = COUTP / 16;
     constexpr int TILES = MB * NB;
-    constexpr int TPW = (TILES + 3) / 4;        // tiles per wave
+    // tiles of a wave: with 16 k blocks or more, whole columns of MB tiles (each B
+    // fragment is read once), else single tiles
+    constexpr bool COLS = NB >= 16;
+    constexpr int TPB = COLS ? (NB + 3) / 4 : (TILES + 3) / 4;  // B fragments per wave
+    constexpr int TPW = COLS ? MB * TPB : TPB;                   // tiles per wave
+    static_assert(MB == 1 || MB == 2, "a wave's single tiles share one row block");
     constexpr int DYC = COUTP / 8, XC = CINP / 8;  // 16-byte chunks per pixel
     static_assert(32 * DYC <= 256 && 34 * XC <= 272, "one dY and one input chunk per thread (two for 8 threads)");
     static_assert(CINP % 4 == 0, "a transpose-read lane's four channels share one tap");
-    __shared__ __align__(16) uint16_t sdy[32][COUTP];      // [px][co]
-    __shared__ __align__(16) uint16_t sx[3][34][CINP];     // [ring slot][input column x0 - 1 + m][ci]
+    __shared__ __align__(16) uint16_t sdys[2][32][COUTP];  // [row & 1][px][co]
+    __shared__ __align__(16) uint16_t sx[4][34][CINP];     // [ring slot][input column x0 - 1 + m][ci]
     __shared__ float sbias[256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int quad = lane >> 4;
@@ -318,17 +356,18 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
         (void *)(a.dy + img * COUTP), 0, (int)((int64_t)H * W * COUTP * 2), kWgBufWord3);
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(a.x + img * CINP), 0, (int)((int64_t)H * W * CINP * 2), kWgBufWord3);
-    u32x4 ndy = {0, 0, 0, 0}, nx0 = ndy, nx1 = ndy;
-    auto fetch = [&](int it) {
+    u32x4 ndy[kWgAhead], nx0[kWgAhead], nx1[kWgAhead];
+    const uint32_t ldy = dy_in ? (uint32_t)(((x0 + dpx) * COUTP + dch) * 2) : kWgDrop;
+    const uint32_t lx0 = v0 ? (uint32_t)(((x0 - 1 + m0) * CINP + c0) * 2) : kWgDrop;
+    const uint32_t lx1 = v1 ? (uint32_t)(((x0 - 1 + m1) * CINP + c1) * 2) : kWgDrop;
+    auto fetch = [&](int it, int s) {
         // this iteration's rows: input row y0 - 1 + it, dY row y0 - 2 + it
         const int xrow = y0 - 1 + it, drow = y0 - 2 + it;
-        const uint32_t ody = dy_in && drow >= y0 ? (uint32_t)(((drow * W + x0 + dpx) * COUTP + dch) * 2) : kWgDrop;
-        const bool row_ok = xrow >= 0 && xrow < H && xrow <= y1;
-        const uint32_t ox0 = v0 && row_ok ? (uint32_t)(((xrow * W + x0 - 1 + m0) * CINP + c0) * 2) : kWgDrop;
-        const uint32_t ox1 = v1 && row_ok ? (uint32_t)(((xrow * W + x0 - 1 + m1) * CINP + c1) * 2) : kWgDrop;
-        ndy = __builtin_amdgcn_raw_buffer_load_b128(rs_dy, ody, 0, 0);
-        nx0 = __builtin_amdgcn_raw_buffer_load_b128(rs_x, ox0, 0, 0);
-        nx1 = __builtin_amdgcn_raw_buffer_load_b128(rs_x, ox1, 0, 0);
+        const bool dy_ok = drow >= y0 && drow < y1, x_ok = xrow >= 0 && xrow < H && xrow <= y1;
+        const uint32_t rdy = (uint32_t)drow * (uint32_t)(W * COUTP * 2), rx = (uint32_t)xrow * (uint32_t)(W * CINP * 2);
+        ndy[s] = __builtin_amdgcn_raw_buffer_load_b128(rs_dy, dy_ok ? ldy + rdy : kWgDrop, 0, 0);
+        nx0[s] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_ok ? lx0 + rx : kWgDrop, 0, 0);
+        if (34 * XC > 256) nx1[s] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_ok ? lx1 + rx : kWgDrop, 0, 0);
     };
 
     // transpose-read roles of this lane in its 16-lane group: pixel j of four,
@@ -342,40 +381,80 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
     constexpr int BG = 256 / COUTP, BPX = 32 / BG;
     float bsum = 0.0f;
 
-    const int nit = y1 - y0 + 2;
-    fetch(0);
-    for (int it = 0; it < nit; ++it) {
-        const int xrow = y0 - 1 + it, y = y0 - 2 + it;
-        __syncthreads();  // the previous iteration's reads of sdy and of this ring slot are done
-        const int slot = (xrow + 3) % 3;
-        if (dy_role) *(u32x4 *)&sdy[dpx][dch] = ndy;
-        if (xr0) *(u32x4 *)&sx[slot][m0][c0] = nx0;
-        if (xr1) *(u32x4 *)&sx[slot][m1][c1] = nx1;
-        if (it + 1 < nit) fetch(it + 1);
-        __syncthreads();
-        if (y < y0) continue;  // ring warm-up: input rows y0 - 1 and y0
-        // output row y reads input rows y-1 .. y+1: ring slots (y + 2 + ky) % 3;
-        // lane group quad takes pixels 8 quad .. 8 quad + 7 (two reads of four)
+    // the B fragments of a wave's q-th k block: k columns 16 nb + ta .. +3 share one tap
+    // (taps past 8 are padding columns, whose results are not stored: any in-bounds
+    // values do); output row y reads input row y - 1 + tap / 3, whose slot is tap / 3
+    // after the one of row y - 1.  Where a wave's lanes share the tap, the slot's offset
+    // is added per row; else the addresses for the four slots of row y - 1 are kept.
+    const int px = 8 * quad + tj;
+    constexpr bool kOneTap = CINP % 16 == 0;
+    const uint16_t *bp[TPB][kOneTap ? 1 : 4];
+    int ky[TPB];
 #pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int tile = wave + 4 * q;
-            if (tile >= TILES) break;
-            const int mb = tile % MB, nb = tile / MB;
-            const int px = 8 * quad + tj;
+    for (int q = 0; q < TPB; ++q) {
+        const int nb = COLS ? wave + 4 * q : (wave + 4 * q) / MB, kk = 16 * nb + ta;
+        const int tap = min(kk / CINP, 8), ci = kk % CINP;
+        ky[q] = __builtin_amdgcn_readfirstlane(tap / 3);
+        if constexpr (kOneTap) {
+            bp[q][0] = &sx[0][px + tap % 3][ci];
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bp[q][r] = &sx[(r + tap / 3) & 3][px + tap % 3][ci];
+        }
+    }
+    // input row y0 - 1 + it lies in ring slot it % 4, dY row y0 - 2 + it in buffer it % 2
+    const int nit = y1 - y0 + 2;
+#pragma unroll
+    for (int i = 0; i < kWgAhead; ++i) fetch(i, i);
+    auto step = [&](int it, auto ic) {
+        constexpr int i = decltype(ic)::value, s = i % kWgAhead, slot = i, first = (i + 2) & 3;
+        // the slots written here are not among those the iteration before reads, and the
+        // barrier of that one is past the reads of the one before it
+        uint16_t(*sdy)[COUTP] = sdys[i & 1];
+        if (dy_role) *(u32x4 *)&sdy[dpx][dch] = ndy[s];
+        if (xr0) *(u32x4 *)&sx[slot][m0][c0] = nx0[s];
+        if (34 * XC > 256 && xr1) *(u32x4 *)&sx[slot][m1][c1] = nx1[s];
+        fetch(it + kWgAhead, s);
+        __syncthreads();
+        if (it < 2) return;  // ring warm-up: input rows y0 - 1 and y0
+        // lane group quad takes pixels 8 quad .. 8 quad + 7 (two reads of four)
+        auto read_a = [&](int mb) {
             const bf16x4 a0 = read_tr(&sdy[px][16 * mb + ta]), a1 = read_tr(&sdy[px + 4][16 * mb + ta]);
-            // k columns 16 nb + ta .. +3 share one tap (taps past 8 are padding
-            // columns, whose results are not stored: any in-bounds values do)
-            const int kk = 16 * nb + ta;
-            const int tap = min(kk / CINP, 8), ci = kk % CINP;
-            const uint16_t(*xs)[CINP] = sx[(y + 2 + tap / 3) % 3];
-            const int xm = px + tap % 3;
-            const bf16x4 b0 = read_tr(&xs[xm][ci]), b1 = read_tr(&xs[xm + 4][ci]);
-            const bf16x8 av = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-            const bf16x8 bv = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
-            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[q], 0, 0, 0);
+            return __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto read_b = [&](int q) {
+            const uint16_t *at = kOneTap ? bp[q][0] + ((first + ky[q]) & 3) * (34 * CINP) : bp[q][kOneTap ? 0 : first];
+            const bf16x4 b0 = read_tr(at), b1 = read_tr(at + 4 * CINP);
+            return __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        if constexpr (COLS) {
+            bf16x8 av[MB];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) av[mb] = read_a(mb);
+#pragma unroll
+            for (int q = 0; q < TPB; ++q) {
+                if (wave + 4 * q >= NB) break;
+                const bf16x8 bv = read_b(q);
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[MB * q + mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mb], bv, acc[MB * q + mb], 0, 0, 0);
+            }
+        } else {
+            const bf16x8 av = read_a(wave % MB);  // 4 % MB == 0: one row block per wave
+#pragma unroll
+            for (int q = 0; q < TPB; ++q) {
+                if (wave + 4 * q >= TILES) break;
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, read_b(q), acc[q], 0, 0, 0);
+            }
         }
 #pragma unroll
-        for (int i = 0; i < BPX; ++i) bsum += bf2f(sdy[BPX * (t / COUTP) + i][t % COUTP]);
+        for (int k = 0; k < BPX; ++k) bsum += bf2f(sdy[BPX * (t / COUTP) + k][t % COUTP]);
+    };
+    for (int it = 0; it < nit; it += 4) {
+        step(it, std::integral_constant<int, 0>{});
+        if (it + 1 < nit) step(it + 1, std::integral_constant<int, 1>{});
+        if (it + 2 < nit) step(it + 2, std::integral_constant<int, 2>{});
+        if (it + 3 < nit) step(it + 3, std::integral_constant<int, 3>{});
     }
     // partial[block][co][k]
     const int col = lane & 15;
@@ -383,8 +462,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a)
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
         const int tile = wave + 4 * q;
-        if (tile >= TILES) break;
-        const int mb = tile % MB, nb = tile / MB;
+        const int mb = COLS ? q % MB : tile % MB, nb = COLS ? wave + 4 * (q / MB) : tile / MB;
+        if (nb >= NB) break;
         if (16 * nb + col >= 9 * CINP) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) part[(size_t)(16 * mb + 4 * quad + i) * 9 * CINP + 16 * nb + col] = acc[q][i];
