@@ -494,27 +494,28 @@ def main():
     agg_ops = AGG_OPS_PER_PDR * P * vol
     achieved = agg_ops / agg_s
     kernel = "aggregate_queue_kernel" if ss.get_tuning()["blocks_per_cu"] > 0 else "aggregate_kernel"
-    # the kernel's path arithmetic runs in 32-bit lanes, so its peak is the
-    # 32-bit one; the packed 16-bit peak (what a u16 form could reach) is beside it
+    # the pass (costs and paths) computes in packed 16-bit lanes, so its peak is the
+    # packed one; the 32-bit peak is beside it
     roofline = {"kernel": kernel, "bound": "alu", "achieved": round(achieved / 1e12, 3),
-                "peak": round(VALU_PEAK_OPS / 1e12, 3), "unit": "Tops/s", "frac": round(achieved / VALU_PEAK_OPS, 4),
+                "peak": round(VALU_PEAK_OPS_PACKED16 / 1e12, 3), "unit": "Tops/s",
+                "frac": round(achieved / VALU_PEAK_OPS_PACKED16, 4),
                 "traffic": measured_traffic(),
-                "peak_packed_u16": round(VALU_PEAK_OPS_PACKED16 / 1e12, 3),
-                "frac_packed_u16": round(achieved / VALU_PEAK_OPS_PACKED16, 4),
+                "peak_u32": round(VALU_PEAK_OPS / 1e12, 3),
+                "frac_u32": round(achieved / VALU_PEAK_OPS, 4),
                 "ops_per_pixel_disp_path": AGG_OPS_PER_PDR,
                 "ops_per_launch": agg_ops, "avg_launch_us": round(agg_s * 1e6, 2),
                 "timed_by": "library per-pass HIP events on the launch stream, second timed loop of the same steps"}
     # floors of the whole step: with 8 paths the summed costs cannot stay on
     # chip, so at least one uint16 write and read of W*H*D values, plus the two
     # images in and depth, disparity and flags out; and the aggregation's
-    # operations at the VALU peak
+    # operations at the packed VALU peak
     step_s = ms_step / 1000.0
     hbm_floor_bytes = 4 * vol + (2 + 4 + 4 + 1) * W * H
     floors = {"hbm_bytes": hbm_floor_bytes, "hbm_us": round(hbm_floor_bytes / HBM_PEAK * 1e6, 2),
-              "valu_ops": agg_ops, "valu_us": round(agg_ops / VALU_PEAK_OPS * 1e6, 2),
+              "valu_ops": agg_ops, "valu_us": round(agg_ops / VALU_PEAK_OPS_PACKED16 * 1e6, 2),
               "step_us": round(step_s * 1e6, 2),
               "hbm_frac": round(hbm_floor_bytes / HBM_PEAK / step_s, 4),
-              "valu_frac": round(agg_ops / VALU_PEAK_OPS / step_s, 4)}
+              "valu_frac": round(agg_ops / VALU_PEAK_OPS_PACKED16 / step_s, 4)}
     floors["roofline_fraction"] = max(floors["hbm_frac"], floors["valu_frac"])
     out = {
         "metric": "stereo pairs/sec & Mpix·disp/s at 1280×720 D=128: 8-path SGM vs 2-path+net",

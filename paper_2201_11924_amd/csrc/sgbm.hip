@@ -5,9 +5,8 @@
 //
 // Two passes: block_cost_rows_kernel (square blocks of 3 and 5) or block_cost_kernel
 // writes the block-cost volume (16-bit, d fastest, the path buffers' layout);
-// aggregate_volume_kernel runs the path
-// recurrence of every line from that volume, with the lines, steps and pairs of
-// the census-fed aggregation.
+// aggregate_volume_kernel runs the path recurrence of every line from that volume,
+// with the lines, steps and pairs of the census-fed aggregation.
 #include "aggregate_impl.h"
 
 namespace ss {
