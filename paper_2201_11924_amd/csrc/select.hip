@@ -227,16 +227,16 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
     constexpr int kValBytes = V16 ? 2 : 1;
     constexpr int kDpad = kLanesPerLine * DPL;
     const int W = a.W, D = a.D;
-    // LDS: right-image keys indexed by xr + Dpad (xr >= -(Dpad-1)); the row's
-    // per-pixel results, written to HBM in coalesced row stores after the pixel
-    // loop (the loop itself issues no global store, so its look-ahead loads are
-    // waited on precisely)
+    // LDS: right-image keys indexed by xr + Dpad (xr >= -(Dpad-1)); what a pixel's
+    // results follow from, taken up after the pixel loop with one pixel per thread:
+    // the uniqueness test and the sub-pixel fit there instead of by one lane of 16 in
+    // the loop (whose instructions bound the pass over two planes: 16 pairs of
+    // 1280x720 808 -> 754 us), and coalesced row stores (the loop itself issues no global store,
+    // so its look-ahead loads are waited on precisely)
     uint32_t *keyR = smem;
-    float *dsub_row = (float *)(keyR + kDpad + W);
-    uint16_t *s1_row = (uint16_t *)(dsub_row + W);
-    uint16_t *s2_row = s1_row + W;
-    uint8_t *dint_row = (uint8_t *)(s2_row + W);
-    uint8_t *uniq_row = dint_row + W;
+    uint32_t *best_row = keyR + kDpad + W;  // S1 << 8 | d*
+    uint32_t *nb_row = best_row + W;        // S(d* - 1) << 16 | S(d* + 1)
+    uint16_t *s2_row = (uint16_t *)(nb_row + W);
     const size_t row = (size_t)y * W;
     if (right)
         for (int i = threadIdx.x; i < kDpad + W; i += kSelBlock) keyR[i] = 0xFFFFFFFFu;
@@ -284,7 +284,6 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
         }
         kmin = row_min(kmin);
         const int dstar = (int)(kmin & 0xFF);
-        const uint32_t s1 = kmin >> 8;
         // second best: the minimum of S outside the winner's window d*-1 .. d*+1,
         // from the registers (d is in the window when d - d* + 1 is 0, 1 or 2;
         // padding disparities hold 0xFFFF)
@@ -298,18 +297,9 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
         // and an AND over the row gathers both halves into one word
         const uint32_t nb = row_and((pick_value<DPL>(S, dstar - 1 - d0) << 16) | pick_value<DPL>(S, dstar + 1 - d0));
         if (lane == 0) {
-            const int u = a.uniqueness_pct;
-            const bool uniq = u == 0 || s2 == 0xFFFFu || 100u * s1 <= (uint32_t)(100 - u) * s2;
-            float ds = (float)dstar;
-            if (a.subpixel && dstar > 0 && dstar < D - 1) {
-                const int am = (int)(nb >> 16) - (int)s1, bp = (int)(nb & 0xFFFF) - (int)s1;
-                ds = __fadd_rn((float)dstar, __fdiv_rn((float)(am - bp), (float)(2 * (am + bp))));
-            }
-            s1_row[x] = (uint16_t)s1;
+            best_row[x] = kmin;
+            nb_row[x] = nb;
             s2_row[x] = (uint16_t)s2;
-            dint_row[x] = (uint8_t)dstar;
-            dsub_row[x] = ds;
-            uniq_row[x] = uniq;
         }
     };
     // (one step's loads after the other, not interleaved by the scheduler: the
@@ -328,24 +318,30 @@ __device__ __forceinline__ void select_row(const SelectArgs &a, int y, uint32_t 
         }
     }
     __syncthreads();
-    const int lr = a.lr_max_diff;
+    const int lr = a.lr_max_diff, u = a.uniqueness_pct;
     global_t<uint8_t> *const o_flags = global_ptr(a.flags), *const o_dint = global_ptr(a.disp_int);
     global_t<uint8_t> *const o_dright = global_ptr(a.disp_right);
     global_t<float> *const o_masked = global_ptr(a.masked), *const o_dsub = global_ptr(a.disp_sub);
     global_t<uint16_t> *const o_s1 = global_ptr(a.cost_best), *const o_s2 = global_ptr(a.cost_second);
     for (int x = threadIdx.x; x < W; x += kSelBlock) {
-        const int d = dint_row[x];
-        const int xr = x - d;
+        const uint32_t best = best_row[x], nb = nb_row[x], s1 = best >> 8, s2 = s2_row[x];
+        const int d = (int)(best & 0xFF), xr = x - d;
+        const bool uq = u == 0 || s2 == 0xFFFFu || 100u * s1 <= (uint32_t)(100 - u) * s2;
+        float ds = (float)d;
+        if (a.subpixel && d > 0 && d < D - 1) {
+            const int am = (int)(nb >> 16) - (int)s1, bp = (int)(nb & 0xFFFF) - (int)s1;
+            ds = __fadd_rn((float)d, __fdiv_rn((float)(am - bp), (float)(2 * (am + bp))));
+        }
         bool lr_ok = true;
         if (right && lr >= 0) lr_ok = xr >= 0 && abs(d - (int)(keyR[xr + kDpad] & 0xFF)) <= lr;
-        const bool nz = d > 0, uq = uniq_row[x] != 0;
+        const bool nz = d > 0;
         o_flags[row + x] = (uint8_t)(uq | (lr_ok << 1) | (nz << 2));
-        o_masked[row + x] = (uq && lr_ok && nz) ? dsub_row[x] : 0.0f;
+        o_masked[row + x] = (uq && lr_ok && nz) ? ds : 0.0f;
         if (right) o_dright[row + x] = (uint8_t)(keyR[x + kDpad] & 0xFF);
         o_dint[row + x] = (uint8_t)d;
-        o_s1[row + x] = s1_row[x];
-        o_s2[row + x] = s2_row[x];
-        o_dsub[row + x] = dsub_row[x];
+        o_s1[row + x] = (uint16_t)s1;
+        o_s2[row + x] = (uint16_t)s2;
+        o_dsub[row + x] = ds;
     }
 }
 
