@@ -247,7 +247,7 @@ int build_plan(simsense_batch *b)
         P.post_item_off = items.size();
         for (int s = P.s0; s < P.s1; ++s) {
             const Slot &sl = b->slots[s];
-            const int t = ((sl.p.width + 63) / 64) * ((sl.p.height + 3) / 4);
+            const int t = ((sl.p.width + 63) / 64) * ((sl.p.height + kPostTileRows - 1) / kPostTileRows);
             for (int i = 0; i < t; ++i) items.push_back(((uint32_t)s << 20) | (uint32_t)i);
         }
         P.post_nitems = (int)(items.size() - P.post_item_off);

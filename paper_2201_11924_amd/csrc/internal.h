@@ -190,6 +190,7 @@ struct SelectBatch {
     int nitems, max_width;
     int no_right;           // as SelectArgs::no_right, for every slot of the launch
 };
+constexpr int kPostTileRows = 16;  // rows of a batch's post tile (64 columns)
 struct PostBatch {
     const PostArgs *slots;
     const uint32_t *items;  // slot << 20 | tile (64x4 tiles, row-major)
