@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void noise_apply_kernel(NoiseArgs a, const uin
     out[(size_t)y * out_pitch + x] = (uint8_t)r;
 }
 
-NoiseArgs noise_args(const simsense_noise_params &p)
+NoiseArgs noise_args(const simsense_noise_params &p, int64_t pixels = 0)
 {
     NoiseArgs a{};
     a.gain_model = p.gain_model;
@@ -212,10 +212,13 @@ NoiseArgs noise_args(const simsense_noise_params &p)
     // the value (2e-6 of the draws' spread) well below one half (1920x1080 in us, double /
     // single: sigma 900 16.9 / 13.4, gain_sd 3.9 30.2 / 19.5, at the line), the shape small
     // enough for the acceptance test, whose error grows with k (k 256 46.2 / 24.3, 1024
-    // 45.5 / 28.5, 4096 45.1 / 39.5; 640x480 10.1 / 9.9 at 1024, 10.0 / 10.5 at 4096)
+    // 45.5 / 28.5, 4096 45.1 / 39.5; 640x480 10.1 / 9.9 at 1024, 10.0 / 10.5 at 4096),
+    // the image large enough that its waves wait for each other and not for the few that
+    // draw twice (kernel alone: 320x240 7.0 / 6.1, 237x137 5.5 / 5.7, 171x134 without a
+    // gain 2.4 / 2.9)
     const double spread = p.gain_model == 1 ? 2.0 * d * (double)p.theta : p.gain_model == 2 ? (double)p.gain_sd : 0.0;
     const bool shape = p.gain_model != 1 || p.k <= 1024.0f;
-    a.fast = shape && (double)p.scale * (255.0 * spread + (double)p.sigma + fabs((double)p.mu) / 8.0) * 2e-6 <= 2e-3;
+    a.fast = pixels >= 65536 && shape && (double)p.scale * (255.0 * spread + (double)p.sigma + fabs((double)p.mu) / 8.0) * 2e-6 <= 2e-3;
     return a;
 }
 
@@ -260,8 +263,8 @@ int simsense_ir_noise_generate(const simsense_noise_params *params, const uint8_
     if (in_pitch < width || out_pitch < width) return SIMSENSE_ERR_INVALID_ARGUMENT;
     if (!in || !out) return SIMSENSE_ERR_NULL_POINTER;
     dim3 grid((width + 255) / 256, height), block(256);
-    hipLaunchKernelGGL(noise_apply_kernel, grid, block, 0, (hipStream_t)stream, noise_args(*params), in, in_pitch,
-                       width, height, out, out_pitch);
+    hipLaunchKernelGGL(noise_apply_kernel, grid, block, 0, (hipStream_t)stream, noise_args(*params, (int64_t)width * height), in,
+                       in_pitch, width, height, out, out_pitch);
     if (hipGetLastError() != hipSuccess) return SIMSENSE_ERR_DEVICE;
     return SIMSENSE_OK;
 }
