@@ -430,8 +430,11 @@ int simsense_compute_noalloc(const simsense_params *params, const uint8_t *left,
 /* Human-readable name of a status code (static storage). */
 const char *simsense_strerror(int status);
 
-/* Bytes of device scratch a handle with these parameters allocates, or a
- * negative status if the parameters are invalid. */
+/* Bytes of device scratch a handle with these parameters needs, or a negative
+ * status if the parameters are invalid.  A handle may hold one path buffer more
+ * than that (width * height bytes per padded disparity): where bits + p2 > 127,
+ * it keeps matching costs there if the device has the memory, and only takes
+ * longer without. */
 int64_t simsense_scratch_bytes(const simsense_params *params);
 
 #ifdef __cplusplus

@@ -389,7 +389,7 @@ int64_t simsense_scratch_bytes(const simsense_params *params)
 {
     int rc = validate(params);
     if (rc != SIMSENSE_OK) return rc;
-    return (int64_t)layout(params, true).total;
+    return (int64_t)layout(params, false).total;
 }
 
 int simsense_create(const simsense_params *params, simsense_handle **out)
