@@ -74,14 +74,13 @@ bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl)
 // are the longest chains: walking them one and a half times holds up the launch).  They
 // count census bits themselves where that is one word a pixel, and read the volume where
 // it is two (641x479, D = 100, full census: aggregation 215 -> 176 us; one word,
-// 1280x720: 277 -> 289 us).  The cost
-// volume takes the last path buffer: sums leave it free; otherwise, without a spare
-// one, the direction that fills it runs after all others and replaces each cost by its
-// path value (each is read once, before it is overwritten).
-void plan_aggregation(AggregateArgs &a, int num_paths, bool sums, bool row_sums, bool block, int hl, uint8_t *const *buffers,
-                      int nbuffers)
+// 1280x720: 277 -> 289 us).  The cost volume takes the last path buffer: sums leave it
+// free; otherwise, without a spare one, the direction that fills it runs after all others
+// and replaces each cost by its path value (each is read once, before it is overwritten).
+void plan_aggregation(AggregateArgs &a, int num_paths, bool costs, bool sums, bool row_sums, bool block, int hl,
+                      uint8_t *const *buffers, int nbuffers)
 {
-    if (!block) a.cost = num_paths > 2 ? buffers[nbuffers - 1] : nullptr;
+    if (!block) a.cost = costs ? buffers[nbuffers - 1] : nullptr;
     a.row_costs = a.cost && (block || a.bits > 32);
     a.nunits = 0;
     for (int r = 0; r < num_paths; ++r) {
@@ -93,7 +92,7 @@ void plan_aggregation(AggregateArgs &a, int num_paths, bool sums, bool row_sums,
         a.pair[u] = pair;
         a.out[u] = buffers[u];
     }
-    a.last_first = a.out[a.nunits - 1] == a.cost ? a.nunits - 1 : a.nunits;
+    a.last_first = a.cost && a.out[a.nunits - 1] == a.cost ? a.nunits - 1 : a.nunits;
     a.item_begin[0] = 0;
     a.max_item_work = 1;
     for (int u = 0; u < a.nunits; ++u) {
@@ -108,6 +107,10 @@ int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl)
     const int dx = a.dx[unit], dy = a.dy[unit], n = path_lines(dx, dy, a.W, a.H);
     const int lines = item_lines(a, unit, hl), lanes = dy == 0 ? effective_lanes(a.Dpad, hl) : kLanesPerLine;
     int len = 0;
+    if (counts_census(a) && dy != 0) {
+        const ColumnLines g = column_lines(dx, item, a.W, a.H);
+        return (g.end - g.begin) * agg_step_cost(column_disparities(a.Dpad), lanes);
+    }
     for (int l = item * lines; l < std::min(n, (item + 1) * lines); ++l) len = std::max(len, line_length(dx, dy, l, a.W, a.H));
     const int steps = a.pair[unit] ? 3 * len / 2 : len;  // of each wave, in a row
     return steps * agg_step_cost(lane_disparities(a.Dpad, lanes), lanes);
@@ -120,7 +123,7 @@ hipError_t launch_aggregate(const AggregateArgs &a, bool wide, int hl, hipStream
 
 hipError_t launch_aggregate_queue(const AggregateQueue &q, int dpad, bool wide, int hl, int grid, hipStream_t s)
 {
-    if (grid + q.nlast == 0) return hipSuccess;
+    if (grid == 0) return hipSuccess;
     return launch_agg(nullptr, &q, grid, dpad, hl, wide, s);
 }
 

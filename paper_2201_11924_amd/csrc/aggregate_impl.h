@@ -38,7 +38,8 @@
 // cost_kernel wrote (1 byte per pixel and disparity, in the path buffers' layout):
 // recomputing them from the census words costs 4.7 SIMD cycles more per disparity
 // and step than unpacking a byte.  Costs where x - d < 0 are `bits`, and 255 where
-// d >= D, so the steps need no border case.  Horizontal units count the bits of
+// d >= D, so the steps need no border case.  Where no buffer is left for the volume they
+// count 32-bit words after all (run_columns).  Horizontal units count the bits of
 // 32-bit census words themselves (a lane's right words slide by one column per step:
 // the pixels of a segment share all but a few), which saves the reads.
 #pragma once
@@ -66,6 +67,7 @@ constexpr uint32_t kNone = 0x7BFF7BFFu;
 // DPP controls (GFX9 encoding)
 constexpr int kRowShl1 = 0x101, kRowShr1 = 0x111;
 constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
+constexpr int kQuadOdd = 0xF5;  // lanes 1, 1, 3, 3 of each four
 constexpr int kWaveShl1 = 0x130, kWaveShr1 = 0x138;
 
 __device__ __forceinline__ u16x2_t h2(uint32_t v) { return __builtin_bit_cast(u16x2_t, v); }
@@ -77,6 +79,12 @@ __device__ __forceinline__ uint32_t pk_min3(uint32_t a, uint32_t b, uint32_t c)
 {
     const f16x2_t m = __builtin_elementwise_minimum(__builtin_bit_cast(f16x2_t, a), __builtin_bit_cast(f16x2_t, b));
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(m, __builtin_bit_cast(f16x2_t, c)));
+}
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) { return w1(__builtin_elementwise_max(h2(a), h2(b))); }
+__device__ __forceinline__ uint32_t pk_max3(uint32_t a, uint32_t b, uint32_t c)
+{
+    const f16x2_t m = __builtin_elementwise_maximum(__builtin_bit_cast(f16x2_t, a), __builtin_bit_cast(f16x2_t, b));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(m, __builtin_bit_cast(f16x2_t, c)));
 }
 // a 16-bit value in both halves
 __device__ __forceinline__ uint32_t both(uint32_t v) { return w1(u16x2_t{(uint16_t)v, (uint16_t)v}); }
@@ -184,7 +192,7 @@ struct LineOps {
 // order in memory.  DPL = 1 uses the low half only.
 template <int DPL, bool V16>
 struct Lane {
-    static_assert(DPL <= 2 || DPL % 4 == 0, "two disparities per register, whole words in memory");
+    static_assert(DPL <= 2 || DPL % 4 == 0 || (DPL == 6 && !V16), "two disparities per register, whole words in memory (6: 16-bit pieces)");
     static constexpr int N = DPL == 1 ? 1 : DPL / 2;
     static constexpr int kBytes = DPL * (V16 ? 2 : 1);
     static constexpr int NW = (kBytes + 3) / 4;  // words in memory
@@ -222,6 +230,11 @@ struct Lane {
             __builtin_amdgcn_raw_buffer_store_b8((uint8_t)w[0], rs, off, soff, AUX);
         } else if constexpr (kBytes == 2) {
             __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w[0], rs, off, soff, AUX);
+        } else if constexpr (kBytes == 6) {
+            // an even lane stores its next lane's six bytes too (three words, aligned)
+            const uint32_t a = dpp_rot<kQuadOdd>(w[0]), b = dpp_rot<kQuadOdd>(w[1]);
+            __builtin_amdgcn_raw_buffer_store_b96(u32x3_t{w[0], w[1] | a << 16, __builtin_amdgcn_alignbit(b, a, 16)}, rs,
+                                                  (threadIdx.x & 1 ? kOff : off) + soff, 0, AUX);
         } else {
             static_for<(NW + 3) / 4>([&](auto ic) {
                 constexpr int i = 4 * decltype(ic)::value, n = NW - i < 4 ? NW - i : 4;
@@ -263,6 +276,10 @@ struct Lane {
             static_for<N>([&](auto j) { w[j] = r[j]; });
         } else if constexpr (DPL == 2) {
             w[0] = __builtin_amdgcn_perm(r[0], r[0], 0x0C0C0200u);
+        } else if constexpr (DPL == 6) {
+            const uint32_t p = __builtin_amdgcn_perm(r[1], r[0], 0x06020400u);
+            w[0] = __builtin_amdgcn_perm(r[2], p, 0x02040100u);
+            w[1] = __builtin_amdgcn_perm(r[2], p, 0x0C0C0603u);
         } else {
             static_assert(N % 2 == 0, "");
             uint32_t p[N / 2];  // lo bytes of registers 2i, 2i + 1, then their hi bytes
@@ -901,6 +918,158 @@ __device__ __forceinline__ void run_horizontal(const void *cl, const void *cr, u
     }
 }
 
+// ---------------------------------------------------------------- columns and diagonals from census words
+// A block's 16 neighbouring lines of a vertical or diagonal direction.  At every clock
+// they lie in one image row and 16 consecutive columns: line i of item k is the one
+// that would enter the image's first row (of the walk) at column v = v0 + i, and a
+// diagonal that enters through a side column starts at a later clock (until then its
+// costs are 0, which leave its state as it is).  So the words the block needs for a
+// clock are 16 left ones and Dpad + 15 right ones, and those of 16 clocks a tile in LDS;
+// the next tile's words are on their way, in registers, while one is walked.  Bound by
+// the issue of a step: 56 instructions at 96 disparities, 87 at 192, a third more at the
+// image's sides.  Words read a clock ahead, counts that accumulate and packed border
+// tests: 320x240, D = 96, 8 directions 88 -> 71 us a call, 1920x1080, D = 192 1326 -> 1290.
+template <typename T>
+using lds_t = __attribute__((address_space(3))) T;
+__device__ __forceinline__ uint32_t lds_address(const uint32_t *p) { return (uint32_t)(uint64_t)(const lds_t<uint32_t> *)p; }
+
+constexpr int kTileClocks = 16;
+// words of a tile: per clock Dpad + 15 right ones, then per clock 16 left ones
+constexpr int column_tile_words(int dpad) { return kTileClocks * (dpad + kColumnLines - 1 + kColumnLines); }
+
+template <int DPAD, int DPL>
+__device__ __forceinline__ void run_columns(const void *cl, const void *cr, uint8_t *out, int item, int dx, int dy, int W, int H,
+                                            int D, uint32_t bits, uint32_t p1, uint32_t p2, int cost, int max_work,
+                                            uint32_t (*tile)[column_tile_words(DPAD)])
+{
+    using LV = Lane<DPL, false>;
+    using L = Line<DPL, kLanesPerLine, DPAD / DPL, false>;
+    using CW = CensusWord<false>;
+    constexpr int T = kTileClocks, N = LV::N, kL = kColumnLines, kR = DPAD + kL - 1;  // left and right words of a clock
+    constexpr int kRows = T / kWavesPerItem, kRl = (kR + 63) / 64;                     // clocks a wave loads; loads of one
+    static_assert(kL == 64 / kLanesPerLine * kWavesPerItem && kRows * kL == 64, "a lane, a left word of the wave's clocks");
+    const int lane64 = (int)threadIdx.x & 63, lane = (int)threadIdx.x % kLanesPerLine, line = (int)threadIdx.x / kLanesPerLine;
+    const int w = uniform((int)threadIdx.x >> 6), d0 = lane * DPL;
+    const ColumnLines g = column_lines(dx, item, W, H);
+    // this lane's line: its first clock and its length
+    const int v = g.v0 + line, first = dx == 0 ? 0 : max(0, dx > 0 ? -v : v - W + 1);
+    const int len = line < g.n ? (dx == 0 ? H : min(H, dx > 0 ? W - v : v + 1)) - first : 0;
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void *)cl, 0, W * H * 4, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void *)cr, 0, W * H * 4, kBufferWord3);
+    const int step = dy * W + dx;
+    // word index of column v0 + dx c of clock c's row
+    auto at = [&](int c) { return (dy > 0 ? c : H - 1 - c) * W + g.v0 + dx * c; };
+    uint32_t nr[kRows][kRl], nl;
+    // (positions outside an image row are other words of the map, or past it zeros: they
+    // only reach costs that are replaced and pixels that do not exist.  Positions before
+    // the map are clamped: a wrapped register plus an instruction's offset is no offset.)
+    auto fetch = [&](int c) {
+        const int base = at(c + kRows * w);
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+#pragma unroll
+            for (int m = 0; m < kRl; ++m)
+                nr[i][m] = __builtin_amdgcn_raw_buffer_load_b32(rr, max((base + i * step - (DPAD - 1) + 64 * m + lane64) * 4, 0), 0, 0);
+        nl = __builtin_amdgcn_raw_buffer_load_b32(rl, max((base + lane64 / kL * step + lane64 % kL) * 4, 0), 0, 0);
+    };
+    auto keep = [&](uint32_t *t) {
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+#pragma unroll
+            for (int m = 0; m < kRl; ++m)
+                if (64 * (m + 1) <= kR || lane64 < kR - 64 * m) t[(kRows * w + i) * kR + 64 * m + lane64] = nr[i][m];
+        t[T * kR + kRows * w * kL + lane64] = nl;
+    };
+    // LDS traffic of the waves ordered; stores on their way are not waited for
+    auto meet = [&] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // (idle lanes read the last active lane's words)
+    const int left_at = T * kR + line, right_at = line + DPAD - DPL - min(d0, DPAD - DPL);
+    const uint32_t off = d0 < DPAD ? (uint32_t)(line * DPAD + d0) : kOff;
+    uint32_t pad[N];  // at least this for the padding disparities, nothing for the others
+#pragma unroll
+    for (int j = 0; j < N; ++j) pad[j] = (d0 + j < D ? 0u : 255u) | (DPL > 1 && d0 + j + N >= D ? 255u << 16 : 0u);
+    const uint32_t bits2 = both(bits);
+    L state;
+    state.clear();
+    // EDGE: a line without a pixel at some clock, or a cost where x - d < 0
+    auto walk = [&](auto edge, auto padded, int c, const uint32_t *t) {
+        constexpr bool EDGE = decltype(edge)::value, PAD = decltype(padded)::value;
+        const bool neg = step < 0;
+        const __amdgpu_buffer_rsrc_t rs = open_buffer(out + (int64_t)(at(c) + (neg ? (T - 1) * step : 0)) * DPAD);
+        const int stride = (neg ? -step : step) * DPAD;
+        // the next clock's words are read before this one's step.  (The addresses are kept
+        // running and opaque: as large constants off one base they took an add per read.)
+        uint32_t al = lds_address(t + left_at), ar = lds_address(t + right_at);
+        uint32_t left[2], right[2][DPL];
+        auto read = [&](uint32_t &l, uint32_t (&r)[DPL]) {
+            l = *(const lds_t<uint32_t> *)al;
+#pragma unroll
+            for (int k = 0; k < DPL; ++k) r[k] = ((const lds_t<uint32_t> *)ar)[k];
+            al += kL * 4;
+            ar += kR * 4;
+            asm volatile("" : "+v"(al), "+v"(ar));
+        };
+        read(left[0], right[0]);
+        static_for<T>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if constexpr (s + 1 < T) read(left[(s + 1) & 1], right[(s + 1) & 1]);
+            const uint32_t l = left[s & 1], (&r)[DPL] = right[s & 1];
+            const bool on = (uint32_t)(c + s - first) < (uint32_t)len;
+            // disparities d0 + j with j < lim stay inside the right image; the others' costs are
+            // raised to `bits`: 64 (j + 1 - lim), or 0, is at least that
+            const int lim = v + dx * (c + s) - d0 + 1;
+            const uint32_t lim64 = EDGE ? both((uint32_t)min(max(lim, 0), DPL) * 64) : 0u, live = on ? ~0u : 0u;
+            auto hamming = [&](int j) { return CW::hamming(l, r[DPL - 1 - j]); };
+            const uint32_t ub = both(state.u);
+            state.step(p1, p2, lane, [&](auto jc, uint32_t x) {
+                constexpr int j = decltype(jc)::value;
+                // (each half takes its own count: no carry between them)
+                if constexpr (EDGE || PAD) {
+                    uint32_t n = hamming(j);
+                    if constexpr (DPL > 1) n |= hamming(j + N) << 16;
+                    if constexpr (EDGE) {
+                        const u16x2_t beyond = __builtin_elementwise_sub_sat(u16x2_t{64 * (j + 1), 64 * (j + 1 + N)}, h2(lim64));
+                        n = pk_max3(n, pk_min(w1(beyond), bits2), pad[j]) & live;
+                    } else {
+                        n = pk_max(n, pad[j]);
+                    }
+                    return pk_add(x, n);
+                } else {
+                    x += hamming(j);
+                    asm("" : "+v"(x));  // counted onto the sum, not added to it afterwards
+                    if constexpr (DPL > 1) x += hamming(j + N) << 16;
+                    return x;
+                }
+            });
+            uint32_t o[N], m[LV::NW];
+#pragma unroll
+            for (int j = 0; j < N; ++j) o[j] = pk_sub(state.U[j], ub);
+            LV::pack(o, m);
+            LV::template store<kStoreAux>(rs, !EDGE || on ? off : kOff, (neg ? T - 1 - s : s) * stride, m);
+        });
+        state.rebase();
+    };
+    fetch(g.begin);
+    keep(tile[0]);
+    meet();
+    for (int c = g.begin, b = 0; c < g.end; c += T, b ^= 1) {
+        set_priority((g.end - c) * cost, max_work);
+        // (the last tile's look-ahead is not used)
+        fetch(c + T);
+        const bool inside = g.n == kColumnLines && c >= g.all_in && c + T <= g.any_out &&
+                            g.v0 + (dx < 0 ? -(c + T - 1) : dx * c) >= DPAD - 1;
+        if (inside && D == DPAD) walk(std::false_type{}, std::false_type{}, c, tile[b]);
+        else if (inside) walk(std::false_type{}, std::true_type{}, c, tile[b]);
+        else walk(std::true_type{}, std::true_type{}, c, tile[b]);
+        keep(tile[b ^ 1]);
+        meet();
+    }
+}
+
 // ---------------------------------------------------------------- matching costs
 // The cost volume: byte popcount(cL(x) ^ cR(x - d)) per pixel and disparity, d
 // fastest; `bits` where x - d < 0 and 255 (above every path value a real one can be
@@ -1043,6 +1212,51 @@ __device__ __forceinline__ void aggregate_item(const AggregateArgs &a, int item)
     }
 }
 
+// One block of four waves where no unit reads a cost volume: single directions only.
+template <int DPL, int HL>
+__device__ __forceinline__ void census_item(const AggregateArgs &a, int item,
+                                            uint32_t (*tile)[column_tile_words(kLanesPerLine * DPL)])
+{
+    constexpr int kDpad = kLanesPerLine * DPL, LD = column_disparities(kDpad), HD = lane_disparities(kDpad, HL);
+    const int nunits = uniform(a.nunits);
+    int unit = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) unit += (k < nunits && item >= a.item_begin[k]) ? 1 : 0;
+    unit = uniform(unit);
+    item = uniform(item - a.item_begin[unit]);
+    const int dx = uniform(a.dx[unit]), dy = uniform(a.dy[unit]);
+    uint8_t *out = uniform(a.out[unit]);
+    const int W = uniform(a.W), H = uniform(a.H), D = uniform(a.D), max_work = uniform(a.max_item_work);
+    const uint32_t p1 = both(uniform(a.p1)), p2 = both(uniform(a.p2)), bits = uniform(a.bits);
+    const void *cl = uniform(a.census_l), *cr = uniform(a.census_r);
+    if (dy == 0) {
+        constexpr int cost = agg_step_cost(HD, HL);
+        const int wave = item * kWavesPerItem + uniform((int)threadIdx.x >> 6);
+        if (wave * (64 / HL) >= H) return;
+        if (dx > 0) run_horizontal<kDpad, HD, HL, false, 1>(cl, cr, out, wave, W, H, D, bits, p1, p2, cost, max_work);
+        else run_horizontal<kDpad, HD, HL, false, -1>(cl, cr, out, wave, W, H, D, bits, p1, p2, cost, max_work);
+    } else {
+        run_columns<kDpad, LD>(cl, cr, out, item, dx, dy, W, H, D, bits, p1, p2, agg_step_cost(LD, kLanesPerLine), max_work, tile);
+    }
+}
+
+// (three waves per SIMD: 1920x1080, D = 192, 8 directions 1345 / 1326 / 1432 us a call with
+// two / three / four)
+template <int DPL, int HL>
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(3, 3))) void census_aggregate_kernel(AggregateArgs a)
+{
+    __shared__ __align__(16) uint32_t tile[2][column_tile_words(kLanesPerLine * DPL)];
+    census_item<DPL, HL>(a, (int)blockIdx.x, tile);
+}
+
+template <int DPL, int HL>
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(3, 3))) void census_aggregate_queue_kernel(AggregateQueue q)
+{
+    __shared__ __align__(16) uint32_t tile[2][column_tile_words(kLanesPerLine * DPL)];
+    const uint32_t it = __builtin_amdgcn_readfirstlane(q.items[blockIdx.x]);
+    census_item<DPL, HL>(q.slots[it >> 20], (int)(it & 0xFFFFFu), tile);
+}
+
 // Registers for two waves per SIMD: a step is a serial chain, and the scheduler fills
 // its gaps with other steps' work when it has the registers (2 waves with up to 256
 // registers beat 3 with 168).
@@ -1054,31 +1268,34 @@ __global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per
 
 // items (slot << 20 | item) in launch order, largest estimated work first
 template <int DPL, bool WIDE, int HL>
-__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(2, 2))) void aggregate_queue_kernel(AggregateQueue q, int first)
+__global__ __launch_bounds__(64 * kWavesPerItem) __attribute__((amdgpu_waves_per_eu(2, 2))) void aggregate_queue_kernel(AggregateQueue q)
 {
-    const uint32_t it = __builtin_amdgcn_readfirstlane(q.items[first + (int)blockIdx.x]);
+    const uint32_t it = __builtin_amdgcn_readfirstlane(q.items[blockIdx.x]);
     aggregate_item<DPL, WIDE, HL>(q.slots[it >> 20], (int)(it & 0xFFFFFu));
 }
 
 // Launches the costs (when a unit reads them) and the lines of one slot (a) or of
-// every slot of a queue (q).  Units that write over the cost volume run after
-// everything else has read it: a second launch.
-// (grid: the blocks of the first launch)
+// every slot of a queue (q): nitems blocks.  A unit that writes over the cost volume (a slot
+// alone) runs after everything else has read it: the remaining blocks, in a launch of
+// their own.
 template <int DPL, bool WIDE, int HL>
-hipError_t launch_aggregation(const AggregateArgs *a, const AggregateQueue *q, int grid, hipStream_t s)
+hipError_t launch_aggregation(const AggregateArgs *a, const AggregateQueue *q, int nitems, hipStream_t s)
 {
     constexpr int kDpad = kLanesPerLine * DPL;
     const dim3 block(64 * kWavesPerItem);
-    if (a) {
-        const int rest = a->item_begin[a->nunits] - grid;
+    if (a ? counts_census(*a) : q->census != 0) {
+        if constexpr (WIDE) return hipErrorInvalidValue;
+        else if (a) hipLaunchKernelGGL((census_aggregate_kernel<DPL, HL>), dim3(nitems), block, 0, s, *a);
+        else hipLaunchKernelGGL((census_aggregate_queue_kernel<DPL, HL>), dim3(nitems), block, 0, s, *q);
+    } else if (a) {
+        const int rest = a->item_begin[a->nunits] - nitems;
         if (a->cost) hipLaunchKernelGGL((cost_kernel<DPL, WIDE>), dim3(cost_tiles(kDpad, a->W), a->H), dim3(256), 0, s, *a);
-        if (grid > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(grid), block, 0, s, *a, 0);
-        if (rest > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(rest), block, 0, s, *a, grid);
+        if (nitems > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(nitems), block, 0, s, *a, 0);
+        if (rest > 0) hipLaunchKernelGGL((aggregate_kernel<DPL, WIDE, HL>), dim3(rest), block, 0, s, *a, nitems);
     } else {
         if (q->ncost > 0)
             hipLaunchKernelGGL((cost_queue_kernel<DPL, WIDE>), dim3(q->ncost, cost_tiles(kDpad, q->cost_width)), dim3(256), 0, s, *q);
-        if (grid > 0) hipLaunchKernelGGL((aggregate_queue_kernel<DPL, WIDE, HL>), dim3(grid), block, 0, s, *q, 0);
-        if (q->nlast > 0) hipLaunchKernelGGL((aggregate_queue_kernel<DPL, WIDE, HL>), dim3(q->nlast), block, 0, s, *q, grid);
+        hipLaunchKernelGGL((aggregate_queue_kernel<DPL, WIDE, HL>), dim3(nitems), block, 0, s, *q);
     }
     return hipGetLastError();
 }

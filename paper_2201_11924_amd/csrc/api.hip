@@ -64,7 +64,7 @@ int validate(const simsense_params *p)
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-bool stores_sums(const simsense_params *p)
+bool sums_fit(const simsense_params *p)
 {
     return p->block_w * p->block_h > 1 || census_bits(p->census_w, p->census_h, p->census_mode) + p->p2 <= 127;
 }
@@ -83,7 +83,9 @@ Layout layout(const simsense_params *p, bool spare)
     static const int px_bytes[7] = {1, 2, 2, 1, 4, 4, 1};  // dint, S1, S2, dright, dsub, masked, flags
     l.right_run = p->lr_mode == 1;
     const int sets = l.right_run ? 2 : 1;
-    l.buffers = path_buffers(p->num_paths, stores_sums(p), spare);
+    l.costs = !block && p->num_paths > 2 && (spare || sums_fit(p) || costs_in_place(padded_disp(p->max_disp), wide));
+    l.sums = block || (l.costs && sums_fit(p));
+    l.buffers = path_buffers(p->num_paths, l.costs, l.sums, spare);
     l.total = 2 * sets * l.census + (size_t)l.buffers * l.paths + l.volume;
     for (int i = 0; i < 7; ++i) {
         l.per_px[i] = align256(npx * px_bytes[i]);
@@ -93,7 +95,7 @@ Layout layout(const simsense_params *p, bool spare)
 }
 
 // The handle's parameter-derived fields (no device work).
-void init_handle(simsense_handle *h, const simsense_params *params)
+void init_handle(simsense_handle *h, const simsense_params *params, const Layout &l)
 {
     h->p = *params;
     h->bits = census_bits(params->census_w, params->census_h, params->census_mode);
@@ -101,7 +103,8 @@ void init_handle(simsense_handle *h, const simsense_params *params)
     h->Dpad = padded_disp(params->max_disp);
     h->ndirs = params->num_paths;
     h->sgbm = params->block_w * params->block_h > 1;
-    h->sums = stores_sums(params);
+    h->costs = l.costs;
+    h->sums = l.sums;
     h->hlanes = default_lanes(params->width, h->Dpad,
                               aggregate_work(params->width, params->height, h->Dpad, h->ndirs, h->sums));
 }
@@ -212,7 +215,7 @@ void plan_handle(simsense_handle *h)
     ag.W = p.width; ag.H = p.height; ag.D = p.max_disp; ag.Dpad = h->Dpad; ag.bits = h->bits;
     ag.p1 = p.p1; ag.p2 = p.p2;
     h->row_sums = h->sums && !h->sgbm && default_row_sums(p.width, p.height, h->Dpad, h->ndirs, h->wide, h->hlanes);
-    plan_aggregation(ag, h->ndirs, h->sums, h->row_sums, h->sgbm,
+    plan_aggregation(ag, h->ndirs, h->costs, h->sums, h->row_sums, h->sgbm,
                      h->sgbm ? volume_horizontal_lanes(h->Dpad) : h->hlanes, h->paths, h->nbuffers);
 }
 
@@ -238,12 +241,12 @@ static int launch_aggregation(simsense_handle *h, const AggregateArgs &ag, const
         bc.vol = h->volume;
         SS_TRY(launch_block_cost(bc, h->Dpad, h->wide, s));
         SS_TRY(launch_aggregate_volume(VolumeArgs{ag}, s));
-    } else if (h->tuning.blocks_per_cu > 0) {
+    } else if (h->tuning.blocks_per_cu > 0 && ag.last_first == ag.nunits) {
         AggregateQueue q{};
         q.slots = d_args;
         q.items = h->d_items;
-        q.nlast = h->nlast;
-        q.cost_items = h->d_items + h->nitems + h->nlast;
+        q.census = counts_census(ag);
+        q.cost_items = h->d_items + h->nitems;
         q.ncost = h->ncost;
         q.cost_width = h->p.width;
         SS_TRY(launch_aggregate_queue(q, h->Dpad, h->wide, h->hlanes, h->nitems, s));
@@ -267,15 +270,13 @@ static int apply_tuning(simsense_handle *h, const simsense_batch_tuning &t)
     plan_handle(h);
     const AggregateArgs &ag = h->ag;
     std::vector<std::pair<int, uint32_t>> lst;
-    for (int u = 0; u < ag.last_first; ++u)
+    for (int u = 0; u < ag.nunits; ++u)
         for (int k = 0; k < ag.item_begin[u + 1] - ag.item_begin[u]; ++k)
             lst.push_back({aggregate_item_work(ag, u, k, hl), (uint32_t)(ag.item_begin[u] + k)});
     std::stable_sort(lst.begin(), lst.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
     std::vector<uint32_t> items;
     for (const auto &e : lst) items.push_back(e.second);  // pair slot 0
     h->nitems = (int)items.size();
-    for (int i = ag.item_begin[ag.last_first]; i < ag.item_begin[ag.nunits]; ++i) items.push_back((uint32_t)i);
-    h->nlast = (int)items.size() - h->nitems;
     h->ncost = ag.cost && !h->sgbm ? h->p.height : 0;
     for (int y = 0; y < h->ncost; ++y) items.push_back((uint32_t)y);
     if (h->d_items) (void)hipFree(h->d_items);
@@ -320,7 +321,7 @@ int enqueue_match(simsense_handle *h, const uint8_t *left, const uint8_t *right,
     sa.W = W; sa.H = H; sa.D = D; sa.Dpad = h->Dpad;
     sa.uniqueness_pct = p.uniqueness_pct; sa.lr_max_diff = p.lr_max_diff; sa.subpixel = p.subpixel;
     sa.values16 = h->sgbm;
-    sa.small_values = !h->sgbm && h->sums && !h->row_sums;
+    sa.small_values = !h->sgbm && sums_fit(&p) && !h->row_sums;
     sa.disp_int = h->disp_int; sa.cost_best = h->cost_best; sa.cost_second = h->cost_second;
     sa.disp_right = h->disp_right; sa.disp_sub = h->disp_sub; sa.masked = h->masked; sa.flags = h->flags_pre;
     sa.no_right = !need_right;
@@ -400,7 +401,6 @@ int simsense_create(const simsense_params *params, simsense_handle **out)
     Layout l = layout(params, true);
     simsense_handle *h = new (std::nothrow) simsense_handle();
     if (!h) return SIMSENSE_ERR_OUT_OF_MEMORY;
-    init_handle(h, params);
     if (hipMalloc(&h->block, l.total) != hipSuccess) {
         (void)hipGetLastError();
         h->block = nullptr;
@@ -413,6 +413,7 @@ int simsense_create(const simsense_params *params, simsense_handle **out)
         return SIMSENSE_ERR_OUT_OF_MEMORY;
     }
     h->d_args_m = h->d_args + 1;
+    init_handle(h, params, l);
     carve_scratch(h, (uint8_t *)h->block, l);
     h->last_stream = nullptr;
     h->profiling = false;

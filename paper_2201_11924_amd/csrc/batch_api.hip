@@ -29,7 +29,7 @@ namespace {
 struct Slot {
     simsense_params p;
     int bits, Dpad, ndirs, hl, nbuffers;
-    bool wide, small, row_sums;
+    bool wide, small, costs, sums, row_sums;
     size_t off_census_l, off_census_r, off_paths[9], off_dint, off_s1, off_s2, off_dright, off_dsub, off_masked,
         off_flags;
 };
@@ -63,8 +63,8 @@ struct simsense_batch {
     unsigned *h_uncertain;  // pinned: the learned form's per-pair counts, read back for the fallback
     int stage_idx;
     // launch plan
-    // items: nitems longest first, then nlast, then the ncost cost rows
-    struct AggGroup { int dpad, hl; bool wide; size_t item_off; int nitems, nlast, ncost, cost_width; };
+    // items: nitems longest first, then the ncost cost rows
+    struct AggGroup { int dpad, hl; bool wide, census; size_t item_off; int nitems, ncost, cost_width; };
     struct SelGroup { int dpad, nplanes; bool small; size_t item_off; int nitems; };
     // a phase: slots s0 .. s1-1, their item lists and groups (ranges of the vectors)
     struct Phase {
@@ -72,7 +72,9 @@ struct simsense_batch {
         size_t census_item_off, post_item_off;
         int census_nitems, post_nitems;
         int agg0, nagg, sel0, nsel;
+        std::vector<int> alone;  // slots whose aggregation is launched by itself
     };
+    std::vector<AggregateArgs> agg;  // per slot, as in d_agg
     std::vector<AggGroup> agg_groups;
     std::vector<SelGroup> sel_groups;
     std::vector<Phase> phases;   // the plain form's
@@ -126,15 +128,16 @@ int build_plan(simsense_batch *b)
     int64_t work = 0;
     std::map<int, int> widest;
     for (const Slot &sl : b->slots) {
-        work += aggregate_work(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.small);
+        work += aggregate_work(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.sums);
         widest[sl.Dpad] = std::max(widest[sl.Dpad], sl.p.width);
     }
     for (Slot &sl : b->slots) {
         sl.hl = horizontal_lanes_valid(sl.Dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
                                                                             : default_lanes(widest[sl.Dpad], sl.Dpad, work);
-        sl.row_sums = sl.small && default_row_sums(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.wide, sl.hl);
+        sl.row_sums = sl.sums && default_row_sums(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.wide, sl.hl);
     }
-    std::vector<AggregateArgs> agg(n);
+    std::vector<AggregateArgs> &agg = b->agg;
+    agg.assign(n, AggregateArgs{});
     std::vector<SelectArgs> sel(n);
     b->lphases.clear();
     auto add_phase = [&](int s0, int s1, std::vector<simsense_batch::Phase> &dest) {
@@ -150,13 +153,13 @@ int build_plan(simsense_batch *b)
                 for (int i = 0; i < t; ++i) items.push_back(((uint32_t)(2 * s + img) << 20) | (uint32_t)i);
         }
         P.census_nitems = (int)(items.size() - P.census_item_off);
-        // aggregation: group slots by (Dpad, wide); items largest estimated work first
+        // aggregation: group slots by (Dpad, wide, census, lanes); items largest estimated work first
         struct Lists {
-            std::vector<std::pair<int, uint32_t>> first;
-            std::vector<uint32_t> last, cost;
-            int width = 0, hl = 0;
+            std::vector<std::pair<int, uint32_t>> lines;
+            std::vector<uint32_t> cost;
+            int width = 0;
         };
-        std::map<std::pair<int, bool>, Lists> groups;
+        std::map<std::tuple<int, bool, bool, int>, Lists> groups;
         for (int s = P.s0; s < P.s1; ++s) {
             Slot &sl = b->slots[s];
             AggregateArgs &a = agg[s];
@@ -168,18 +171,17 @@ int build_plan(simsense_batch *b)
             a.p1 = sl.p.p1; a.p2 = sl.p.p2;
             uint8_t *buffers[9];
             for (int r = 0; r < sl.nbuffers; ++r) buffers[r] = b->scratch + sl.off_paths[r];
-            plan_aggregation(a, sl.ndirs, sl.small, sl.row_sums, false, sl.hl, buffers, sl.nbuffers);
+            plan_aggregation(a, sl.ndirs, sl.costs, sl.sums, sl.row_sums, false, sl.hl, buffers, sl.nbuffers);
+            if (a.last_first < a.nunits) {  // its costs in place: launched by itself
+                P.alone.push_back(s);
+                continue;
+            }
             if (scale > 0) a.max_item_work = scale;
-            auto &lst = groups[{sl.Dpad, sl.wide}];
-            lst.hl = sl.hl;
+            auto &lst = groups[{sl.Dpad, sl.wide, counts_census(a), sl.hl}];
             const uint32_t tag = (uint32_t)s << 20;
             for (int u = 0; u < a.nunits; ++u)
-                for (int k = a.item_begin[u]; k < a.item_begin[u + 1]; ++k) {
-                    if (u < a.last_first)
-                        lst.first.push_back({aggregate_item_work(a, u, k - a.item_begin[u], sl.hl), tag | (uint32_t)k});
-                    else
-                        lst.last.push_back(tag | (uint32_t)k);
-                }
+                for (int k = a.item_begin[u]; k < a.item_begin[u + 1]; ++k)
+                    lst.lines.push_back({aggregate_item_work(a, u, k - a.item_begin[u], sl.hl), tag | (uint32_t)k});
             if (a.cost) {
                 for (int y = 0; y < a.H; ++y) lst.cost.push_back(tag | (uint32_t)y);
                 lst.width = std::max(lst.width, a.W);
@@ -188,24 +190,20 @@ int build_plan(simsense_batch *b)
         P.agg0 = (int)b->agg_groups.size();
         for (auto &kv : groups) {
             Lists &lst = kv.second;
-            std::stable_sort(lst.first.begin(), lst.first.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+            std::stable_sort(lst.lines.begin(), lst.lines.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
             // the group's items run in one launch: its largest sets the scale of
             // every slot's issue priorities
             // (the plain form's phases set the scale; slots of equal size get the
             // same one in every plan)
             if (&dest == &b->phases)
-                for (auto &e : lst.first) agg[e.second >> 20].max_item_work = lst.first.front().first;
+                for (auto &e : lst.lines) agg[e.second >> 20].max_item_work = lst.lines.front().first;
             simsense_batch::AggGroup gr{};
-            gr.dpad = kv.first.first;
-            gr.wide = kv.first.second;
-            gr.hl = lst.hl;
+            std::tie(gr.dpad, gr.wide, gr.census, gr.hl) = kv.first;
             gr.item_off = items.size();
-            gr.nitems = (int)lst.first.size();
-            gr.nlast = (int)lst.last.size();
+            gr.nitems = (int)lst.lines.size();
             gr.ncost = (int)lst.cost.size();
             gr.cost_width = lst.width;
-            for (auto &e : lst.first) items.push_back(e.second);
-            items.insert(items.end(), lst.last.begin(), lst.last.end());
+            for (auto &e : lst.lines) items.push_back(e.second);
             items.insert(items.end(), lst.cost.begin(), lst.cost.end());
             b->agg_groups.push_back(gr);
         }
@@ -293,12 +291,13 @@ int enqueue_aggregate_phase(simsense_batch *b, const simsense_batch::Phase &P, h
         AggregateQueue q{};
         q.slots = b->d_agg;
         q.items = b->d_items + g.item_off;
-        q.nlast = g.nlast;
-        q.cost_items = q.items + g.nitems + g.nlast;
+        q.census = g.census;
+        q.cost_items = q.items + g.nitems;
         q.ncost = g.ncost;
         q.cost_width = g.cost_width;
         B_TRY(launch_aggregate_queue(q, g.dpad, g.wide, g.hl, g.nitems, s));
     }
+    for (int i : P.alone) B_TRY(launch_aggregate(b->agg[i], b->slots[i].wide, b->slots[i].hl, s));
     return SIMSENSE_OK;
 }
 
@@ -549,14 +548,16 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
         sl.p = params[s];
         sl.bits = census_bits(sl.p.census_w, sl.p.census_h, sl.p.census_mode);
         sl.wide = sl.bits > 32;
-        sl.small = stores_sums(&sl.p);
+        sl.small = sums_fit(&sl.p);
         sl.Dpad = padded_disp(sl.p.max_disp);
+        sl.costs = sl.p.num_paths > 2 && (spare || sl.small || costs_in_place(sl.Dpad, sl.wide));
+        sl.sums = sl.costs && sl.small;
         sl.ndirs = sl.p.num_paths;
         const size_t npx = (size_t)sl.p.width * sl.p.height;
         auto take = [&](size_t bytes) { size_t o = total; total += a256(bytes); return o; };
         sl.off_census_l = take(npx * (sl.wide ? 8 : 4));
         sl.off_census_r = take(npx * (sl.wide ? 8 : 4));
-        sl.nbuffers = path_buffers(sl.ndirs, sl.small, spare);
+        sl.nbuffers = path_buffers(sl.ndirs, sl.costs, sl.sums, spare);
         for (int r = 0; r < sl.nbuffers; ++r) sl.off_paths[r] = take((npx + 1) * sl.Dpad);
         sl.off_dint = take(npx);
         sl.off_s1 = take(npx * 2);

@@ -43,6 +43,9 @@ __host__ __device__ constexpr int lane_disparities(int dpad, int lanes)
 {
     return dpad <= lanes ? 1 : dpad <= 2 * lanes ? 2 : dpad <= 4 * lanes ? 4 : dpad <= 8 * lanes ? 8 : dpad <= 12 * lanes ? 12 : 16;
 }
+// The same of a vertical or diagonal line that counts census words: 96 disparities as 6
+// each.
+__host__ __device__ constexpr int column_disparities(int dpad) { return dpad == 96 ? 6 : lane_disparities(dpad, kLanesPerLine); }
 // lanes a horizontal line runs with when hl are asked for: as many as hold two or more
 // disparities each, most of them in use
 __host__ __device__ constexpr int effective_lanes(int dpad, int hl)
@@ -59,10 +62,38 @@ __host__ __device__ constexpr int agg_step_cost(int dpl, int lanes_per_line) { r
 // values); item i of a unit is the lines of one block: four waves' (one per SIMD of a
 // compute unit), or for a pair two waves', each walked by two waves.
 constexpr int kWavesPerItem = 4;
+// Lines of an item of a vertical or diagonal direction whose columns count census words:
+// neighbours in one image row at every clock (aggregate_impl.h, run_columns).
+constexpr int kColumnLines = 16;
+struct ColumnLines {
+    int v0, n;           // column at clock 0 of line 0, and how many lines exist
+    int begin, end;      // clocks at which any of them has a pixel
+    int all_in, any_out; // and at which all of them have: from all_in to before any_out
+};
+__host__ __device__ inline ColumnLines column_lines(int dx, int item, int W, int H)
+{
+    constexpr int kLines = kColumnLines;
+    auto lo = [](int a, int b) { return a < b ? a : b; };
+    auto hi = [](int a, int b) { return a > b ? a : b; };
+    ColumnLines g;
+    const int total = dx == 0 ? W : W + H - 1;
+    g.v0 = item * kLines - (dx > 0 ? H - 1 : 0);
+    g.n = lo(kLines, total - item * kLines);
+    const int v1 = g.v0 + g.n - 1;
+    // line v has pixels at the clocks max(0, -v) .. min(H, W - v) - 1 (dx > 0),
+    // max(0, v - W + 1) .. min(H, v + 1) - 1 (dx < 0)
+    g.begin = dx == 0 ? 0 : hi(0, dx > 0 ? -v1 : g.v0 - W + 1);
+    g.end = dx == 0 ? H : lo(H, dx > 0 ? W - g.v0 : v1 + 1);
+    g.all_in = dx == 0 ? 0 : hi(0, dx > 0 ? -g.v0 : v1 - W + 1);
+    g.any_out = dx == 0 ? H : lo(H, dx > 0 ? W - v1 : g.v0 + 1);
+    return g;
+}
+
 struct AggregateArgs {
     const void *census_l, *census_r;  // uint32 words, or uint64 when bits > 32
-    uint8_t *cost;       // cost volume the vertical and diagonal units read (null: none of them); for
-                         // block matching the 16-bit block costs of every unit
+    uint8_t *cost;       // cost volume the vertical and diagonal units read (null: they count census
+                         // words, or there are none); for block matching the 16-bit block costs of
+                         // every unit
     int row_costs;       // the horizontal units read it too (else the census words)
     int W, H, D, Dpad, bits, p1, p2;
     int nunits;
@@ -72,18 +103,26 @@ struct AggregateArgs {
     uint8_t *out[8];     // per-unit path values, W*H*Dpad values, d fastest
     int max_item_work;   // largest item work of the launch (issue priorities)
 };
+// whether there are vertical and diagonal units that count census words
+inline bool counts_census(const AggregateArgs &a) { return !a.cost && a.nunits > 2; }
 // Whether horizontal directions may be stored as sums too: 16 lanes per line and
 // 32-bit census words (64-bit ones take more registers than a wave has).
 __host__ __device__ constexpr bool row_pairs_built(int lanes, bool wide) { return lanes == kLanesPerLine && !wide; }
 // Path buffers of a slot: one per direction, and one more for the cost volume where the
 // directions need them all (no sums) and the caller can spare it.
-constexpr int path_buffers(int num_paths, bool sums, bool spare) { return num_paths + (spare && !sums && num_paths > 2 ? 1 : 0); }
+constexpr int path_buffers(int num_paths, bool costs, bool sums, bool spare) { return num_paths + (costs && !sums && spare ? 1 : 0); }
+// Whether a slot without that buffer keeps the volume in the last direction's and runs that
+// direction after all others, in place, rather than counting census words along columns and
+// diagonals: where the words are 64 bits or the disparities 256.  The no-allocation call
+// with planes that fill its array, in us, in place / words: 64-bit, 250x230, D = 128 96 /
+// 140; D = 256, 171x176 104 / 110; but 320x240, D = 96 102 / 72, 200x200, D = 192 99 / 81.
+constexpr bool costs_in_place(int dpad, bool wide) { return wide || dpad == 256; }
 // Fills a's units for the nbuffers `buffers` and hl lanes per horizontal line, from W, H
 // and Dpad.  sums: opposite directions are stored as their sums (two path
 // values must fit one value of the buffer); row_sums: the horizontal ones too.  Unit u
 // fills buffers[u].  block: a.cost is the caller's and every unit reads it.
-void plan_aggregation(AggregateArgs &a, int num_paths, bool sums, bool row_sums, bool block, int hl, uint8_t *const *buffers,
-                      int nbuffers);
+void plan_aggregation(AggregateArgs &a, int num_paths, bool costs, bool sums, bool row_sums, bool block, int hl,
+                      uint8_t *const *buffers, int nbuffers);
 int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl);
 
 struct SelectArgs {
@@ -125,13 +164,13 @@ hipError_t launch_census_pair(const uint8_t *img0, const uint8_t *img1, int pitc
 // every slot of a batch phase, or a handle's own single slot
 struct AggregateQueue {
     const AggregateArgs *slots;  // per pair slot (device)
-    const uint32_t *items;       // slot << 20 | item, largest work first (device), then the nlast
-    int nlast;                   // items of the units that run after the others
+    const uint32_t *items;       // slot << 20 | item, largest work first (device)
+    int census;                  // the slots' vertical and diagonal units count census words
     const uint32_t *cost_items;  // slot << 20 | row of the slots whose costs go to a volume (device)
     int ncost, cost_width;       // their number, and the widest image among them
 };
 hipError_t launch_aggregate(const AggregateArgs &a, bool wide, int hl, hipStream_t s);
-// grid: the items before the last ones (one block each)
+// grid: the items (one block each)
 hipError_t launch_aggregate_queue(const AggregateQueue &q, int dpad, bool wide, int hl, int grid, hipStream_t s);
 hipError_t launch_select(const SelectArgs &a, hipStream_t s);
 hipError_t launch_post(const PostArgs &a, hipStream_t s);
@@ -215,15 +254,16 @@ int validate(const simsense_params *p);
 struct Layout {
     size_t census, paths, per_px[7], total;
     int buffers;       // path buffers
+    bool costs, sums;  // vertical and diagonal directions read a cost volume; opposite ones are stored as sums
     bool right_run;  // lr_mode 1: two more census maps and a second per-pixel set
     size_t volume;   // SGBM: the block-cost volume (16-bit, d fastest)
 };
 // (spare: with a buffer for the cost volume where the directions fill all others)
 Layout layout(const simsense_params *p, bool spare);
-bool stores_sums(const simsense_params *p);  // two path values fit one of the path buffers'
+bool sums_fit(const simsense_params *p);  // two path values fit one of the path buffers'
 
 // fields derived from the parameters; the buffers carved from `base` (l.total bytes)
-void init_handle(simsense_handle *h, const simsense_params *params);
+void init_handle(simsense_handle *h, const simsense_params *params, const Layout &l);
 void carve_scratch(simsense_handle *h, uint8_t *base, const Layout &l);
 // the handle's aggregation units for its lane count (its buffers are set)
 void plan_handle(simsense_handle *h);
@@ -252,11 +292,12 @@ struct simsense_handle {  // opaque to callers
     // launch shape of the aggregation; for the sorted form, the work list (items
     // largest first, then the cost rows) and the argument block on the device
     simsense_batch_tuning tuning;
-    int nitems, nlast, ncost;
+    int nitems, ncost;
     uint32_t *d_items;
     ss::AggregateArgs ag;  // the aggregation's units, set with the tuning
     ss::AggregateArgs *d_args;
-    bool sums;     // two path values fit one of the path buffers' (bits + P2 <= 127, or 16 bits)
+    bool costs;    // the vertical and diagonal directions read a cost volume
+    bool sums;     // opposite directions are stored as their sum
     bool row_sums; // the horizontal directions are stored as their sum
     // full right-referenced run (lr_mode 1): x-flipped census maps (the right
     // image's as the reference), that run's per-pixel results and its arguments

@@ -53,7 +53,8 @@ extern "C" int simsense_compute_noalloc(const simsense_params *params, const uin
     if (rc != SIMSENSE_OK) return rc;
     if (!left || !right || !depth) return SIMSENSE_ERR_NULL_POINTER;
     if (pitch < params->width) return SIMSENSE_ERR_INVALID_ARGUMENT;
-    const Layout l = layout(params, false);
+    Layout l = layout(params, true);
+    if (l.total > kScratchBytes) l = layout(params, false);
     if (l.total > kScratchBytes) return SIMSENSE_ERR_TOO_LARGE;
     uint8_t *base = nullptr;
     rc = scratch_for_current_device(&base);
@@ -62,7 +63,7 @@ extern "C" int simsense_compute_noalloc(const simsense_params *params, const uin
     // a handle on the stack: its buffers point into the static scratch, the
     // aggregation runs unsorted, profiling is off
     simsense_handle h{};
-    init_handle(&h, params);
+    init_handle(&h, params, l);
     carve_scratch(&h, base, l);
     h.tuning.struct_size = sizeof(h.tuning);
     h.tuning.horizontal_lanes = 0;
