@@ -65,6 +65,15 @@ int default_lanes(int W, int dpad, int64_t total_work)
     return 10 * per_simd >= 16 * row ? 16 : 10 * per_simd >= 5 * row ? 32 : 64;
 }
 
+bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums)
+{
+    if (num_paths == 2) return false;
+    const int64_t volume = (int64_t)W * H * dpad, kMany = 256000000, kFew = 96000000;
+    if (wide || volume <= kFew) return true;
+    if (num_paths == 8) return sums || dpad == 256;
+    return volume <= kMany || (sums && default_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, true)) == kLanesPerLine);
+}
+
 bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl)
 {
     return num_paths > 2 && row_pairs_built(effective_lanes(dpad, hl), wide) && (int64_t)W * H * dpad > (int64_t)256 << 20;
@@ -113,7 +122,7 @@ int aggregate_item_work(const AggregateArgs &a, int unit, int item, int hl)
     }
     for (int l = item * lines; l < std::min(n, (item + 1) * lines); ++l) len = std::max(len, line_length(dx, dy, l, a.W, a.H));
     const int steps = a.pair[unit] ? 3 * len / 2 : len;  // of each wave, in a row
-    return steps * agg_step_cost(lane_disparities(a.Dpad, lanes), lanes);
+    return steps * agg_step_cost(dy == 0 ? row_disparities(a.Dpad, lanes, a.bits > 32) : lane_disparities(a.Dpad, lanes), lanes);
 }
 
 hipError_t launch_aggregate(const AggregateArgs &a, bool wide, int hl, hipStream_t s)

@@ -39,7 +39,8 @@
 // recomputing them from the census words costs 4.7 SIMD cycles more per disparity
 // and step than unpacking a byte.  Costs where x - d < 0 are `bits`, and 255 where
 // d >= D, so the steps need no border case.  Where no buffer is left for the volume they
-// count 32-bit words after all (run_columns).  Horizontal units count the bits of
+// count 32-bit words after all (run_columns), and so they do where the volume is too large
+// for the caches and little is won by it (default_costs).  Horizontal units count the bits of
 // 32-bit census words themselves (a lane's right words slide by one column per step:
 // the pixels of a segment share all but a few), which saves the reads.
 #pragma once
@@ -1160,7 +1161,7 @@ constexpr int sum_steps(int dpl, bool v16) { return v16 && dpl >= 12 ? 4 : 8; }
 template <int DPL, bool WIDE, int HL>
 __device__ __forceinline__ void aggregate_item(const AggregateArgs &a, int item)
 {
-    constexpr int kDpad = kLanesPerLine * DPL, LD = lane_disparities(kDpad, kLanesPerLine), HD = lane_disparities(kDpad, HL);
+    constexpr int kDpad = kLanesPerLine * DPL, LD = lane_disparities(kDpad, kLanesPerLine), HD = row_disparities(kDpad, HL, WIDE);
     const int nunits = uniform(a.nunits);
     int unit = 0;
 #pragma unroll
@@ -1217,7 +1218,7 @@ template <int DPL, int HL>
 __device__ __forceinline__ void census_item(const AggregateArgs &a, int item,
                                             uint32_t (*tile)[column_tile_words(kLanesPerLine * DPL)])
 {
-    constexpr int kDpad = kLanesPerLine * DPL, LD = column_disparities(kDpad), HD = lane_disparities(kDpad, HL);
+    constexpr int kDpad = kLanesPerLine * DPL, LD = column_disparities(kDpad), HD = row_disparities(kDpad, HL, false);
     const int nunits = uniform(a.nunits);
     int unit = 0;
 #pragma unroll

@@ -69,6 +69,12 @@ bool sums_fit(const simsense_params *p)
     return p->block_w * p->block_h > 1 || census_bits(p->census_w, p->census_h, p->census_mode) + p->p2 <= 127;
 }
 
+bool default_costs(const simsense_params *p)
+{
+    return default_costs(p->width, p->height, padded_disp(p->max_disp), p->num_paths,
+                         census_bits(p->census_w, p->census_h, p->census_mode) > 32, sums_fit(p));
+}
+
 Layout layout(const simsense_params *p, bool spare)
 {
     Layout l{};
@@ -83,7 +89,7 @@ Layout layout(const simsense_params *p, bool spare)
     static const int px_bytes[7] = {1, 2, 2, 1, 4, 4, 1};  // dint, S1, S2, dright, dsub, masked, flags
     l.right_run = p->lr_mode == 1;
     const int sets = l.right_run ? 2 : 1;
-    l.costs = !block && p->num_paths > 2 && (spare || sums_fit(p) || costs_in_place(padded_disp(p->max_disp), wide));
+    l.costs = !block && default_costs(p) && (spare || sums_fit(p) || costs_in_place(padded_disp(p->max_disp), wide));
     l.sums = block || (l.costs && sums_fit(p));
     l.buffers = path_buffers(p->num_paths, l.costs, l.sums, spare);
     l.total = 2 * sets * l.census + (size_t)l.buffers * l.paths + l.volume;

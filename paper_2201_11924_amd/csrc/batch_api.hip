@@ -550,7 +550,7 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
         sl.wide = sl.bits > 32;
         sl.small = sums_fit(&sl.p);
         sl.Dpad = padded_disp(sl.p.max_disp);
-        sl.costs = sl.p.num_paths > 2 && (spare || sl.small || costs_in_place(sl.Dpad, sl.wide));
+        sl.costs = default_costs(&sl.p) && (spare || sl.small || costs_in_place(sl.Dpad, sl.wide));
         sl.sums = sl.costs && sl.small;
         sl.ndirs = sl.p.num_paths;
         const size_t npx = (size_t)sl.p.width * sl.p.height;

@@ -31,6 +31,20 @@ int path_lines(int dx, int dy, int W, int H);
 //   16 pairs of 1280x720, 2 paths, with the net: 2805 / 3043 / 3685.
 int default_lanes(int W, int dpad, int64_t total_work);
 int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums);
+// Whether the vertical and diagonal directions read a cost volume by default, rather than
+// count census words.  Each of them reads it once, so a volume beyond the caches costs more
+// than the counting, the sooner the more directions there are and the less is won by it:
+// sums of two directions (sums) save half the planes, 64-bit words (wide) cost twice the
+// counting, and so do 256 disparities of 8 directions.  Whole calls in us, volume / words:
+//   8 directions, no sums: 960x540 D = 128 (66 MB) 272 / 281, D = 192 (100 MB) 414 / 396,
+//   1280x720 D = 128 (118 MB) 461 / 454, 1600x1000 D = 128 (205 MB) 774 / 724, 1539x1041
+//   D = 192 (308 MB) 1479 / 1072; D = 256: 1280x720 888 / 1095, 1920x1080 2220 / 2310;
+//   with sums, 1280x720 D = 128: 405 / 458, 1920x1080 D = 256: 1660 / 2310.
+//   4 directions: 1600x1000 D = 128 (205 MB) 418 / 457, 1920x1080 D = 128 (265 MB) 647 / 557
+//   and with sums 601 / 556, D = 192 (398 MB) 992 / 759 and 873 / 756; with rows as sums too
+//   (below), 2400x1500 D = 96 831 / 882.
+//   64-bit words: 1280x720 D = 128, 8 directions 498 / 938, 1920x1080 D = 192 1803 / 1890.
+bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums);
 // Whether the horizontal directions are stored as sums by default: where the cost volume
 // does not fit the 256 MB last-level cache, so that the aggregation waits for HBM, one
 // buffer less is worth a third walk over the rows (1920x1080, D = 256: whole call 1762 ->
@@ -43,8 +57,15 @@ __host__ __device__ constexpr int lane_disparities(int dpad, int lanes)
 {
     return dpad <= lanes ? 1 : dpad <= 2 * lanes ? 2 : dpad <= 4 * lanes ? 4 : dpad <= 8 * lanes ? 8 : dpad <= 12 * lanes ? 12 : 16;
 }
-// The same of a vertical or diagonal line that counts census words: 96 disparities as 6
-// each.
+// The same of a horizontal line: with 32-bit census words the 32 lanes of 192 disparities
+// hold 6 each, an even lane storing its neighbour's with its own (8 each, with 8 lanes idle,
+// take a third more instructions per step: 1280x720, D = 192, 4 directions 422 -> 403 us a
+// call, 640x480, 8 directions 258 -> 248; three 16-bit stores a lane instead 407, 253).
+__host__ __device__ constexpr int row_disparities(int dpad, int lanes, bool wide)
+{
+    return !wide && dpad == 6 * lanes && lanes == 32 ? 6 : lane_disparities(dpad, lanes);
+}
+// And of a vertical or diagonal line that counts census words: 96 disparities as 6 each.
 __host__ __device__ constexpr int column_disparities(int dpad) { return dpad == 96 ? 6 : lane_disparities(dpad, kLanesPerLine); }
 // lanes a horizontal line runs with when hl are asked for: as many as hold two or more
 // disparities each, most of them in use
@@ -260,7 +281,8 @@ struct Layout {
 };
 // (spare: with a buffer for the cost volume where the directions fill all others)
 Layout layout(const simsense_params *p, bool spare);
-bool sums_fit(const simsense_params *p);  // two path values fit one of the path buffers'
+bool sums_fit(const simsense_params *p);     // two path values fit one of the path buffers'
+bool default_costs(const simsense_params *p);  // (above) for a handle's or a batch slot's parameters
 
 // fields derived from the parameters; the buffers carved from `base` (l.total bytes)
 void init_handle(simsense_handle *h, const simsense_params *params, const Layout &l);
