@@ -68,10 +68,15 @@ int default_lanes(int W, int dpad, int64_t total_work)
 bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums)
 {
     if (num_paths == 2) return false;
-    const int64_t volume = (int64_t)W * H * dpad, kMany = 256000000, kFew = 96000000;
+    const int64_t volume = (int64_t)W * H * dpad, kFew = 96000000, kTall = 192000000, kVast = 400000000;
+    const int64_t kMany = dpad <= 64 ? 160000000 : dpad == 96 ? 190000000 : 228000000;
     if (wide || volume <= kFew) return true;
+    const bool few_columns = H > W && num_paths * W < (volume <= kTall ? 8000 : 5700);
+    if (few_columns && (sums || dpad == 256 || volume <= kVast)) return true;
     if (num_paths == 8) return sums || dpad == 256;
-    return volume <= kMany || (sums && default_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, true)) == kLanesPerLine);
+    if (dpad == 256) return sums || volume <= kVast;
+    return volume <= kMany || (sums && default_row_sums(W, H, dpad, num_paths, wide,
+                                                        default_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, true))));
 }
 
 bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl)

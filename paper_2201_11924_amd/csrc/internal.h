@@ -40,10 +40,21 @@ int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums);
 //   1280x720 D = 128 (118 MB) 461 / 454, 1600x1000 D = 128 (205 MB) 774 / 724, 1539x1041
 //   D = 192 (308 MB) 1479 / 1072; D = 256: 1280x720 888 / 1095, 1920x1080 2220 / 2310;
 //   with sums, 1280x720 D = 128: 405 / 458, 1920x1080 D = 256: 1660 / 2310.
-//   4 directions: 1600x1000 D = 128 (205 MB) 418 / 457, 1920x1080 D = 128 (265 MB) 647 / 557
-//   and with sums 601 / 556, D = 192 (398 MB) 992 / 759 and 873 / 756; with rows as sums too
-//   (below), 2400x1500 D = 96 831 / 882.
+//   4 directions: 1416x1048 D = 128 (190 MB) 0.91 (volume over words), 1755x1046 (235 MB) 1.05,
+//   1439x741 D = 192 (205 MB) 0.94, 1565x782 (235 MB) 1.12, 1821x1086 D = 96 (190 MB) 1.01,
+//   1804x1270 (220 MB) 1.08, 2389x1340 D = 64 (205 MB) 1.21, 2410x1620 (250 MB) 1.31; with
+//   sums 1627x1056 D = 128 (220 MB) 1.05, 1920x1080 (265 MB) 601 / 556 us, D = 192 (398 MB) 873
+//   / 756; with rows as sums too (below), 2400x1500 D = 96 831 / 882.
 //   64-bit words: 1280x720 D = 128, 8 directions 498 / 938, 1920x1080 D = 192 1803 / 1890.
+// Where columns are the longest chains and there are few of them, a launch waits for their
+// steps, which counting makes longer, and not for memory (volume over words, 8 directions,
+// no sums): 397x2051 D = 192 (156 MB) 0.86, 925x1139 D = 128 (135 MB) 0.97, 693x2160 D = 128
+// (192 MB) 0.90, 1693x2826 D = 32 (153 MB) 1.15, 734x1615 D = 192 (228 MB) 1.01, 430x2766
+// (228 MB) 0.89, 762x2892 (423 MB) 1.23; 4 directions: 701x3030
+// D = 128 (272 MB) 0.90, 955x2481 D = 192 (455 MB) 1.26, with sums 805x4164 (644 MB) 0.84.
+// And 4 directions of 256 disparities: 1050x960 (258 MB) 0.96, 1885x818 (395 MB) 1.06,
+// 1605x1541 (633 MB) 1.29, 568x3646 (530 MB) 0.72, with sums 1050x960 0.90, 2032x676 (352 MB)
+// 1.00, 1428x1473 (538 MB) 1.04.
 bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums);
 // Whether the horizontal directions are stored as sums by default: where the cost volume
 // does not fit the 256 MB last-level cache, so that the aggregation waits for HBM, one

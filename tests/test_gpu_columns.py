@@ -75,14 +75,23 @@ def test_room_for_a_volume(nat, W, H, D, paths):  # noqa: F811
     compare(nat, p)
 
 
-# volumes just over and under the sizes from which words are counted (96e6 and 256e6 bytes)
+# volumes about the sizes from which words are counted (96e6 bytes; 4 directions 160e6, 190e6, 228e6)
 @pytest.mark.parametrize("W,H,D,kw", [
     (6100, 1000, 16, {}), (3007, 1000, 30, {}), (1600, 950, 64, {}), (1411, 771, 90, {}), (1411, 708, 96, {}),
     (1300, 580, 128, {}), (1250, 420, 192, {}), (1250, 399, 192, {}), (1249, 421, 179, {}), (62, 8192, 192, {}),
     (8192, 62, 192, {}), (1411, 971, 192, dict(num_paths=4)), (1411, 971, 192, dict(num_paths=4, p2=86)),
-    (1411, 943, 192, dict(num_paths=4, p2=86)), (1050, 960, 256, dict(num_paths=4)),
+    (1411, 943, 192, dict(num_paths=4, p2=86)), (1211, 970, 192, dict(num_paths=4)), (1050, 960, 256, dict(num_paths=4)),
     (2003, 1001, 121, dict(num_paths=4, p2=86))])
 def test_large_volumes(orc, nat, W, H, D, kw):  # noqa: F811
+    check(orc, nat, W, H, D, **dict(dict(p2=200), **kw))
+
+
+# columns longer than rows, about the sizes from which words are counted there (712 and 1000
+# columns, 192e6 bytes), and 4 directions of 256 disparities
+@pytest.mark.parametrize("W,H,D,kw", [
+    (397, 2051, 192, {}), (711, 1650, 192, {}), (713, 1650, 192, {}), (1003, 1100, 128, {}),
+    (700, 1500, 250, dict(num_paths=4)), (1050, 960, 256, dict(num_paths=4, p2=86))])
+def test_long_columns(orc, nat, W, H, D, kw):  # noqa: F811
     check(orc, nat, W, H, D, **dict(dict(p2=200), **kw))
 
 
