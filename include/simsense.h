@@ -397,7 +397,7 @@ int simsense_batch_autotune(simsense_batch *b, const simsense_pair *pairs, int32
 /* Launch shape of one handle's aggregation pass (the results do not depend on
  * it).  Same struct as the batch tuning, with blocks_per_cu 0 meaning line
  * blocks in direction order and 1..8 largest first.  Default: horizontal_lanes 0
- * (by image size, disparities and paths), blocks_per_cu 3.
+ * (by the image's rows and the paths: the more of them, the fewer lanes), blocks_per_cu 3.
  * Synchronous (uploads the work list); returns SIMSENSE_ERR_INVALID_ARGUMENT
  * for values outside those ranges or a lane count that does not divide the
  * padded disparity count. */

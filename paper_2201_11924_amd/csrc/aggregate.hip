@@ -57,12 +57,20 @@ int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums)
     return (int64_t)W * H / 4 * walks / 2 * agg_step_cost(lane_disparities(dpad, kLanesPerLine), kLanesPerLine);
 }
 
-int default_lanes(int W, int dpad, int64_t total_work)
+constexpr int kSimds = 1024;
+
+int launch_lanes(int W, int dpad, int64_t total_work)
 {
-    constexpr int kSimds = 1024;
     const int64_t row = (int64_t)W * agg_step_cost(lane_disparities(dpad, kLanesPerLine), kLanesPerLine);
     const int64_t per_simd = total_work / kSimds;
     return 10 * per_simd >= 16 * row ? 16 : 10 * per_simd >= 5 * row ? 32 : 64;
+}
+
+int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums)
+{
+    if (num_paths == 2 && dpad < 256) return H > kSimds ? 16 : 2 * H > kSimds ? 32 : 64;
+    const int hl = launch_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, sums));
+    return num_paths == 4 && !costs && hl == 32 && H + W / 2 > 2 * kSimds ? 16 : hl;
 }
 
 bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums)
@@ -76,7 +84,7 @@ bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums)
     if (num_paths == 8) return sums || dpad == 256;
     if (dpad == 256) return sums || volume <= kVast;
     return volume <= kMany || (sums && default_row_sums(W, H, dpad, num_paths, wide,
-                                                        default_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, true))));
+                                                        default_lanes(W, H, dpad, num_paths, true, true)));
 }
 
 bool default_row_sums(int W, int H, int dpad, int num_paths, bool wide, int hl)

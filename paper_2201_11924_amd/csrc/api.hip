@@ -111,8 +111,7 @@ void init_handle(simsense_handle *h, const simsense_params *params, const Layout
     h->sgbm = params->block_w * params->block_h > 1;
     h->costs = l.costs;
     h->sums = l.sums;
-    h->hlanes = default_lanes(params->width, h->Dpad,
-                              aggregate_work(params->width, params->height, h->Dpad, h->ndirs, h->sums));
+    h->hlanes = default_lanes(params->width, params->height, h->Dpad, h->ndirs, h->costs, h->sums);
 }
 
 // Points the handle's buffers into one block of scratch laid out by layout().
@@ -271,7 +270,7 @@ static int apply_tuning(simsense_handle *h, const simsense_batch_tuning &t)
     const simsense_params &p = h->p;
     const int hl = h->hlanes = t.horizontal_lanes != 0
                                    ? t.horizontal_lanes
-                                   : default_lanes(p.width, h->Dpad, aggregate_work(p.width, p.height, h->Dpad, h->ndirs, h->sums));
+                                   : default_lanes(p.width, p.height, h->Dpad, h->ndirs, h->costs, h->sums);
     h->tuning = t;
     plan_handle(h);
     const AggregateArgs &ag = h->ag;

@@ -133,7 +133,7 @@ int build_plan(simsense_batch *b)
     }
     for (Slot &sl : b->slots) {
         sl.hl = horizontal_lanes_valid(sl.Dpad, b->tuning.horizontal_lanes) ? b->tuning.horizontal_lanes
-                                                                            : default_lanes(widest[sl.Dpad], sl.Dpad, work);
+                                                                            : launch_lanes(widest[sl.Dpad], sl.Dpad, work);
         sl.row_sums = sl.sums && default_row_sums(sl.p.width, sl.p.height, sl.Dpad, sl.ndirs, sl.wide, sl.hl);
     }
     std::vector<AggregateArgs> &agg = b->agg;

@@ -22,14 +22,26 @@ int census_bits(int cw, int ch, int mode);
 extern const int kPathDx[8];
 extern const int kPathDy[8];
 int path_lines(int dx, int dy, int W, int H);
-// Default lanes per horizontal line of a slot W pixels wide, in a launch of total_work
-// (the sum of aggregate_work over its slots).  More lanes shorten the chain of a row's
-// steps, fewer spend less on the steps' cross-lane part.  Measured aggregation passes,
-// 16 / 32 / 64 lanes, at the launch's work per SIMD over a row's work (16 lanes):
-//   0.23 (640x480, D = 128, 2 paths) 99 / 72 / 65 us;  0.66 (960x540, D = 96, 4) 160 / 122;
-//   1.3 (848x480, D = 128, 8) 169 / 143 / 187;  1.9 (1280x720, D = 128, 8) 271 / 308 / 334;
+// Default lanes per horizontal line of the slots of a batch, the widest with W pixels a row,
+// from its total_work (the sum of aggregate_work over them), and of one pair by the same rule
+// but for the cases below.  More lanes shorten the chain of a row's steps, fewer spend less on
+// the steps' cross-lane part.  Measured aggregation passes, 16 / 32 / 64 lanes, at the work
+// per SIMD over a row's work (for one pair that is H / 8192 times twice the walks: W and the
+// disparities stand in both):
+//   0.66 (960x540, D = 96, 4 paths) 160 / 122 us;  1.3 (848x480, D = 128, 8) 169 / 143 / 187;
+//   1.9 (1280x720, D = 128, 8) 271 / 308 / 334;
 //   16 pairs of 1280x720, 2 paths, with the net: 2805 / 3043 / 3685.
-int default_lanes(int W, int dpad, int64_t total_work);
+int launch_lanes(int W, int dpad, int64_t total_work);
+// One pair: rows alone (2 paths) of up to 192 disparities take the most lanes with which no
+// SIMD has two waves, whole calls: 640x480 D = 128 99 / 72 / 65, 891x596 D = 96 179 / 141 /
+// 159, 154x598 D = 160 64 / 51 / 56, 804x837 D = 96 174 / 140 / 156, 686x1052 D = 192 217 /
+// 226 / 274, 1539x1041 D = 160 570 / 581 / 732, 1812x1307 D = 96 420 / 434 (with 256 the wider
+// forms stay level: 686x871 285 / 219 / 224, 1190x1608 568 / 563 / 658).  4 paths that count
+// census words gain nothing from 32 lanes where the rows' waves and the columns' (H + W / 2)
+// come to more than two per SIMD: 1920x1080 D = 192 (2040) 856 / 757, 1749x1160 (2034) 856 /
+// 770, 1863x1120 (2051) 867 / 925, 2062x1080 (2111) 905 / 989, 2055x1200 D = 128 (2227) 689 /
+// 762, 2379x1250 D = 192 1113 / 1141.
+int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums);
 int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums);
 // Whether the vertical and diagonal directions read a cost volume by default, rather than
 // count census words.  Each of them reads it once, so a volume beyond the caches costs more
