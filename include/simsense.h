@@ -338,7 +338,8 @@ typedef struct simsense_pair {
  *                    16, 32 or 64 (a quarter, half or whole wavefront; fewer where
  *                    that would leave less than two disparities per lane), 0 = the
  *                    default for each disparity range; pairs whose padded
- *                    disparity count it does not divide keep their default.
+ *                    disparity count it does not divide keep their default
+ *                    (65 to 96 disparities: 32 is 64 where that is the default).
  *  blocks_per_cu     1..8.  Kept for callers that set it: the aggregation's blocks
  *                    are taken largest first for every value, and how many are
  *                    resident on a compute unit follows from their registers. */
@@ -387,9 +388,10 @@ int simsense_batch_learned_fallback(simsense_batch *b, simsense_net *net, simsen
 int simsense_batch_set_tuning(simsense_batch *b, const simsense_batch_tuning *t);
 int simsense_batch_get_tuning(const simsense_batch *b, simsense_batch_tuning *t);
 /* Times every tuning candidate (horizontal_lanes in {16, 32, 64} x blocks_per_cu in
- * {1, 2, 3, 4}) over `reps` launches on `pairs`, writes the mean milliseconds of
- * candidate i to ms[i] (host, up to max_candidates) and their number to *count,
- * keeps the fastest and returns it in *best.  Synchronous. */
+ * {1, 2, 3, 4}) over `reps` launches on `pairs`, candidates that launch the same
+ * thing once, writes the mean milliseconds of candidate i to ms[i] (host, up to
+ * max_candidates) and their number to *count, keeps the fastest and returns it in
+ * *best.  Synchronous. */
 int simsense_batch_autotune(simsense_batch *b, const simsense_pair *pairs, int32_t reps,
                             simsense_batch_tuning *best, float *ms, int32_t max_candidates, int32_t *count,
                             void *stream);
@@ -405,9 +407,9 @@ int simsense_set_tuning(simsense_handle *h, const simsense_batch_tuning *t);
 int simsense_get_tuning(const simsense_handle *h, simsense_batch_tuning *t);
 /* Times every candidate (the valid horizontal_lanes of {16, 32, 64} x
  * blocks_per_cu in {0, 1, 2, 3, 4}) over `reps` matching passes (census ..
- * selection) of the given pair, writes the mean milliseconds of candidate i to
- * ms[i] (host, up to max_candidates) and their number to *count, keeps the
- * fastest and returns it in *best.  Synchronous. */
+ * selection) of the given pair, candidates that launch the same thing once, writes
+ * the mean milliseconds of candidate i to ms[i] (host, up to max_candidates) and
+ * their number to *count, keeps the fastest and returns it in *best.  Synchronous. */
 int simsense_autotune(simsense_handle *h, const uint8_t *left, const uint8_t *right, int32_t pitch, int32_t reps,
                       simsense_batch_tuning *best, float *ms, int32_t max_candidates, int32_t *count, void *stream);
 

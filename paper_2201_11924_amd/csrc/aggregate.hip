@@ -73,6 +73,12 @@ int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums)
     return num_paths == 4 && !costs && hl == 32 && H + W / 2 > 2 * kSimds ? 16 : hl;
 }
 
+int chosen_lanes(int asked, int dpad, int by_default)
+{
+    if (asked == 0) return by_default;
+    return dpad == 96 && asked == 32 && by_default == 64 ? 64 : asked;
+}
+
 bool default_costs(int W, int H, int dpad, int num_paths, bool wide, bool sums)
 {
     if (num_paths == 2) return false;

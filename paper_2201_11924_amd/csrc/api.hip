@@ -1,6 +1,7 @@
 // C ABI of the depth library: parameter validation, the handle and its device
 // scratch, and the order in which the passes are enqueued.
 #include <algorithm>
+#include <map>
 #include <new>
 #include <string.h>
 #include <utility>
@@ -268,9 +269,8 @@ static int apply_tuning(simsense_handle *h, const simsense_batch_tuning &t)
 {
     if (t.horizontal_lanes != 0 && !horizontal_lanes_valid(h->Dpad, t.horizontal_lanes)) return SIMSENSE_ERR_INVALID_ARGUMENT;
     const simsense_params &p = h->p;
-    const int hl = h->hlanes = t.horizontal_lanes != 0
-                                   ? t.horizontal_lanes
-                                   : default_lanes(p.width, p.height, h->Dpad, h->ndirs, h->costs, h->sums);
+    const int hl = h->hlanes = chosen_lanes(t.horizontal_lanes, h->Dpad,
+                                            default_lanes(p.width, p.height, h->Dpad, h->ndirs, h->costs, h->sums));
     h->tuning = t;
     plan_handle(h);
     const AggregateArgs &ag = h->ag;
@@ -602,6 +602,9 @@ int simsense_autotune(simsense_handle *h, const uint8_t *left, const uint8_t *ri
     h->profiling = false;
     float best_ms = 1e30f;
     simsense_batch_tuning best_t = h->tuning;
+    // candidates that launch the same thing are timed once and report that time: lane
+    // counts that run with the same one, sorted items for every blocks_per_cu above 0
+    std::map<std::pair<int, bool>, float> timed;
     int c = 0, rc = SIMSENSE_OK;
     for (int li = 0; li < 3 && rc == SIMSENSE_OK; ++li) {
         if (!horizontal_lanes_valid(h->Dpad, lanes[li])) continue;
@@ -611,18 +614,24 @@ int simsense_autotune(simsense_handle *h, const uint8_t *left, const uint8_t *ri
             t.horizontal_lanes = lanes[li];
             t.blocks_per_cu = bpc;
             rc = simsense_set_tuning(h, &t);
-            if (rc == SIMSENSE_OK) rc = enqueue_match(h, left, right, pitch, st);  // warm-up
             if (rc != SIMSENSE_OK) break;
-            if (hipEventRecord(e0, st) != hipSuccess) { rc = SIMSENSE_ERR_DEVICE; break; }
-            for (int r = 0; r < reps && rc == SIMSENSE_OK; ++r) rc = enqueue_match(h, left, right, pitch, st);
-            if (rc != SIMSENSE_OK) break;
-            float m = 0.0f;
-            if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                hipEventElapsedTime(&m, e0, e1) != hipSuccess) {
-                rc = SIMSENSE_ERR_DEVICE;
-                break;
+            const std::pair<int, bool> shape = h->sgbm ? std::make_pair(0, false)
+                                                       : std::make_pair(effective_lanes(h->Dpad, h->hlanes), bpc > 0);
+            if (!timed.count(shape)) {
+                rc = enqueue_match(h, left, right, pitch, st);  // warm-up
+                if (rc != SIMSENSE_OK) break;
+                if (hipEventRecord(e0, st) != hipSuccess) { rc = SIMSENSE_ERR_DEVICE; break; }
+                for (int r = 0; r < reps && rc == SIMSENSE_OK; ++r) rc = enqueue_match(h, left, right, pitch, st);
+                if (rc != SIMSENSE_OK) break;
+                float m = 0.0f;
+                if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                    hipEventElapsedTime(&m, e0, e1) != hipSuccess) {
+                    rc = SIMSENSE_ERR_DEVICE;
+                    break;
+                }
+                timed[shape] = m / (float)reps;
             }
-            m /= (float)reps;
+            const float m = timed[shape];
             if (ms && c < max_candidates) ms[c] = m;
             ++c;
             if (m < best_ms) {

@@ -42,6 +42,11 @@ int launch_lanes(int W, int dpad, int64_t total_work);
 // 770, 1863x1120 (2051) 867 / 925, 2062x1080 (2111) 905 / 989, 2055x1200 D = 128 (2227) 689 /
 // 762, 2379x1250 D = 192 1113 / 1141.
 int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums);
+// The lanes a tuning stands for (asked; 0 the default).  64 cannot be asked for with 96
+// disparities, which they do not divide, but are the default of launches short of rows
+// (100x201, 2 paths: 27 us a call, with 32 lanes 29, with 16 36): there 32 stand for them, or
+// every tuned handle would be slower than an untuned one.
+int chosen_lanes(int asked, int dpad, int by_default);
 int64_t aggregate_work(int W, int H, int dpad, int num_paths, bool sums);
 // Whether the vertical and diagonal directions read a cost volume by default, rather than
 // count census words.  Each of them reads it once, so a volume beyond the caches costs more

@@ -17,3 +17,33 @@ def test_default_of_rows_alone(orc, nat, H, D, kw):  # noqa: F811
 @pytest.mark.parametrize("W,H", [(1900, 1097), (1903, 1098)])
 def test_default_of_four_paths_from_words(orc, nat, W, H):  # noqa: F811
     check(orc, nat, W, H, 128, num_paths=4, p2=200)
+
+
+@pytest.mark.parametrize("D,lanes", [(60, (16, 32, 64)), (90, (16, 32)), (128, (16, 32, 64))])
+def test_autotune_times_each_launch_once(nat, D, lanes):  # noqa: F811
+    """Candidates that launch the same thing report one time: a handle's blocks_per_cu above
+    0, a batch's all, and 32 and 64 lanes of 64 disparities."""
+    import torch
+    p = dict(width=130, height=70, max_disp=D, census_w=7, census_h=9, census_mode=0, p1=7, p2=86, uniqueness_pct=10,
+             lr_max_diff=1, num_paths=8, median=3, subpixel=1, focal_px=400.0, baseline_m=0.055)
+    left = torch.randint(0, 256, (70, 130), dtype=torch.uint8, device="cuda")
+    right = torch.roll(left, -3, 1)
+    ss = nat.SimSense(p)
+    want = [t.clone() for t in ss(left, right)]
+    best, ms = ss.autotune(left, right, reps=3)
+    got = ss(left, right)
+    ss.close()
+    assert len(ms) == 5 * len(lanes) and best["horizontal_lanes"] in lanes
+    assert all(len(set(ms[i + 1:i + 5])) == 1 for i in range(0, len(ms), 5)), ms
+    assert D != 60 or ms[5:10] == ms[10:15]
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
+    b = nat.Batch([p, p])
+    outs = b.outputs()
+    best, ms = b.autotune([left] * 2, [right] * 2, outs, reps=3)
+    b.compute([left] * 2, [right] * 2, outs)
+    torch.cuda.synchronize()
+    assert len(ms) == 4 * len(lanes) and best["horizontal_lanes"] in lanes
+    assert all(len(set(ms[i:i + 4])) == 1 for i in range(0, len(ms), 4)), ms
+    assert D != 60 or ms[4:8] == ms[8:12]
+    assert all(torch.equal(o[k], w) for o in outs for k, w in zip(("depth", "disp", "flags"), want))
+    b.close()
