@@ -95,11 +95,12 @@ __device__ __forceinline__ void draws(const NoiseArgs &a, uint32_t i, float &gam
 // precision, and a bound on how far it lies from the one of draws(): false where a
 // decision of the gamma's rejection loop could differ.
 //
-// The bounds: with the hardware's log2, sqrt and cosine (of turns), over all 2^23
-// uniforms, sqrt(-2 log u) is off by at most 4.9e-7 (and at most 5.77), the cosine by
-// 1.3e-7, log u by 1.63e-7 of itself, and log v over all floats in [2^-10, 2^6) by
-// 1.4e-7 (1 + |log v|); so a normal is off by at most kEx.  Every product and sum adds
-// half a unit, kEps of its result, in either form.
+// The bounds, each the largest error against double precision over every value that can
+// occur: with the hardware's log2, sqrt and cosine (of turns), over all 2^23 uniforms,
+// sqrt(-2 log u) is off by at most 4.88e-7 (and at most 5.77), the cosine by 1.25e-7,
+// log u by 1.63e-7 of itself, and log v over all floats in [2^-14, 2^6) by 1.39e-7
+// (1 + |log v|) (v = t^3, 0.05 < t < 3.4: k >= 1); so a normal is off by at most kEx.
+// Every product and sum adds half a unit, kEps of its result, in either form.
 constexpr float kEps = 5.97e-8f, kEx = 1.7e-6f, kLog2 = 0.69314718055994531f;
 
 __device__ __forceinline__ float fast_u01(uint32_t x) { return ((float)(x >> 9) + 0.5f) * (1.0f / 8388608.0f); }  // exact
@@ -215,10 +216,14 @@ NoiseArgs noise_args(const simsense_noise_params &p, int64_t pixels = 0)
     // 45.5 / 28.5, 4096 45.1 / 39.5; 640x480 10.1 / 9.9 at 1024, 10.0 / 10.5 at 4096),
     // the image large enough that its waves wait for each other and not for the few that
     // draw twice (kernel alone: 320x240 7.0 / 6.1, 237x137 5.5 / 5.7, 171x134 without a
-    // gain 2.4 / 2.9)
+    // gain 2.4 / 2.9), the more of them the closer k is to 1, where t is often near 0 (in a
+    // graph, double / single: k 1 320x240 9.0 / 11.3, 560x420 15.0 / 15.3, 640x480 17.6 /
+    // 14.2; k 1.2 320x240 7.9 / 9.9, 480x360 10.4 / 11.1, 560x420 14.2 / 10.9; k 1.5 320x240
+    // 7.8 / 8.3, 400x300 9.1 / 7.7; k 2 320x240 7.8 / 7.1)
     const double spread = p.gain_model == 1 ? 2.0 * d * (double)p.theta : p.gain_model == 2 ? (double)p.gain_sd : 0.0;
     const bool shape = p.gain_model != 1 || p.k <= 1024.0f;
-    a.fast = pixels >= 65536 && shape && (double)p.scale * (255.0 * spread + (double)p.sigma + fabs((double)p.mu) / 8.0) * 2e-6 <= 2e-3;
+    const int64_t enough = p.gain_model != 1 || p.k >= 2.0f ? 65536 : p.k >= 1.25f ? 98304 : p.k >= 1.05f ? 180000 : 240000;
+    a.fast = pixels >= enough && shape && (double)p.scale * (255.0 * spread + (double)p.sigma + fabs((double)p.mu) / 8.0) * 2e-6 <= 2e-3;
     return a;
 }
 
