@@ -374,43 +374,47 @@ void launch_sel3(const SelectArgs *a, const SelectBatch *b, hipStream_t s)
                            select_lds_bytes<DPL>(b->max_width), s, *b);
 }
 
-// planes: one per direction (2, 4, 8), or the two horizontal ones and the sums of the
-// others' pairs (3, 5; byte sums only of small values), or sums only (2, 4)
+// planes: one per direction (2, 4, 8; 8 only of values too large for byte sums, 4 not of
+// 16-bit ones), or the two horizontal ones and the sums of the others' pairs (3, 5; byte sums
+// only of small values), or sums only (2, 4)
 template <int DPL, bool SMALL, bool V16>
-void launch_sel2(const SelectArgs *a, const SelectBatch *b, int nplanes, hipStream_t s)
+hipError_t launch_sel2(const SelectArgs *a, const SelectBatch *b, int nplanes, hipStream_t s)
 {
-    switch (nplanes) {
-    case 2: return launch_sel3<DPL, 2, SMALL, V16>(a, b, s);
-    case 4: return launch_sel3<DPL, 4, SMALL, V16>(a, b, s);
-    case 8: return launch_sel3<DPL, 8, SMALL, V16>(a, b, s);
-    default: break;
-    }
-
-    if constexpr (SMALL || V16) {
+    if (nplanes == 2) launch_sel3<DPL, 2, SMALL, V16>(a, b, s);
+    else if constexpr (!SMALL && !V16) {
+        if (nplanes == 4) launch_sel3<DPL, 4, SMALL, V16>(a, b, s);
+        else if (nplanes == 8) launch_sel3<DPL, 8, SMALL, V16>(a, b, s);
+        else return hipErrorInvalidValue;
+    } else {
         if (nplanes == 3) launch_sel3<DPL, 3, SMALL, V16>(a, b, s);
-        else launch_sel3<DPL, 5, SMALL, V16>(a, b, s);
+        else if (nplanes == 5) launch_sel3<DPL, 5, SMALL, V16>(a, b, s);
+        else if constexpr (SMALL) {
+            if (nplanes != 4) return hipErrorInvalidValue;
+            launch_sel3<DPL, 4, SMALL, V16>(a, b, s);
+        } else {
+            return hipErrorInvalidValue;
+        }
     }
+    return hipGetLastError();
 }
 template <int DPL>
-void launch_sel1(const SelectArgs *a, const SelectBatch *b, int nplanes, bool small, hipStream_t s)
+hipError_t launch_sel1(const SelectArgs *a, const SelectBatch *b, int nplanes, bool small, hipStream_t s)
 {
-    if (a && a->values16) launch_sel2<DPL, false, true>(a, b, nplanes, s);
-    else if (small) launch_sel2<DPL, true, false>(a, b, nplanes, s);
-    else launch_sel2<DPL, false, false>(a, b, nplanes, s);
+    if (a && a->values16) return launch_sel2<DPL, false, true>(a, b, nplanes, s);
+    return small ? launch_sel2<DPL, true, false>(a, b, nplanes, s) : launch_sel2<DPL, false, false>(a, b, nplanes, s);
 }
 hipError_t launch_sel(const SelectArgs *a, const SelectBatch *b, int dpad, int nplanes, bool small, hipStream_t s)
 {
     switch (dpad / kLanesPerLine) {
-    case 1: launch_sel1<1>(a, b, nplanes, small, s); break;
-    case 2: launch_sel1<2>(a, b, nplanes, small, s); break;
-    case 4: launch_sel1<4>(a, b, nplanes, small, s); break;
-    case 6: launch_sel1<6>(a, b, nplanes, small, s); break;
-    case 8: launch_sel1<8>(a, b, nplanes, small, s); break;
-    case 12: launch_sel1<12>(a, b, nplanes, small, s); break;
-    case 16: launch_sel1<16>(a, b, nplanes, small, s); break;
+    case 1: return launch_sel1<1>(a, b, nplanes, small, s);
+    case 2: return launch_sel1<2>(a, b, nplanes, small, s);
+    case 4: return launch_sel1<4>(a, b, nplanes, small, s);
+    case 6: return launch_sel1<6>(a, b, nplanes, small, s);
+    case 8: return launch_sel1<8>(a, b, nplanes, small, s);
+    case 12: return launch_sel1<12>(a, b, nplanes, small, s);
+    case 16: return launch_sel1<16>(a, b, nplanes, small, s);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 }  // namespace
 
