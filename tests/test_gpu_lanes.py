@@ -47,3 +47,35 @@ def test_autotune_times_each_launch_once(nat, D, lanes):  # noqa: F811
     assert D != 60 or ms[4:8] == ms[8:12]
     assert all(torch.equal(o[k], w) for o in outs for k, w in zip(("depth", "disp", "flags"), want))
     b.close()
+
+
+@pytest.mark.parametrize("D", [256, 250])
+def test_row_sums_of_four_paths(orc, nat, D):  # noqa: F811
+    """Two planes, both sums, from a volume large enough that 16 lanes store the rows as
+    their sum; and the default shape, whose rows are planes of their own."""
+    check(orc, nat, 1411, 771, D, tunings=((16, 3), (0, 3)), num_paths=4)
+
+
+def test_row_sums_in_a_batch(nat):  # noqa: F811
+    """Slots with rows as sums beside slots without, of 8 and 4 paths: equal to single pairs
+    whose rows are planes of their own (32 lanes)."""
+    import torch
+    ps = [dict(width=W, height=H, max_disp=D, census_w=7, census_h=9, census_mode=0, p1=7, p2=86, uniqueness_pct=10,
+               lr_max_diff=1, num_paths=paths, median=3, subpixel=1, focal_px=400.0, baseline_m=0.055)
+          for W, H, D, paths in ((1411, 771, 256, 8), (200, 90, 256, 8), (1411, 771, 250, 4), (150, 101, 256, 4))]
+    g = torch.Generator(device="cuda").manual_seed(6)
+    lefts = [torch.randint(0, 256, (p["height"], p["width"]), generator=g, dtype=torch.uint8, device="cuda") for p in ps]
+    rights = [torch.roll(a, -7, 1) for a in lefts]
+    b = nat.Batch(ps)
+    b.set_tuning(16, 2)
+    outs = b.outputs()
+    for rep in range(2):
+        b.compute(lefts, rights, outs)
+        torch.cuda.synchronize()
+        for i, (p, o) in enumerate(zip(ps, outs)):
+            ss = nat.SimSense(p)
+            ss.set_tuning(32, 3)
+            for k, t in zip(("depth", "disp", "flags"), ss(lefts[i], rights[i])):
+                assert torch.equal(o[k], t), (rep, i, k)
+            ss.close()
+    b.close()
