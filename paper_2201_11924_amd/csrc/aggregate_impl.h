@@ -18,8 +18,8 @@
 // The lanes keep un-normalised sums
 //   U(p,d) = C(p,d) + min(U(p-r,d), U(p-r,d+-1) + P1, u + P2),  u = min_k U(p-r,k),
 // for which induction gives L_r(p,d) = U(p,d) - u exactly, so a step that stores
-// nothing needs no normalisation; U is brought back to U - u once per segment of
-// kSeg steps (16-bit block costs, whose sums grow faster, every step).  All values
+// nothing needs no normalisation; U is brought back to U - u every 8 or 16 steps
+// (16-bit block costs, whose sums grow faster, every step).  All values
 // stay below 0x7C00, where 16-bit patterns order the same as half floats and as
 // integers, so three-way minima use v_pk_minimum3_f16 (no value is ever a NaN
 // or changed by it).
@@ -1150,7 +1150,6 @@ __global__ __launch_bounds__(256) void cost_queue_kernel(AggregateQueue q)
 }
 
 // ---------------------------------------------------------------- the aggregation launch
-// One wave's lines: item `item` of the slot (a running number over its units).
 // Steps between two states of a pair: 8, or 4 where the forward values of 8 steps
 // would not fit the registers.
 constexpr int sum_steps(int dpl, bool v16) { return v16 && dpl >= 12 ? 4 : 8; }

@@ -544,32 +544,32 @@ int simsense_batch_create(const simsense_params *params, int32_t n, simsense_bat
     b->tuning.blocks_per_cu = 2;
     // (spare: with the cost-volume buffers of slots whose directions fill all others)
     auto lay_out = [&](bool spare) {
-      size_t total = 0;
-      for (int s = 0; s < n; ++s) {
-        Slot &sl = b->slots[s];
-        sl.p = params[s];
-        sl.bits = census_bits(sl.p.census_w, sl.p.census_h, sl.p.census_mode);
-        sl.wide = sl.bits > 32;
-        sl.small = sums_fit(&sl.p);
-        sl.Dpad = padded_disp(sl.p.max_disp);
-        sl.costs = default_costs(&sl.p) && (spare || sl.small || costs_in_place(sl.Dpad, sl.wide));
-        sl.sums = sl.costs && sl.small;
-        sl.ndirs = sl.p.num_paths;
-        const size_t npx = (size_t)sl.p.width * sl.p.height;
-        auto take = [&](size_t bytes) { size_t o = total; total += a256(bytes); return o; };
-        sl.off_census_l = take(npx * (sl.wide ? 8 : 4));
-        sl.off_census_r = take(npx * (sl.wide ? 8 : 4));
-        sl.nbuffers = path_buffers(sl.ndirs, sl.costs, sl.sums, spare);
-        for (int r = 0; r < sl.nbuffers; ++r) sl.off_paths[r] = take((npx + 1) * sl.Dpad);
-        sl.off_dint = take(npx);
-        sl.off_s1 = take(npx * 2);
-        sl.off_s2 = take(npx * 2);
-        sl.off_dright = take(npx);
-        sl.off_dsub = take(npx * 4);
-        sl.off_masked = take(npx * 4);
-        sl.off_flags = take(npx);
-      }
-      b->scratch_bytes = total;
+        size_t total = 0;
+        for (int s = 0; s < n; ++s) {
+            Slot &sl = b->slots[s];
+            sl.p = params[s];
+            sl.bits = census_bits(sl.p.census_w, sl.p.census_h, sl.p.census_mode);
+            sl.wide = sl.bits > 32;
+            sl.small = sums_fit(&sl.p);
+            sl.Dpad = padded_disp(sl.p.max_disp);
+            sl.costs = default_costs(&sl.p) && (spare || sl.small || costs_in_place(sl.Dpad, sl.wide));
+            sl.sums = sl.costs && sl.small;
+            sl.ndirs = sl.p.num_paths;
+            const size_t npx = (size_t)sl.p.width * sl.p.height;
+            auto take = [&](size_t bytes) { size_t o = total; total += a256(bytes); return o; };
+            sl.off_census_l = take(npx * (sl.wide ? 8 : 4));
+            sl.off_census_r = take(npx * (sl.wide ? 8 : 4));
+            sl.nbuffers = path_buffers(sl.ndirs, sl.costs, sl.sums, spare);
+            for (int r = 0; r < sl.nbuffers; ++r) sl.off_paths[r] = take((npx + 1) * sl.Dpad);
+            sl.off_dint = take(npx);
+            sl.off_s1 = take(npx * 2);
+            sl.off_s2 = take(npx * 2);
+            sl.off_dright = take(npx);
+            sl.off_dsub = take(npx * 4);
+            sl.off_masked = take(npx * 4);
+            sl.off_flags = take(npx);
+        }
+        b->scratch_bytes = total;
     };
     int rc = SIMSENSE_OK;
     lay_out(true);

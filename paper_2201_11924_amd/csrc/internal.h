@@ -281,7 +281,7 @@ struct SelectBatch {
 constexpr int kPostTileRows = 16;  // rows of a batch's post tile (64 columns)
 struct PostBatch {
     const PostArgs *slots;
-    const uint32_t *items;  // slot << 20 | tile (64x4 tiles, row-major)
+    const uint32_t *items;  // slot << 20 | tile (64 x kPostTileRows, row-major)
     int nitems;
 };
 hipError_t launch_census_batch(const CensusBatch &b, bool out64, hipStream_t s);
