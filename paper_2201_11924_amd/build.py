@@ -35,8 +35,11 @@ FLAGS = [
 # The aggregation's steps are serial chains with DPP moves, which need idle issue
 # slots after the instruction that makes their source: the ILP scheduler fills them
 # with other steps' independent work (the default one, after low register counts,
-# leaves 3 times the s_nops).
-_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+# leaves 3 times the s_nops).  Loops start on a cache line: where a kernel's loops fall
+# otherwise moves with every instruction before them (one s_nop at the kernel's start:
+# 320x240, D = 64 53.2 -> 52.4 us a call, 500x375, D = 48 99.8 -> 101.6; three: 960x540,
+# D = 96 171 -> 175; aligned 52.9, 100.0, 171).
+_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp", "-falign-loops=64"]
 FILE_FLAGS = {
     "net_infer.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "sgbm.hip": _ILP,
