@@ -70,7 +70,7 @@ int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums)
 {
     if (num_paths == 2 && dpad < 256) return H > kSimds ? 16 : 2 * H > kSimds ? 32 : 64;
     const int hl = launch_lanes(W, dpad, aggregate_work(W, H, dpad, num_paths, sums));
-    return num_paths == 4 && !costs && hl == 32 && H + W / 2 > 2 * kSimds ? 16 : hl;
+    return num_paths == 4 && !costs && dpad < 256 && hl == 32 && H > kSimds && H + W / 2 > 2 * kSimds ? 16 : hl;
 }
 
 int chosen_lanes(int asked, int dpad, int by_default)

@@ -37,10 +37,11 @@ int launch_lanes(int W, int dpad, int64_t total_work);
 // 159, 154x598 D = 160 64 / 51 / 56, 804x837 D = 96 174 / 140 / 156, 686x1052 D = 192 217 /
 // 226 / 274, 1539x1041 D = 160 570 / 581 / 732, 1812x1307 D = 96 420 / 434 (with 256 the wider
 // forms stay level: 686x871 285 / 219 / 224, 1190x1608 568 / 563 / 658).  4 paths that count
-// census words gain nothing from 32 lanes where the rows' waves and the columns' (H + W / 2)
-// come to more than two per SIMD: 1920x1080 D = 192 (2040) 856 / 757, 1749x1160 (2034) 856 /
-// 770, 1863x1120 (2051) 867 / 925, 2062x1080 (2111) 905 / 989, 2055x1200 D = 128 (2227) 689 /
-// 762, 2379x1250 D = 192 1113 / 1141.
+// census words of up to 192 disparities gain nothing from 32 lanes where the rows have more
+// than one wave a SIMD (H > 1024) and rows and columns together (H + W / 2) more than two:
+// 1920x1080 D = 192 (2040) 856 / 757, 1749x1160 (2034) 856 / 770, 1863x1120 (2051) 867 / 925,
+// 2062x1080 (2111) 905 / 989, 2055x1200 D = 128 (2227) 689 / 762, 2379x1250 D = 192 1113 /
+// 1141; but 3715x658 D = 256 (2515) 1589 / 1330.
 int default_lanes(int W, int H, int dpad, int num_paths, bool costs, bool sums);
 // The lanes a tuning stands for (asked; 0 the default).  64 cannot be asked for with 96
 // disparities, which they do not divide, but are the default of launches short of rows
